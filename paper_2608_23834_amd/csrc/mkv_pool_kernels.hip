@@ -9,6 +9,8 @@
 // is compiled with -ffp-contract=off.
 #include <hip/hip_runtime.h>
 
+#include <type_traits>
+
 #include "mkv_append.h"
 #include "mkv_internal.h"
 #include "../../include/minima_kv.h"
@@ -24,126 +26,214 @@ static int grid_for(int64_t items, int cap) {
 // ===========================================================================
 
 // One workgroup: validate the whole call, then hand out FP8 ids in ascending
-// (request, page) order and list every page that receives tokens.
-__global__ __launch_bounds__(1024) void append_plan_kernel(int n_req, int32_t* bt, uint8_t* tags,
-                                                           int max_pages, const int32_t* sb,
-                                                           const int32_t* cu, int32_t* ctrl,
-                                                           const int32_t* fp8_stack, int32_t* list,
-                                                           int n_fp8, int n_new_total, int32_t* rc8) {
+// (request, page) order and list every page that receives tokens.  The touched
+// pages of up to PLAN_NT requests form one run of entries, PLAN_KB consecutive
+// ones per thread (request found by a binary search in the run's prefix sums,
+// then stepped), every table load of a batch in flight together: the cost is
+// round trips, so requests are not walked one after the other.  A call whose
+// entries fit one batch (most prompts of a few requests) is loaded once,
+// validated and listed after one scan; a longer one takes a validating pass
+// and a listing pass.
+constexpr int PLAN_NT = 1024, PLAN_KB = 4;
+constexpr int PLAN_BATCH = PLAN_NT * PLAN_KB;
+__global__ __launch_bounds__(PLAN_NT) void append_plan_kernel(int n_req, int32_t* bt, uint8_t* tags,
+                                                              int max_pages, const int32_t* sb,
+                                                              const int32_t* cu, int32_t* ctrl,
+                                                              const int32_t* fp8_stack, int32_t* list,
+                                                              int n_fp8, int n_new_total, int32_t* rc8) {
   __shared__ int scratch[32];
-  __shared__ int s_err, s_need, s_touch;
+  __shared__ int s_err, s_need;
+  __shared__ int s_base[PLAN_NT], s_p0[PLAN_NT];  // per request of the run: first entry, first page
   const int tid = threadIdx.x;
   if (tid == 0) {
-    s_err = 0; s_need = 0; s_touch = 0;
-    // rows of request r are cu[r] .. cu[r+1]-1 of an n_new_total-row input
-    if (cu[0] != 0 || cu[n_req] != n_new_total) s_err = MKV_DEVERR_RANGE;
-  }
-  __syncthreads();
-  for (int r = 0; r < n_req; ++r) {
-    const int n = cu[r + 1] - cu[r], s0 = sb[r];
-    if (n < 0 || s0 < 0) {
-      if (tid == 0) atomicOr(&s_err, (int)MKV_DEVERR_RANGE);
-      continue;
-    }
-    if (n == 0) continue;
-    const int p0 = s0 / PAGE, p1 = (s0 + n - 1) / PAGE;
-    if (p1 >= max_pages) {
-      if (tid == 0) atomicOr(&s_err, (int)MKV_DEVERR_RANGE);
-      continue;
-    }
-    int need = 0, bad = 0;
-    for (int p = p0 + tid; p <= p1; p += blockDim.x) {
-      const int64_t i = (int64_t)r * max_pages + p;
-      if (bt[i] < 0) need++;
-      else if (tags[i] != TAG_R) bad |= MKV_DEVERR_NOT_RECENT;
-      else if (bt[i] >= n_fp8) bad |= MKV_DEVERR_RANGE;
-    }
-    if (need) atomicAdd(&s_need, need);
-    if (bad) atomicOr(&s_err, bad);
-    if (tid == 0) s_touch += p1 - p0 + 1;
+    s_err = 0;
+    s_need = 0;
   }
   __syncthreads();
   const int top = ctrl[CTRL_FP8_TOP];
-  if (tid == 0) {
-    if (s_err == 0 && s_need > top) s_err |= MKV_DEVERR_FP8_EXHAUSTED;
-    if (s_err == 0 && s_touch > n_fp8) s_err |= MKV_DEVERR_RANGE;
+  int err = 0;
+  // rows of request r are cu[r] .. cu[r+1]-1 of an n_new_total-row input
+  if (tid == 0 && (cu[0] != 0 || cu[n_req] != n_new_total)) err = MKV_DEVERR_RANGE;
+  // requests r0 .. r0 + PLAN_NT - 1 -> their run of entries; returns its length
+  auto load_run = [&](int r0) {
+    const int r = r0 + tid;
+    int touch = 0, p0 = 0;
+    if (r < n_req) {
+      const int n = cu[r + 1] - cu[r], s0 = sb[r];
+      if (n < 0 || s0 < 0) {
+        err |= MKV_DEVERR_RANGE;
+      } else if (n > 0) {
+        p0 = s0 / PAGE;
+        const int p1 = (int)(((int64_t)s0 + n - 1) / PAGE);
+        if (p1 >= max_pages) err |= MKV_DEVERR_RANGE;
+        else touch = p1 - p0 + 1;
+      }
+    }
+    int total;
+    s_base[tid] = block_excl_scan(touch, scratch, &total);
+    s_p0[tid] = p0;
+    __syncthreads();
+    return total;
+  };
+  int e_r[PLAN_KB], e_p[PLAN_KB], e_id[PLAN_KB];  // request (-1: no entry), page, table entry
+  // entries e0 + PLAN_KB tid .. of the run; counts the unmapped ones
+  auto load_batch = [&](int r0, int e0, int total) {
+    const int f0 = e0 + PLAN_KB * tid;
+    int lo = 0, hi = min(n_req - r0, PLAN_NT) - 1;  // the last request whose first entry is <= f0
+    while (lo < hi) {
+      const int mid = (lo + hi + 1) >> 1;
+      if (s_base[mid] <= f0) lo = mid;
+      else hi = mid - 1;
+    }
+    const int nr = min(n_req - r0, PLAN_NT);
+    int tg[PLAN_KB];
+#pragma unroll
+    for (int j = 0; j < PLAN_KB; ++j) {
+      const int f = f0 + j;
+      while (lo + 1 < nr && s_base[lo + 1] <= f) ++lo;  // (requests without entries are stepped over)
+      const bool in = f < total;
+      e_r[j] = in ? r0 + lo : -1;
+      e_p[j] = in ? s_p0[lo] + (f - s_base[lo]) : 0;
+      const int64_t i = in ? (int64_t)e_r[j] * max_pages + e_p[j] : 0;
+      e_id[j] = bt[i];
+      tg[j] = tags[i];
+    }
+    int fresh = 0;
+#pragma unroll
+    for (int j = 0; j < PLAN_KB; ++j) {
+      if (e_r[j] < 0) continue;
+      if (e_id[j] < 0) ++fresh;
+      else if (tg[j] != TAG_R) err |= MKV_DEVERR_NOT_RECENT;
+      else if (e_id[j] >= n_fp8) err |= MKV_DEVERR_RANGE;
+    }
+    return fresh;
+  };
+  // the batch's list entries from base_list + e0 on, fresh ids from rank on
+  auto write_batch = [&](int base_list, int e0, int rank) {
+#pragma unroll
+    for (int j = 0; j < PLAN_KB; ++j) {
+      if (e_r[j] < 0) continue;
+      int id = e_id[j];
+      if (id < 0) {
+        const int64_t i = (int64_t)e_r[j] * max_pages + e_p[j];
+        id = fp8_stack[top - 1 - rank++];
+        bt[i] = id;
+        tags[i] = TAG_R;
+        rc8[id] = 1;  // one request reference
+      }
+      int32_t* e = list + 4LL * (base_list + e0 + PLAN_KB * tid + j);
+      e[0] = e_r[j];
+      e[1] = e_p[j];
+      e[2] = id;
+      e[3] = 0;
+    }
+  };
+  int64_t n_list = 0;
+  int fresh = 0, need = 0, rank = 0;
+  bool one = false;  // the whole call is one batch, kept in registers
+  for (int r0 = 0; r0 < n_req; r0 += PLAN_NT) {
+    const int total = load_run(r0);
+    one = n_req <= PLAN_NT && total <= PLAN_BATCH;
+    for (int e0 = 0; e0 < total; e0 += PLAN_BATCH) fresh += load_batch(r0, e0, total);
+    n_list += total;
+    if (r0 + PLAN_NT < n_req) __syncthreads();  // the run's arrays are free
   }
-  __syncthreads();
-  if (s_err) {
+  if (err) atomicOr(&s_err, err);
+  if (one) {
+    rank = block_excl_scan(fresh, scratch, &need);  // its barriers also publish s_err
+  } else {
+    if (fresh) atomicAdd(&s_need, fresh);
+    __syncthreads();
+    need = s_need;
+  }
+  err = s_err;
+  if (err == 0 && need > top) err |= MKV_DEVERR_FP8_EXHAUSTED;
+  if (err == 0 && n_list > n_fp8) err |= MKV_DEVERR_RANGE;
+  if (err) {
     if (tid == 0) {
-      atomicOr(&ctrl[CTRL_ERR], s_err);
+      atomicOr(&ctrl[CTRL_ERR], err);
       ctrl[CTRL_ABORT] = 1;
       ctrl[CTRL_NLIST] = 0;
     }
     return;
   }
-  int base_alloc = 0, base_list = 0;
-  for (int r = 0; r < n_req; ++r) {
-    const int n = cu[r + 1] - cu[r], s0 = sb[r];
-    if (n <= 0) continue;
-    const int p0 = s0 / PAGE, p1 = (s0 + n - 1) / PAGE;
-    for (int c0 = p0; c0 <= p1; c0 += blockDim.x) {
-      const int p = c0 + tid;
-      const bool in = p <= p1;
-      const int64_t i = (int64_t)r * max_pages + p;
-      const int unm = (in && bt[i] < 0) ? 1 : 0;
-      int tot;
-      const int rank = block_excl_scan(unm, scratch, &tot);
-      if (in) {
-        int id;
-        if (unm) {
-          id = fp8_stack[top - 1 - (base_alloc + rank)];
-          bt[i] = id;
-          tags[i] = TAG_R;
-          rc8[id] = 1;  // one request reference
-        } else {
-          id = bt[i];
-        }
-        int32_t* e = list + 4LL * (base_list + (p - p0));
-        e[0] = r;
-        e[1] = p;
-        e[2] = id;
-        e[3] = 0;
+  if (one) {
+    write_batch(0, 0, rank);
+  } else {
+    int base_list = 0, base_fresh = 0;
+    for (int r0 = 0; r0 < n_req; r0 += PLAN_NT) {
+      __syncthreads();
+      const int total = load_run(r0);
+      for (int e0 = 0; e0 < total; e0 += PLAN_BATCH) {
+        const int c = load_batch(r0, e0, total);
+        int tot;
+        const int pre = block_excl_scan(c, scratch, &tot);
+        write_batch(base_list, e0, base_fresh + pre);
+        base_fresh += tot;
       }
-      base_alloc += tot;
+      base_list += total;
     }
-    base_list += p1 - p0 + 1;
   }
   if (tid == 0) {
-    ctrl[CTRL_FP8_TOP] = top - base_alloc;
-    ctrl[CTRL_NLIST] = base_list;
+    ctrl[CTRL_FP8_TOP] = top - need;
+    ctrl[CTRL_NLIST] = (int)n_list;
     ctrl[CTRL_ABORT] = 0;
   }
 }
 
+// x / s correctly rounded, for a fixed divisor whose correctly rounded
+// reciprocal y = 1 / s is at hand: a Newton step on the quotient, then Markstein's
+// final step (with y correctly rounded and q within an ulp of x / s, q + (x - q s)
+// y rounds to the correctly rounded quotient).  Needs the remainders exact: div_fast(s).
+// A quotient small enough to lose them is far below every E4M3 code's rounding
+// boundary; its sign is x's (a zero quotient included).
+__device__ __forceinline__ float div_by(float x, float s, float y) {
+  float q = x * y;
+  q = __builtin_fmaf(__builtin_fmaf(-q, s, x), y, q);
+  q = __builtin_fmaf(__builtin_fmaf(-q, s, x), y, q);
+  return __builtin_copysignf(q, x);
+}
+__device__ __forceinline__ bool div_fast(float s) { return s >= 0x1p-60f && s <= 0x1p60f; }
+// four fp32 values -> four E4M3 bytes, as f32_to_e4m3
+__device__ __forceinline__ uint32_t pack_e4m3(float a, float b, float c, float d) {
+  auto sat = [](float x) { return fminf(fmaxf(x, -448.0f), 448.0f); };
+  const int lo = __builtin_amdgcn_cvt_pk_fp8_f32(sat(a), sat(b), 0, false);
+  return (uint32_t)__builtin_amdgcn_cvt_pk_fp8_f32(sat(c), sat(d), lo, true);
+}
 
 // Quantize one tensor (K or V) of one page-head with one wave.  Slots [0, t0)
-// already hold codes with the page's scale; the new fp32 values are rows
+// already hold codes with the page's scale; the new bf16 values are rows
 // row0 + t (t in [t0, t1)) of src, [row][H][D].  The scale only grows: when the
 // new amax exceeds 448 * s_old the old codes are re-rounded to the new scale.
-// All loads are issued before any store so that one wave needs about one
-// memory round trip (plus one more when old codes are re-rounded).
-template <int D>
-__device__ void quant_task(uint8_t* reg, float* sc, int kv, const uint16_t* src, int64_t row0,
-                           int t0, int t1, int H, int h, int lane) {
-  constexpr int CL = D / 16, D4 = D / 4, NC = PAGE * D4 / 64;  // NC uint2 per lane at most
-  const uint16_t* srow = src + (row0 * H + h) * D;  // token t at srow[t * H * D + c]
+// Lane l holds channels 4 (l % (D/4)) .. + 3 of NT consecutive tokens, so it has
+// every byte of its K dwords (one token, four channels) and of its V dwords (one
+// channel, the four tokens of a group; four consecutive dwords per group, see
+// fp8_off): all stores are whole dwords.  A page that already holds tokens
+// (t0 > 0) has its old dwords loaded beside the new rows.  The bound is memory:
+// 32 K tokens x 4 heads x 4 layers read 134 MB and write 67 MB per tensor pair
+// and layer; storing V byte by byte the launch took 367 us.
+template <int D, bool kv>
+__device__ __forceinline__ void quant_task(uint8_t* reg, float* sc, const uint16_t* src, int64_t row0,
+                                           int t0, int t1, int H, int h, int lane) {
+  constexpr int CL = D / 16, D4 = D / 4, NT = PAGE * D4 / 64, NG = NT / 4;
+  const int cg = lane % D4, tb = (lane / D4) * NT;  // channel group, first token
+  const uint16_t* srow = src + (row0 * H + h) * D + 4 * cg;  // token t at srow[t * H * D]
   const int64_t tstride = (int64_t)H * D;
+  uint32_t* rw = reinterpret_cast<uint32_t*>(reg + (kv ? PAGE * D : 0));
+  // K: dword of token t at t D4 + cg; V: the dwords of token group g at
+  // ((r 4 + g) CL + m), r = 4 cg / CL, m = 4 cg % CL .. + 3
+  uint4* rv = reinterpret_cast<uint4*>(rw) + (4 * cg / CL) * CL + (4 * cg % CL) / 4;  // group g: + g CL / 4
   const float s_old = t0 > 0 ? sc[kv] : 0.0f;
-  const int n4 = (t1 - t0) * D4;  // new inputs, 4 channels per item
-  uint2 x[NC];
+  uint2 x[NT];
+#pragma unroll
+  for (int k = 0; k < NT; ++k) {
+    const int t = tb + k;
+    x[k] = make_uint2(0u, 0u);
+    if (t >= t0 && t < t1) x[k] = *reinterpret_cast<const uint2*>(srow + t * tstride);
+  }
   float amax = 0.0f;
 #pragma unroll
-  for (int k = 0; k < NC; ++k) {
-    const int idx = lane + 64 * k;
-    x[k] = make_uint2(0u, 0u);
-    if (idx < n4) {
-      const int t = t0 + idx / D4, c = 4 * (idx % D4);
-      x[k] = *reinterpret_cast<const uint2*>(srow + t * tstride + c);
-    }
-  }
-#pragma unroll
-  for (int k = 0; k < NC; ++k) {
+  for (int k = 0; k < NT; ++k) {
     amax = fmaxf(amax, fmaxf(fmaxf(fabsf(__uint_as_float(x[k].x << 16)),
                                    fabsf(__uint_as_float(x[k].x & 0xFFFF0000u))),
                              fmaxf(fabsf(__uint_as_float(x[k].y << 16)),
@@ -159,71 +249,88 @@ __device__ void quant_task(uint8_t* reg, float* sc, int kv, const uint16_t* src,
     s_new = amax / 448.0f;
     requant = true;
   }
-  uint32_t* rw = reinterpret_cast<uint32_t*>(reg + (kv ? PAGE * D : 0));
-  if (requant) {
-    // dwords holding old codes: K rows t < t0; V token groups g < ceil(t0/4)
-    const int gn = (t0 + 3) / 4;  // V dwords of token groups g < gn: 16 * gn * CL = gn * D
-    const int n_old = kv ? gn * D : t0 * D4;
-    uint32_t ow[NC];
+  // four channels of token tb + k
+  auto f4 = [&](int k, int b) {
+    const uint32_t w = b < 2 ? x[k].x : x[k].y;
+    return __uint_as_float(b & 1 ? w & 0xFFFF0000u : w << 16);
+  };
+  if (__builtin_amdgcn_readfirstlane(div_fast(s_new) && !requant)) {
+    const float y = 1.0f / s_new;
+    const bool whole = __builtin_amdgcn_readfirstlane(t0 == 0 && t1 == PAGE);
 #pragma unroll
-    for (int k = 0; k < NC; ++k) {
-      const int w = lane + 64 * k;
-      const int wi = kv ? (w / (CL * gn)) * 4 * CL + (w % (CL * gn)) : w;
-      ow[k] = w < n_old ? rw[wi] : 0u;
-    }
+    for (int j = 0; j < NG; ++j) {
+      const int ta = tb + 4 * j;  // the group's first token
+      float q[4][4];              // [token][channel]
 #pragma unroll
-    for (int k = 0; k < NC; ++k) {
-      const int w = lane + 64 * k;
-      if (w < n_old) {
-        const int wi = kv ? (w / (CL * gn)) * 4 * CL + (w % (CL * gn)) : w;
-        const int g = (wi / CL) % 4;
-        uint32_t outw = 0;
+      for (int u = 0; u < 4; ++u)
 #pragma unroll
-        for (int b = 0; b < 4; ++b) {
-          const int t = kv ? 4 * g + b : wi / D4;
-          uint32_t code = (ow[k] >> (8 * b)) & 0xFFu;
-          if (t < t0) code = f32_to_e4m3((e4m3_to_f32(code) * s_old) / s_new);
-          outw |= code << (8 * b);
+        for (int b = 0; b < 4; ++b) q[u][b] = div_by(f4(4 * j + u, b), s_new, y);
+      // the group's dwords: K dword u = token ta + u, V dword b = channel 4 cg + b
+      uint32_t w[4];
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        w[i] = kv ? pack_e4m3(q[0][i], q[1][i], q[2][i], q[3][i]) : pack_e4m3(q[i][0], q[i][1], q[i][2], q[i][3]);
+      if (kv) {
+        uint4* dst = rv + (ta / 4) * (CL / 4);
+        if (!whole) {  // bytes of tokens [t0, t1) are new; others old, or zero in a fresh page
+          uint32_t m = 0;
+#pragma unroll
+          for (int u = 0; u < 4; ++u) m |= ta + u >= t0 && ta + u < t1 ? 0xFFu << (8 * u) : 0u;
+          const uint4 o = t0 > 0 ? *dst : make_uint4(0u, 0u, 0u, 0u);
+          w[0] = (w[0] & m) | (o.x & ~m);
+          w[1] = (w[1] & m) | (o.y & ~m);
+          w[2] = (w[2] & m) | (o.z & ~m);
+          w[3] = (w[3] & m) | (o.w & ~m);
         }
-        rw[wi] = outw;
-      }
-    }
-    __builtin_amdgcn_s_waitcnt(0);  // re-rounded dwords land before new-code byte stores
-  }
-  // new codes
-#pragma unroll
-  for (int k = 0; k < NC; ++k) {
-    const int idx = lane + 64 * k;
-    if (idx < n4) {
-      const int t = t0 + idx / D4, c = 4 * (idx % D4);
-      uint32_t code[4];
-      const uint32_t hv[4] = {x[k].x << 16, x[k].x & 0xFFFF0000u, x[k].y << 16, x[k].y & 0xFFFF0000u};
-#pragma unroll
-      for (int b = 0; b < 4; ++b)
-        code[b] = s_new > 0.0f ? f32_to_e4m3(__uint_as_float(hv[b]) / s_new) : 0u;
-      if (!kv) {
-        rw[(t * D + c) / 4] = code[0] | (code[1] << 8) | (code[2] << 16) | (code[3] << 24);
+        *dst = make_uint4(w[0], w[1], w[2], w[3]);
       } else {
 #pragma unroll
-        for (int b = 0; b < 4; ++b) reg[fp8_off<D>(1, t, c + b)] = (uint8_t)code[b];
-      }
-    }
-  }
-  // a fresh page: zero every slot past the new tokens
-  if (t0 == 0 && t1 < PAGE) {
-    if (!kv) {
-      for (int w = t1 * D4 + lane; w < PAGE * D4; w += 64) rw[w] = 0u;
-    } else {
-      for (int w = lane; w < PAGE * D4; w += 64) {
-        const int g = (w / CL) % 4;
-        if (4 * g >= t1) {
-          rw[w] = 0u;
-        } else if (4 * g + 4 > t1) {
-#pragma unroll
-          for (int b = 0; b < 4; ++b)
-            if (4 * g + b >= t1) reg[PAGE * D + 4 * w + b] = 0;
+        for (int u = 0; u < 4; ++u) {
+          const int t = ta + u;
+          const bool nw = whole || (t >= t0 && t < t1);
+          if (nw || t0 == 0) rw[t * D4 + cg] = nw ? w[u] : 0u;
         }
       }
+    }
+  } else {
+    // old codes to re-round, or a scale without a fast division: rare, so one
+    // body for the groups; group j is in x[0 .. 3], the later ones move down after it
+#pragma unroll 1
+    for (int j = 0; j < NG; ++j) {
+      const int ta = tb + 4 * j;
+      // the group's dwords: K dword u = token ta + u, V dword b = channel 4 cg + b
+      uint32_t w[4] = {0u, 0u, 0u, 0u};
+      if (t0 > 0) {  // old codes, re-rounded when the scale grew; none in a fresh page
+        if (kv) {
+          const uint4 o = rv[(ta / 4) * (CL / 4)];
+          w[0] = o.x; w[1] = o.y; w[2] = o.z; w[3] = o.w;
+        } else {
+#pragma unroll
+          for (int u = 0; u < 4; ++u) w[u] = rw[(ta + u) * D4 + cg];
+        }
+      }
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        uint32_t o = 0;
+#pragma unroll
+        for (int b = 0; b < 4; ++b) {
+          const int u = kv ? b : i, t = ta + u;  // token of byte b of dword i
+          const float xv = kv ? f4(b, i) : f4(i, b);
+          const uint32_t code = (w[i] >> (8 * b)) & 0xFFu;
+          const bool nw = t >= t0 && t < t1, re = requant && t < t0;
+          const uint32_t c = f32_to_e4m3((nw ? xv : e4m3_to_f32(code) * s_old) / s_new);
+          o |= (re || (nw && s_new > 0.0f) ? c : nw ? 0u : code) << (8 * b);
+        }
+        w[i] = o;
+      }
+      if (kv) {
+        rv[(ta / 4) * (CL / 4)] = make_uint4(w[0], w[1], w[2], w[3]);
+      } else {
+#pragma unroll
+        for (int u = 0; u < 4; ++u) rw[(ta + u) * D4 + cg] = w[u];
+      }
+#pragma unroll
+      for (int k = 0; k + 4 < NT; ++k) x[k] = x[k + 4];
     }
   }
   if (lane == 0) sc[kv] = s_new;
@@ -248,8 +355,12 @@ __device__ __forceinline__ void run_quant_task(const PoolView& P, int64_t task, 
   const int64_t ph = ((int64_t)layer * P.n_fp8 + id) * H + h;
   const int64_t row0 = (int64_t)cu[r] + p * PAGE - s0;  // input row of slot t is row0 + t
   const uint16_t* src = (kv ? v : k) + (int64_t)li * n_new_total * H * D;
-  quant_task<D>(P.fp8 + ph * fp8_region_bytes(D), P.fp8_scales + ph * 2, kv, src, row0, t0, t1, H,
-                h, lane);
+  uint8_t* reg = P.fp8 + ph * fp8_region_bytes(D);
+  float* sc = P.fp8_scales + ph * 2;
+  if (kv)
+    quant_task<D, true>(reg, sc, src, row0, t0, t1, H, h, lane);
+  else
+    quant_task<D, false>(reg, sc, src, row0, t0, t1, H, h, lane);
 }
 
 // Quantize every listed page-head of every requested layer (grid-stride over
@@ -261,7 +372,7 @@ __global__ __launch_bounds__(256) void append_quant_kernel(PoolView P, int layer
                                                            const uint16_t* v) {
   if (P.ctrl[CTRL_ABORT]) return;
   const int64_t n_tasks = (int64_t)P.ctrl[CTRL_NLIST] * n_lcall * P.n_kv_heads * 2;
-  const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+  const int lane = threadIdx.x & 63, wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   for (int64_t t = (int64_t)blockIdx.x * 4 + wid; t < n_tasks; t += (int64_t)gridDim.x * 4)
     run_quant_task<D>(P, t, layer_sel, n_lcall, sb, cu, n_new_total, k, v, P.list, lane);
 }
