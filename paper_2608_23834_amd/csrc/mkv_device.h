@@ -141,31 +141,22 @@ __device__ __forceinline__ int32_t e4m3_times_512(uint32_t b) {
 }
 
 // fp64 -> binary16, round to nearest even, saturating at +-65504 (stored
-// metadata stays finite).  Method: pick the binary16 quantum 2^e of |x| (the
-// spacing of binary16 numbers in |x|'s binade, never below the subnormal
-// quantum 2^-24), scale |x| by 2^-e -- exact, a power of two -- and round that
-// once to an integer m with rint (the default mode is ties-to-even).  m is the
-// binary16 significand; m = 2048 means the rounding carried into the next
-// binade.  One rounding, no intermediate format.
-__device__ inline uint16_t f64_to_f16_rne_sat(double x) {
-  const uint32_t sign = signbit(x) ? 0x8000u : 0u;
-  const double ax = fabs(x);
-  if (isnan(x)) return (uint16_t)(sign | 0x7E00u);
-  if (ax >= 65504.0) return (uint16_t)(sign | 0x7BFFu);  // largest finite binary16
-  if (ax == 0.0) return (uint16_t)sign;
-  int bexp;
-  (void)frexp(ax, &bexp);            // ax in [2^(bexp-1), 2^bexp)
-  const int e = max(bexp - 11, -24);  // quantum: 11 significant bits, subnormals below 2^-14
-  double m = rint(ldexp(ax, -e));     // 0 <= m <= 2048
-  int ee = e;
-  if (m == 2048.0) {  // carried into the next binade
-    m = 1024.0;
-    ee += 1;
-  }
-  const uint32_t mi = (uint32_t)m;
-  if (mi < 1024u) return (uint16_t)(sign | mi);  // subnormal (ee = -24) or zero
-  const uint32_t biased = (uint32_t)(ee + 25);   // value = mi * 2^ee, mi in [1024, 2048)
-  return (uint16_t)(sign | (biased << 10) | (mi - 1024u));
+// metadata stays finite).  Method: round to fp32 to odd -- truncate, and set the
+// last bit when anything was cut off -- then to binary16 with the hardware's
+// conversion: an odd last bit keeps the value off every binary16 tie, and fp32
+// carries more than two bits beyond binary16's, so the second rounding sees on
+// which side of a boundary x lies (one rounding in effect).  The truncation
+// comes from the fp64 -> fp32 conversion by stepping back where it rounded away
+// from zero.  Ten instructions, against about thirty through frexp and ldexp.
+__device__ __forceinline__ uint16_t f64_to_f16_rne_sat(double x) {
+  const float f = (float)x;
+  const double d = (double)f;
+  uint32_t u = __float_as_uint(f);
+  u -= fabs(d) > fabs(x) ? 1u : 0u;
+  u |= d != x ? 1u : 0u;
+  const float c = fminf(fmaxf(__uint_as_float(u), -65504.0f), 65504.0f);  // largest finite binary16
+  const uint16_t h = __builtin_bit_cast(uint16_t, (_Float16)c);
+  return x != x ? (uint16_t)((signbit(x) ? 0x8000u : 0u) | 0x7E00u) : h;
 }
 __device__ __forceinline__ double f16_bits_to_f64(uint16_t h) {
   _Float16 v = __builtin_bit_cast(_Float16, h);

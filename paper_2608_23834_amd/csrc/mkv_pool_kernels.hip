@@ -809,130 +809,289 @@ __global__ __launch_bounds__(MIG_NT) void migrate_list_kernel(
   }
 }
 
-// TQ3 key code of one rotated coordinate: the codebook level nearest to
-// z = y / sqrt(n2) * (normalised coordinate; levels +-{0.25, 0.75, 1.375,
-// 2.25}), ties to the lower level.  The decision boundaries are 0 and
-// +-{8, 17, 29} / 16, so with u = (16 y)^2 the magnitude class of z is the
-// number of boundaries b with u beyond b^2 n2 -- three exact 64-bit integer
-// comparisons (u < 2^60 and b^2 n2 < 2^54 for |X_j| <= 448 * 2^9, d <= 256).
-// A positive z takes codes 4 + class (strictly beyond a boundary to move up);
-// z <= 0 takes 3 - class (at or beyond a boundary to move down, so a tie and
-// z = 0 stay on the side of the lower code).
-__device__ __forceinline__ int tq3_decide(int32_t y, int64_t n2) {
-  const int64_t u = (16LL * y) * (16LL * y);
-  const int64_t b1 = 64LL * n2, b2 = 289LL * n2, b3 = 841LL * n2;
-  if (y > 0) return 4 + (int)(u > b1) + (int)(u > b2) + (int)(u > b3);
-  return 3 - (int)(u >= b1) - (int)(u >= b2) - (int)(u >= b3);
+// A chunk's dwords from its quads (the inverse of quad_sel, a whole chunk at once).
+template <int NDW>
+__device__ __forceinline__ void pack_quads(uint32_t* dw, const uint32_t* quad) {
+#pragma unroll
+  for (int j = 0; j < NDW; ++j) dw[j] = quad[2 * j] | quad[2 * j + 1] << 3;
+#pragma unroll
+  for (int p = 0; p < NDW / 3; ++p) {
+    const uint32_t a = quad[2 * NDW + 2 * p], b = quad[2 * NDW + 2 * p + 1];
+    dw[3 * p] |= (a & 0x03030303u) << 6;
+    dw[3 * p + 1] |= (a & 0x04040404u) << 4 | (b & 0x01010101u) << 7;
+    dw[3 * p + 2] |= (b & 0x06060606u) << 5;
+  }
+}
+// NDW dwords to a chunk: 8-byte stores where the chunk size keeps them aligned
+template <int NDW>
+__device__ __forceinline__ void store_chunk(uint32_t* out, const uint32_t* dw) {
+  if constexpr (NDW % 2 == 0) {
+#pragma unroll
+    for (int j = 0; j < NDW / 2; ++j) reinterpret_cast<uint2*>(out)[j] = make_uint2(dw[2 * j], dw[2 * j + 1]);
+  } else {
+#pragma unroll
+    for (int j = 0; j < NDW; ++j) out[j] = dw[j];
+  }
+}
+// dwords per row of the value quads in LDS (the chunk's quads, padded: 16-byte rows off one bank)
+__host__ __device__ constexpr int enc_row(int d) { return d / 16 + 4; }
+
+// Encode of one FP8 page-head into its TQ3 region by two independent waves, one
+// for the keys and one for the values; no barrier, no LDS between them.
+//
+// Keys (enc_keys): lane 4 t + g owns channels D/4 g .. of token t, which is one
+// K chunk of the region.  X = sigma * e4m3 * 2^9 (integers; kept doubled, X2 =
+// 2 X, by the conversion's scale), the Sylvester Walsh-Hadamard transform in int32
+// (exact): strides below D/4 inside the lane, the two others across the four lanes
+// of a token.  The code of a rotated coordinate y is the codebook level nearest
+// to z = y / sqrt(n2) (levels +-{0.25, 0.75, 1.375, 2.25}), ties to the lower level: the boundaries are 0 and
+// +-{8, 17, 29} / 16, a positive y passes boundary b when 16 y > b sqrt(n2)
+// strictly, y <= 0 when 16 |y| >= b sqrt(n2).  As y is an integer that is a
+// comparison with f = floor(b sqrt(n2) / 16), found once per token and checked
+// in 64-bit integers: with A = 2 |y| + (y <= 0) both signs read A >= 2 f + 2, or
+// A >= 2 f + 1 where (16 f)^2 = b^2 n2 exactly.
+template <int D>
+__device__ __forceinline__ void enc_keys(const uint32_t* sgn, const uint8_t* f8, float sK, uint8_t* reg,
+                                         int lane) {
+  constexpr int QK = D / 4, NDW = 3 * D / 128, CB = 3 * D / 32;
+  const int t = lane >> 2, g = lane & 3;
+  uint4 raw[QK / 16];
+#pragma unroll
+  for (int i = 0; i < QK / 16; ++i) raw[i] = reinterpret_cast<const uint4*>(f8 + t * D + QK * g)[i];
+  int y[QK];
+  double nn = 0.0;  // sum of X2^2 (integers below 2^53: exact)
+#pragma unroll
+  for (int i = 0; i < QK / 4; ++i) {
+    const uint4& r = raw[i / 4];
+    const uint32_t w = (i % 4 == 0 ? r.x : i % 4 == 1 ? r.y : i % 4 == 2 ? r.z : r.w) ^ sgn[i];
+    typedef float f2 __attribute__((ext_vector_type(2)));
+    const f2 lo = __builtin_amdgcn_cvt_scalef32_pk_f32_fp8(w, 1024.0f, false);
+    const f2 hi = __builtin_amdgcn_cvt_scalef32_pk_f32_fp8(w, 1024.0f, true);
+    const float f[4] = {lo[0], lo[1], hi[0], hi[1]};
+#pragma unroll
+    for (int b = 0; b < 4; ++b) {
+      nn = __builtin_fma((double)f[b], (double)f[b], nn);
+      y[4 * i + b] = (int)f[b];
+    }
+  }
+  auto sum4 = [](double v) {  // over the token's four lanes
+    auto step = [](double x, auto ctl) {
+      const uint64_t u = __builtin_bit_cast(uint64_t, x);
+      constexpr int C = decltype(ctl)::value;
+      const uint32_t a = (uint32_t)__builtin_amdgcn_mov_dpp((int)(uint32_t)u, C, 0xF, 0xF, false);
+      const uint32_t b = (uint32_t)__builtin_amdgcn_mov_dpp((int)(uint32_t)(u >> 32), C, 0xF, 0xF, false);
+      return x + __builtin_bit_cast(double, (uint64_t)b << 32 | a);
+    };
+    v = step(v, std::integral_constant<int, 0xB1>{});
+    return step(v, std::integral_constant<int, 0x4E>{});
+  };
+  const int64_t n2 = (int64_t)sum4(nn) >> 2;  // sum of X^2
+  // With lane g's values offset by c = 1, 0, 0, -1 (an impulse at channel 0 of
+  // the lane is that offset in all its outputs) those steps leave the lanes off
+  // by beta = 0, 0, 1, -1 (see below), which the decision takes into account.
+  const int beta = g == 2 ? 1 : g == 3 ? -1 : 0;
+  y[0] += g == 0 ? 1 : g == 3 ? -1 : 0;
+#pragma unroll
+  for (int s = 1; s < QK; s <<= 1)
+#pragma unroll
+    for (int i = 0; i < QK; ++i)
+      if (!(i & s)) {
+        const int a = y[i], b = y[i + s];
+        y[i] = a + b;
+        y[i + s] = a - b;
+      }
+  // strides D/4 and D/2: lanes g ^ 1 and g ^ 2; the upper lane holds a - b, taken
+  // as a + ~b (one instruction less than a - b), which is one too low
+  const int m1 = (g & 1) ? -1 : 0, m2 = (g & 2) ? -1 : 0;
+#pragma unroll
+  for (int i = 0; i < QK; ++i) {
+    y[i] = __builtin_amdgcn_mov_dpp(y[i], 0xB1, 0xF, 0xF, false) + (y[i] ^ m1);
+    y[i] = __builtin_amdgcn_mov_dpp(y[i], 0x4E, 0xF, 0xF, false) + (y[i] ^ m2);
+  }
+  // with the lane's offset, A + beta = max(y2, 1 + 2 beta - y2) for the offset y2
+  int th[3];  // A + beta >= th[k]: past boundary k
+  {
+    const int bnd[3] = {8, 17, 29};
+    const double sq = sqrt((double)n2);
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+      const int64_t rhs = (int64_t)(bnd[k] * bnd[k]) * n2;
+      int64_t f = (int64_t)(sq * (bnd[k] * 0.0625));
+      if (256 * f * f > rhs) --f;
+      if (256 * (f + 1) * (f + 1) <= rhs) ++f;
+      th[k] = (int)(2 * f + 2) - (256 * f * f == rhs ? 1 : 0) + beta;
+      if (n2 == 0) th[k] = 0x7FFFFFFF;  // a zero key: every code 3
+    }
+  }
+  const int a0 = 1 + 2 * beta;
+  const uint32_t flip = beta ? 0x07070707u : 0u;  // an odd offset turns A's parity round
+  // codes, four to a word (quad q: channels 4 q .. of the chunk), and sum of 64 level^2
+  uint32_t quad[QK / 4], ms = 0, mr = 0;
+#pragma unroll
+  for (int q = 0; q < QK / 4; ++q) {
+    uint32_t c[4];
+#pragma unroll
+    for (int b = 0; b < 4; ++b) {
+      const int y2 = y[4 * q + b];
+      const int A = max(y2, a0 - y2);  // 2 |y| + (y <= 0) + beta
+      const bool c1 = A >= th[1];
+      const bool c2 = A >= (c1 ? th[2] : th[0]);
+      const int cnt = (c1 ? 6 : 4) + (c2 ? 1 : 0);  // 4 + boundaries passed
+      c[b] = (uint32_t)(cnt ^ -(A & 1));  // low three bits: 4 + n, or 3 - n where y <= 0
+    }
+    const uint32_t p01 = __builtin_amdgcn_perm(c[1], c[0], 0x0C0C0400u);
+    const uint32_t p23 = __builtin_amdgcn_perm(c[3], c[2], 0x04000C0Cu);
+    quad[q] = ((p01 | p23) & 0x07070707u) ^ flip;
+    // 64 level^2 = 324, 121, 36, 4, 4, 36, 121, 324 = 4 * {81, 30, 9, 1, ...} + {0, 1, 0, 0, ...}
+    ms = __builtin_amdgcn_sad_u8(__builtin_amdgcn_perm(0x511E0901u, 0x01091E51u, quad[q]), 0u, ms);
+    mr = __builtin_amdgcn_sad_u8(__builtin_amdgcn_perm(0x00010000u, 0x00000100u, quad[q]), 0u, mr);
+  }
+  int M = (int)(4 * ms + mr);
+  M += __builtin_amdgcn_mov_dpp(M, 0xB1, 0xF, 0xF, false);
+  M += __builtin_amdgcn_mov_dpp(M, 0x4E, 0xF, 0xF, false);
+  uint32_t dw[NDW];
+  pack_quads<NDW>(dw, quad);
+  uint32_t* out = reinterpret_cast<uint32_t*>(reg + (g * 16 + t) * CB);
+  store_chunk<NDW>(out, dw);
+  if (g == 0) {
+    uint16_t g16 = 0;
+    if (n2) {
+      const double rr = (double)n2 / (double)M;
+      const double root = sqrt(rr);
+      g16 = f64_to_f16_rne_sat(root * ((double)sK * 0.015625));
+    }
+    reinterpret_cast<uint16_t*>(reg + 12 * D)[t] = g16;
+  }
 }
 
-// Encode one FP8 page-head into a TQ3 region per work item (grid-stride over
-// listed pages x layers x heads).  256 threads.
+// Values (enc_values): lane l owns channel 64 i + l, i < D/64.  zero = fp16(min),
+// scale = fp16((max - min) / 7) and code = clamp(rint((v - zero) / scale), 0, 7)
+// are defined in fp64.  The code is computed as fma(e, sV / scale, -zero / scale)
+// in fp32 (e the E4M3 value), whose error is below G = 2^-21 (|zero / scale| + 8)
+// wherever the code is not clamped anyway: it is the fp64 one unless the
+// result lies within G of a rounding boundary, and a wave with such a value
+// (about one in a hundred) takes the fp64 division.  The quads meet in LDS, where
+// lane 16 g + r builds chunk (r, g).
 template <int D>
-__global__ __launch_bounds__(256) void migrate_encode_kernel(PoolView P) {
+__device__ __forceinline__ void enc_values(const uint8_t* f8, float sV, uint8_t* reg, uint32_t* lds, int lane) {
+  constexpr int CL = D / 16, NDW = 3 * D / 128, CB = 3 * D / 32, NI = D / 64, LP = enc_row(D);
+  uint32_t w[NI][4];
+#pragma unroll
+  for (int i = 0; i < NI; ++i)
+#pragma unroll
+    for (int g = 0; g < 4; ++g) {
+      const int c = 64 * i + lane;
+      w[i][g] = reinterpret_cast<const uint32_t*>(f8 + PAGE * D)[((c / CL) * 4 + g) * CL + c % CL];
+    }
+#pragma unroll
+  for (int i = 0; i < NI; ++i) {
+    const int c = 64 * i + lane;
+    typedef float f2 __attribute__((ext_vector_type(2)));
+    float e[PAGE];
+#pragma unroll
+    for (int g = 0; g < 4; ++g) {
+      const f2 lo2 = __builtin_amdgcn_cvt_scalef32_pk_f32_fp8(w[i][g], 1.0f, false);
+      const f2 hi2 = __builtin_amdgcn_cvt_scalef32_pk_f32_fp8(w[i][g], 1.0f, true);
+      e[4 * g] = lo2[0], e[4 * g + 1] = lo2[1], e[4 * g + 2] = hi2[0], e[4 * g + 3] = hi2[1];
+    }
+    float emin = e[0], emax = e[0];
+#pragma unroll
+    for (int t = 1; t < PAGE; ++t) {
+      emin = fminf(emin, e[t]);
+      emax = fmaxf(emax, e[t]);
+    }
+    const double lo = (double)sV * (double)emin, hi = (double)sV * (double)emax;  // exact; sV >= 0
+    const uint16_t z16 = f64_to_f16_rne_sat(lo);
+    const uint16_t s16 = f64_to_f16_rne_sat((hi - lo) / 7.0);
+    reinterpret_cast<uint16_t*>(reg + 12 * D + 32)[c] = s16;
+    reinterpret_cast<uint16_t*>(reg + 14 * D + 32)[c] = z16;
+    const float zf = (float)__builtin_bit_cast(_Float16, z16), sf = (float)__builtin_bit_cast(_Float16, s16);
+    const float a = sf != 0.0f ? sV / sf : 0.0f, b = sf != 0.0f ? -zf / sf : 0.0f;
+    const float lim = 0.5f - (fabsf(b) + 8.0f) * 0x1p-21f;
+    uint32_t quad[4];
+    float off = 0.0f;
+#pragma unroll
+    for (int g = 0; g < 4; ++g) {
+      quad[g] = 0;
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const float q = __builtin_fmaf(e[4 * g + u], a, b);
+        const float rq = __builtin_rintf(q);
+        off = fmaxf(off, fabsf(q - rq));
+        quad[g] = __builtin_amdgcn_cvt_pk_u8_f32(fminf(fmaxf(rq, 0.0f), 7.0f), u, quad[g]);
+      }
+    }
+    if (__any(!(off <= lim))) {
+      const double z = f16_bits_to_f64(z16), s = f16_bits_to_f64(s16);
+#pragma unroll
+      for (int g = 0; g < 4; ++g) {
+        quad[g] = 0;
+#pragma unroll 1
+        for (int u = 0; u < 4; ++u) {
+          const double v = (double)sV * (double)e4m3_to_f32((w[i][g] >> (8 * u)) & 0xFFu);
+          const double q = fmin(fmax(rint((v - z) / s), 0.0), 7.0);
+          quad[g] |= (s != 0.0 ? (uint32_t)q : 0u) << (8 * u);
+        }
+      }
+    }
+#pragma unroll
+    for (int g = 0; g < 4; ++g) lds[((c / CL) * 4 + g) * LP + c % CL] = quad[g];
+  }
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  {
+    const int g = lane >> 4, r = lane & 15;
+    uint32_t quad[CL], dw[NDW];
+    const uint4* row = reinterpret_cast<const uint4*>(lds + (r * 4 + g) * LP);
+#pragma unroll
+    for (int q = 0; q < CL / 4; ++q) {
+      const uint4 x = row[q];
+      quad[4 * q] = x.x, quad[4 * q + 1] = x.y, quad[4 * q + 2] = x.z, quad[4 * q + 3] = x.w;
+    }
+    pack_quads<NDW>(dw, quad);
+    store_chunk<NDW>(reinterpret_cast<uint32_t*>(reg + 6 * D + (g * 16 + r) * CB), dw);
+  }
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();  // the rows are free for the wave's next page-head
+}
+
+// Encode every listed page-head (listed pages x layers x heads, grid-stride).
+// Waves 2 j and 2 j + 1 of the launch take one page-head together, one its keys
+// and one its values, and swap the roles from one page-head to the next (the key
+// half has about 1.7 times the instructions).  Bound by VALU issue: about
+// 1,700 + 1,000 instructions per page-head of d = 256.  The launch is what one
+// round of resident workgroups holds: a decode step, which lists a page or two
+// or none, pays for few workgroups.
+constexpr int ENC_WG = 4;  // waves per workgroup
+template <int D>
+__global__ __launch_bounds__(64 * ENC_WG, 3) void migrate_encode_kernel(PoolView P) {
   if (P.ctrl[CTRL_ABORT]) return;
-  constexpr int CL = D / 16, NDW = 3 * D / 128, CB = 3 * D / 32;
-  __shared__ int32_t y[PAGE * D];
-  __shared__ uint8_t kc[PAGE * D];
-  __shared__ uint8_t vc[PAGE * D];
+  __shared__ __align__(16) uint32_t s_quads[ENC_WG][64 * enc_row(D)];
   const int H = P.n_kv_heads, L = P.n_layers;
   const int64_t n_items = (int64_t)P.ctrl[CTRL_NLIST] * L * H;
-  const int tid = threadIdx.x, tok = tid >> 4, l16 = tid & 15;
-  for (int64_t item = blockIdx.x; item < n_items; item += gridDim.x) {
+  const int lane = threadIdx.x & 63, wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int64_t pair0 = (int64_t)blockIdx.x * (ENC_WG / 2) + (wid >> 1);
+  if (pair0 >= n_items) return;
+  // sign bits of the rotation's diagonal at the E4M3 bytes of this lane's key channels
+  uint32_t sgn[D / 16];
+  {
+    const uint32_t* sg = reinterpret_cast<const uint32_t*>(P.sigma + (D / 4) * (lane & 3));
+#pragma unroll
+    for (int i = 0; i < D / 16; ++i) sgn[i] = sg[i] & 0x80808080u;
+  }
+  int role = (wid + blockIdx.x) & 1;
+  for (int64_t item = pair0; item < n_items; item += (int64_t)gridDim.x * (ENC_WG / 2), role ^= 1) {
     const int e = (int)(item / (L * H));
     const int lh = (int)(item % (L * H));
     const int layer = lh / H, h = lh % H;
     const int src = P.list[4 * e + 2], dst = P.list[4 * e + 3];
     const int64_t sph = ((int64_t)layer * P.n_fp8 + src) * H + h;
     const uint8_t* f8 = P.fp8 + sph * fp8_region_bytes(D);
-    const float sK = P.fp8_scales[sph * 2], sV = P.fp8_scales[sph * 2 + 1];
     uint8_t* reg = P.tq3 + (((int64_t)layer * P.n_tq3 + dst) * H + h) * tq3_region_bytes(D);
-    // keys: X = sigma * e4m3 * 2^9 (integers), n2 = |X|^2
-    int64_t n2 = 0;
-    for (int j = 0; j < D / 16; ++j) {
-      const int c = l16 + 16 * j;
-      const int32_t X = (int32_t)P.sigma[c] * e4m3_times_512(f8[tok * D + c]);
-      y[tok * D + c] = X;
-      n2 += (int64_t)X * X;
-    }
-#pragma unroll
-    for (int o = 1; o < 16; o <<= 1) n2 += __shfl_xor(n2, o, 64);
-    __syncthreads();
-    // Sylvester Walsh-Hadamard transform of each token row (exact in int32)
-    for (int s = 1; s < D; s <<= 1) {
-      for (int b = l16; b < D / 2; b += 16) {
-        const int i = (b / s) * 2 * s + (b % s);
-        const int32_t a0 = y[tok * D + i], a1 = y[tok * D + i + s];
-        y[tok * D + i] = a0 + a1;
-        y[tok * D + i + s] = a0 - a1;
-      }
-      __syncthreads();
-    }
-    int M = 0;
-    for (int j = 0; j < D / 16; ++j) {
-      const int c = l16 + 16 * j;
-      const int code = n2 ? tq3_decide(y[tok * D + c], n2) : 3;
-      kc[tok * D + c] = (uint8_t)code;
-      M += mu2x64(code);
-    }
-#pragma unroll
-    for (int o = 1; o < 16; o <<= 1) M += __shfl_xor(M, o, 64);
-    if (l16 == 0) {
-      uint16_t g16 = 0;
-      if (n2) {
-        const double rr = (double)n2 / (double)M;
-        const double sq = sqrt(rr);
-        const double g = sq * ((double)sK * 0.015625);
-        g16 = f64_to_f16_rne_sat(g);
-      }
-      reinterpret_cast<uint16_t*>(reg + 12 * D)[tok] = g16;
-    }
-    // values: per channel asymmetric 3-bit over the 16 tokens
-    if (tid < D) {
-      const int c = tid;
-      double lo = INFINITY, hi = -INFINITY;
-      for (int t = 0; t < PAGE; ++t) {
-        const double vv = (double)sV * (double)e4m3_to_f32(f8[fp8_off<D>(1, t, c)]);
-        lo = fmin(lo, vv);
-        hi = fmax(hi, vv);
-      }
-      const uint16_t z16 = f64_to_f16_rne_sat(lo);
-      const uint16_t s16 = f64_to_f16_rne_sat((hi - lo) / 7.0);
-      reinterpret_cast<uint16_t*>(reg + 12 * D + 32)[c] = s16;
-      reinterpret_cast<uint16_t*>(reg + 14 * D + 32)[c] = z16;
-      const double z = f16_bits_to_f64(z16), s = f16_bits_to_f64(s16);
-      for (int t = 0; t < PAGE; ++t) {
-        int code = 0;
-        if (s != 0.0) {
-          const double vv = (double)sV * (double)e4m3_to_f32(f8[fp8_off<D>(1, t, c)]);
-          double u = rint((vv - z) / s);
-          u = fmin(fmax(u, 0.0), 7.0);
-          code = (int)u;
-        }
-        vc[t * D + c] = (uint8_t)code;
-      }
-    }
-    __syncthreads();
-    // pack: threads 0..63 build K chunks (t, g), threads 64..127 V chunks (r, g)
-    if (tid < 128) {
-      uint32_t Dw[NDW];
-#pragma unroll
-      for (int w = 0; w < NDW; ++w) Dw[w] = 0;
-      uint8_t* out;
-      if (tid < 64) {
-        const int t = tid >> 2, g = tid & 3;
-        for (int q = 0; q < D / 16; ++q)
-          for (int b = 0; b < 4; ++b) quad_put<NDW>(Dw, q, b, kc[t * D + (D / 4) * g + 4 * q + b]);
-        out = reg + (g * 16 + t) * CB;
-      } else {
-        const int rr = (tid - 64) >> 2, g = (tid - 64) & 3;
-        for (int q = 0; q < CL; ++q)
-          for (int b = 0; b < 4; ++b) quad_put<NDW>(Dw, q, b, vc[(4 * g + b) * D + CL * rr + q]);
-        out = reg + 6 * D + (g * 16 + rr) * CB;
-      }
-#pragma unroll
-      for (int w = 0; w < NDW; ++w) reinterpret_cast<uint32_t*>(out)[w] = Dw[w];
-    }
-    __syncthreads();
+    if (role == 0)
+      enc_keys<D>(sgn, f8, P.fp8_scales[sph * 2], reg, lane);
+    else
+      enc_values<D>(f8, P.fp8_scales[sph * 2 + 1], reg, s_quads[wid], lane);
   }
 }
 
@@ -1481,11 +1640,11 @@ hipError_t launch_migrate(const PoolView& P, int n_req, int32_t* bt, uint8_t* ta
   }
   int64_t bound = (int64_t)n_req * max_pages;
   if (bound > P.n_fp8) bound = P.n_fp8;
-  const int grid = grid_for(bound * P.n_layers * P.n_kv_heads, 4096);
+  const int grid = grid_for((bound * P.n_layers * P.n_kv_heads + ENC_WG / 2 - 1) / (ENC_WG / 2), 1024);
   if (P.d == 256)
-    hipLaunchKernelGGL(migrate_encode_kernel<256>, dim3(grid), dim3(256), 0, s, P);
+    hipLaunchKernelGGL(migrate_encode_kernel<256>, dim3(grid), dim3(64 * ENC_WG), 0, s, P);
   else
-    hipLaunchKernelGGL(migrate_encode_kernel<128>, dim3(grid), dim3(256), 0, s, P);
+    hipLaunchKernelGGL(migrate_encode_kernel<128>, dim3(grid), dim3(64 * ENC_WG), 0, s, P);
   hipLaunchKernelGGL(migrate_publish_kernel, dim3(1), dim3(1024), 0, s, bt, tags, max_pages, P.ctrl,
                      P.fp8_stack, P.list, P.rc8, P.rc3);
   return hipGetLastError();

@@ -64,3 +64,49 @@ def test_append_plan_sizes(torch_cuda, n_req, n):
     t.append(lens, layer_kv=(k, k[:, ::-1].copy()))
     t.check_tables()
     t.check_pages()
+
+
+def _special_pages(d, h, rng):
+    """Blocks of 16 tokens whose codes sit on decision boundaries."""
+    blocks = []
+    one = np.zeros((16, h, d), np.float32)
+    for i in range(16):
+        one[i, :, (i * 37) % d] = (-1.0) ** i * 2.0 ** (i % 4)
+    blocks.append(one)                                        # basis vectors: exact ties, y = 0
+    blocks.append(np.zeros((16, h, d), np.float32))           # zero keys
+    blocks.append(np.ones((16, h, d), np.float32))            # constant values (scale 0)
+    two = np.zeros((16, h, d), np.float32)
+    two[:, :, 0], two[:, :, 1] = 1.0, -1.0
+    blocks.append(two)
+    ramp = np.tile((np.arange(16, dtype=np.float32) * 0.5)[:, None, None], (1, h, d))
+    blocks.append(ramp)                                       # values on half-code boundaries
+    blocks.append(ramp - 448.0)
+    blocks.append(np.tile((np.arange(16) % 2 * 13.0 + 1.0).astype(np.float32)[:, None, None], (1, h, d)))
+    blocks.append(_rows(rng, 16, h, d, 1e-7))                 # binary16 subnormal metadata
+    blocks.append(_rows(rng, 16, h, d, 1e-30))
+    blocks.append(_rows(rng, 16, h, d, 1e6))                  # saturating metadata
+    blocks.append(np.sign(_rows(rng, 16, h, d)) * 448.0)      # the largest integer sums
+    big = _rows(rng, 16, h, d)
+    big[:, :, :4] *= 64.0
+    blocks.append(big)
+    off = _rows(rng, 16, h, d, 1e-2) + 100.0                  # zero >> scale: wide guard band
+    blocks.append(off)
+    blocks += [_rows(rng, 16, h, d, 2.0 ** s) for s in (-8, 0, 6)]
+    return np.concatenate(blocks)
+
+
+@pytest.mark.parametrize("d", [128, 256])
+def test_encode_special_pages(torch_cuda, d):
+    rng = np.random.default_rng(d)
+    h = 3
+    x = _special_pages(d, h, rng)
+    n = x.shape[0]
+    t = _twin(d, h, [n, n], recent=16, n_layers=2)
+    k = wl.bf16_round(np.concatenate([x, x[::-1]]))
+    v = wl.bf16_round(np.concatenate([x[::-1], x]))
+    t.append([n, n], layer_kv=(np.stack([k, v]), np.stack([v, k])))
+    t.check_pages()
+    t.migrate(np.zeros((2, t.max_pages), np.uint8))
+    t.check_tables()
+    n8, n3 = t.check_pages()
+    assert n3 >= 2 * (n // 16 - 1)
