@@ -288,7 +288,8 @@ mkv_status paged_attn_decode_noalloc(mkv_pool* pool, int32_t layer, int32_t n_re
  * own KV must already be appended as FP8).  q: device bf16
  * [n_q_total][n_q_heads][d]; cu_q: device int32 [n_req+1]; out: device fp32
  * [n_q_total][n_q_heads][d]; ws >= paged_attn_workspace_bytes(..., n_q_total)
- * (it holds the compact per-format page lists).  q, out and ws must be
+ * (it holds the per-format page lists, the work items and the partial
+ * outputs of row blocks that are cut along their pages).  q, out and ws must be
  * 16-byte aligned (MKV_EINVAL otherwise).  A request whose query range or
  * length is invalid sets the error word and its locatable rows get zeros.
  * Query ranges are expected not to overlap (cu_q nondecreasing); ranges that

@@ -5,41 +5,42 @@
 // rotated queries against TQ3 key codes times the FP16 key-norm correction,
 // plain queries against FP8 keys, one online softmax per query row.
 //
-// Launch: the partition kernel (compact per-format lists, Sec. 4.1), a stage
-// table kernel (per request: the TQ3 pages in pairs, then the FP8 pages), a
-// row-block table kernel (first 128-row block of each request) and the
-// attention kernel.  Grid (row block over all requests, KV head); 512
-// threads = 8 waves, one workgroup per CU, two waves per SIMD.  A query row
-// is a (query token, head of the GQA group) pair; a workgroup owns 128 rows:
+// Launch: a list kernel (per request the TQ3 and the FP8 pages in logical order,
+// Sec. 4.1), a plan kernel (the row blocks, how far each has to read, and how the
+// blocks are cut along the pages when there are too few of them for the chip),
+// the attention kernel, and a merge of the cut blocks' parts where any can be.
+// Grid (work item, KV head); 512 threads = 8 waves, one workgroup per CU, two
+// waves per SIMD.  A query row is a (query token, head of the GQA group) pair; a
+// workgroup owns 128 rows and a range of their passes, a pass being a pair of
+// pages of one format (first the TQ3 pairs, then the FP8 pairs):
 //  * four score waves of 32 rows each hold their rows' rotated queries as
-//    three E4M3 terms in registers, copy their share of every stage (direct
-//    HBM -> LDS copies into a ring of eight stages) and of the stage table,
-//    unpack TQ3 pairs into MFMA operand layouts in LDS (key codes -> E4M3
-//    codebook bytes, value codes as bytes, the V scale split for exact fp16
-//    products).  Pass p issues S^T = K Q^T of pair p on
-//    v_mfma_f32_32x32x64_f8f6f4 (M = the pair's 32 tokens, N = the 32 rows,
-//    K = 64 channels; three MFMAs per k-step, one per query term) and,
-//    between those MFMAs, finishes pair p - 1: the causal mask, the online
+//    three E4M3 terms in registers and unpack TQ3 pairs into MFMA operand
+//    layouts in LDS (key codes -> E4M3 codebook bytes, value codes
+//    as bytes, the V scale split for exact fp16 products).  Pass p issues S^T = K
+//    Q^T of pair p on v_mfma_f32_32x32x64_f8f6f4 (M = the pair's 32 tokens, N =
+//    the 32 rows, K = 64 channels; three MFMAs per k-step, one per query term)
+//    and, between those MFMAs, finishes pair p - 1: the causal mask, the online
 //    softmax in base 2 (lazy rescale, threshold 2^8) and the weights as fp16
 //    hi + lo pairs, handed over in LDS;
 //  * four PV waves, wave v owning the 32-channel blocks 2v, 2v + 1 of all
 //    128 rows, hold O^T accumulators (32 channels x 32 rows per block and
-//    score wave) and compute O^T += V^T P^T on v_mfma_f32_32x32x16_f16 (M =
+//    score wave), copy every page (direct HBM -> LDS copies into a ring) and the
+//    page lists, and compute O^T += V^T P^T on v_mfma_f32_32x32x16_f16 (M =
 //    32 channels, N = 32 rows, K = the 16 tokens of one page; a lane's score
 //    outputs are exactly the 8 tokens per page its weight operand holds):
 //    values as exact fp16 operands (scale_hi * code, scale_lo * code), the
 //    zero term as one rank-2 product of the pages' zeros and weight sums,
 //    applying the rescale the score waves passed along first.
 // Pass p (one barrier): the score waves issue pair p's product and finish
-// pair p - 1 while the PV waves take pair p - 2.  FP8 pages: the score waves
+// pair p - 1 while the PV waves take pair p - 2.  FP8 pairs: the score waves
 // score them on the f16 MFMA against the plain query (the fp8 MFMA keeps too
-// few bits where FP8 keys carry large norms) with one zero-padded half of
-// the tile, and fold the page's V scale into the weights; the PV waves read
-// the page's values from the ring.  The workgroups of one (request, KV head)
-// read the same pages at about the same time, so the page bytes come from
-// L2 after the first reader.
+// few bits where FP8 keys carry large norms) and fold the pages' V scales into
+// the weights; the PV waves read the pages' values from the ring.  The
+// workgroups of one (request, KV head) read the same pages at about the same
+// time, so the page bytes come from L2 after the first reader.
 #include <hip/hip_runtime.h>
 
+#include <atomic>
 #include <type_traits>
 
 #include "mkv_attn.h"
@@ -50,83 +51,289 @@ namespace mkv {
 
 constexpr int NSW = 4;       // score waves per chunk workgroup (one PV wave each)
 constexpr int CW = 2 * NSW;  // waves per chunk workgroup
-constexpr int CSLOTS = 8;    // raw stages in the shared ring
+constexpr int CSLOTS = 8;    // slots of the page ring: a TQ3 pair or one FP8 page each
+// FP8 pairs take two slots for three passes; while they run, the buffers of
+// unpacked TQ3 operands behind the ring are four slots more
+constexpr int CSLOTS8 = 12;
 constexpr int CMASK_LP = 0x3FFFFFFF / PAGE;
 
 struct ChunkArgs {
   PoolView P;
-  int layer, n_req, max_pages, n_q_total;
+  int layer, n_req, max_pages, n_q_total, stride;
   const uint16_t* q;
   const int32_t* cu_q;
   const int32_t* seq_lens;
   float* out;
-  const int32_t* list8;   // [n_req][max_pages][2] (logical page, physical id)
-  const int32_t* list3;
-  const int32_t* counts;  // [n_req][2] (n_fp8, n_tq3)
-  const int4* stages;     // [n_req][max_pages] stage table (chunk_stages_kernel)
-  const int32_t* rbo;     // [n_req + 1] first row block of each request (chunk_rows_kernel)
-  float sm_log2;          // log2(e) / sqrt(d)
+  const int2* list8;   // [n_req][stride] (logical page, physical id), in pairs
+  const int2* list3;
+  const int32_t* hdr;  // [0] work items, [1] blocks cut into parts
+  const int4* items;   // two per work item, see chunk_plan_kernel
+  float* parts;        // the parts of cut blocks, see chunk_part_floats
+  float sm_log2;       // log2(e) / sqrt(d)
 };
 
 static size_t al256(size_t b) { return (b + 255) / 256 * 256; }
 
-// workspace: the two compact lists, their counts and the stage table (one
-// int4 per stage; the chunk kernel copies it in 1 KiB blocks, so 1 KiB of
-// slack after it keeps the last block inside the workspace)
+// CUs a KV head's row blocks can spread over, and the most work items that cut
+// blocks are planned for (two rounds)
+static int cu_share(int n_kv_heads) { return n_kv_heads >= 256 ? 1 : 256 / n_kv_heads; }
+constexpr int MAX_ITEMS = 512;  // 2 * cu_share at most
+constexpr int MAX_PARTS = 32;   // parts of one block at most
+static int64_t chunk_blocks(int n_q_total, int group) { return ((int64_t)n_q_total * group + NSW * 32 - 1) / (NSW * 32); }
+// Blocks are cut only where at least that many of them (the query ranges not
+// overlapping) leave room in two rounds.
+static bool chunk_may_cut(int n_q_total, int group, int n_kv_heads) {
+  return chunk_blocks(n_q_total, group) <= 2 * cu_share(n_kv_heads);
+}
+// One part of one KV head: O^T accumulators of the PV waves as they stand in
+// registers ([PV wave][block][score wave][4][lane] float4s), then (m, l) per row.
+__host__ __device__ constexpr int64_t chunk_part_floats(int d) { return 128LL * d + 256; }
+
+// workspace: the two page lists (even rows with room for a masked last page;
+// the kernel copies them in 1 KiB blocks, so 1 KiB of slack follows), the pages'
+// running counts, the row blocks, the work items and the parts of cut blocks
 struct ChunkWs {
-  size_t list8, list3, counts, stages, rbo, total;
+  size_t list8, list3, cum, rbo, hdr, items, splits, parts, total;
+  int stride;
 };
-static ChunkWs chunk_ws(int n_req, int max_pages) {
+static ChunkWs chunk_ws(int n_req, int max_pages, int n_q_total, int n_kv_heads, int group, int d) {
   ChunkWs w;
-  const size_t lb = al256((size_t)n_req * max_pages * 2 * sizeof(int32_t));
+  w.stride = (max_pages + 2) & ~1;
+  const size_t lb = al256((size_t)n_req * w.stride * sizeof(int2) + 1024);
+  const bool cut = chunk_may_cut(n_q_total, group, n_kv_heads);
+  const size_t n_items = (size_t)chunk_blocks(n_q_total, group) + n_req + (cut ? MAX_ITEMS : 0);
   w.list8 = 0;
   w.list3 = lb;
-  w.counts = 2 * lb;
-  w.stages = w.counts + al256((size_t)n_req * 2 * sizeof(int32_t));
-  w.rbo = w.stages + al256((size_t)n_req * max_pages * sizeof(int4) + 1024);
-  w.total = w.rbo + al256((size_t)(n_req + 1) * sizeof(int32_t));
+  w.cum = 2 * lb;
+  w.rbo = 3 * lb;
+  w.hdr = w.rbo + al256((size_t)(n_req + 1) * sizeof(int32_t));
+  w.items = w.hdr + 256;
+  w.splits = w.items + al256(n_items * 2 * sizeof(int4));
+  w.parts = w.splits + (cut ? MAX_ITEMS * sizeof(int4) : 0);
+  // a part holds at least one pass: short tables cannot be cut into many
+  const int64_t passes = (max_pages + 1) / 2 + 1;
+  int64_t n_parts = cut ? 2LL * cu_share(n_kv_heads) : 0;
+  const int64_t most = ((int64_t)chunk_blocks(n_q_total, group) + n_req) * (passes < MAX_PARTS ? passes : MAX_PARTS);
+  if (n_parts > most) n_parts = most;
+  w.total = w.parts + (size_t)n_parts * n_kv_heads * chunk_part_floats(d) * sizeof(float);
   return w;
 }
 size_t chunk_ws_bytes(int n_req, int max_pages, int n_q_total, int n_kv_heads, int group, int d) {
-  (void)n_q_total; (void)n_kv_heads; (void)group; (void)d;
-  return chunk_ws(n_req, max_pages).total;
+  return chunk_ws(n_req, max_pages, n_q_total, n_kv_heads, group, d).total;
 }
 
-// Stage table of a chunk call: per request, stage j -> {lp_a, id_a, lp_b,
-// id_b}: the TQ3 pages in pairs (list entries 2 j, 2 j + 1; a missing page b
-// is masked) first, then the FP8 pages one per stage (id_b = -1).  Ids
-// outside the pool become page 0 with every token masked, and set the range
-// error bit.
-__global__ __launch_bounds__(256) void chunk_stages_kernel(int max_pages, int n_tq3, int n_fp8,
-                                                           const int32_t* list8,
-                                                           const int32_t* list3,
-                                                           const int32_t* counts, int4* stages,
-                                                           int32_t* err) {
-  const int r = blockIdx.y, j = blockIdx.x * 256 + threadIdx.x;
-  const int n8 = counts[2 * r], n3 = counts[2 * r + 1];
-  const int st3 = (n3 + 1) / 2, n_st = st3 + n8;  // at most the request's pages
-  if (j >= n_st) return;
-  const int2* l3 = reinterpret_cast<const int2*>(list3) + (int64_t)r * max_pages;
-  const int2* l8 = reinterpret_cast<const int2*>(list8) + (int64_t)r * max_pages;
-  bool bad = false;
-  auto checked = [&](int2 e, int n_ids) {
-    if (e.y < 0 || e.y >= n_ids) {
-      bad = true;
-      return make_int2(CMASK_LP, 0);
-    }
-    return e;
-  };
-  int4 st;
-  if (j < st3) {
-    const int2 ea = checked(l3[2 * j], n_tq3);
-    const int2 eb = 2 * j + 1 < n3 ? checked(l3[2 * j + 1], n_tq3) : make_int2(CMASK_LP, ea.y);
-    st = make_int4(ea.x, ea.y, eb.x, eb.y);
-  } else {
-    const int2 e = checked(l8[j - st3], n_fp8);
-    st = make_int4(e.x, e.y, 0, -1);
+// Page lists of a chunk call, one workgroup per request: the TQ3 and the FP8
+// pages in logical order, so entries 2 j and 2 j + 1 are pair j of their format
+// (an odd list ends with a masked page), and per logical page the counts of both
+// formats up to and including it.  Ids outside the pool become page 0 with every
+// token masked, and set the range error bit.  Four consecutive pages per thread,
+// one scan of both counts per 4,096 pages: the cost is round trips.
+constexpr int LIST_NT = 1024, LIST_KB = 4;
+__global__ __launch_bounds__(LIST_NT) void chunk_lists_kernel(const int32_t* bt, const uint8_t* tags,
+                                                              int max_pages, int stride,
+                                                              const int32_t* seq_lens, int n_fp8,
+                                                              int n_tq3, int2* list8, int2* list3,
+                                                              int2* cum, int32_t* err) {
+  __shared__ int scratch[32];
+  const int r = blockIdx.x, tid = threadIdx.x;
+  const int S = seq_lens[r];
+  const int np = S >= 1 ? (S - 1) / PAGE + 1 : 0;
+  if (S < 1 || np > max_pages) {  // its blocks write zeros
+    if (tid == 0) atomicOr(err, (int)MKV_DEVERR_RANGE);
+    return;
   }
-  stages[(int64_t)r * max_pages + j] = st;
-  if (bad) atomicOr(err, (int)MKV_DEVERR_RANGE);
+  int2* l8 = list8 + (int64_t)r * stride;
+  int2* l3 = list3 + (int64_t)r * stride;
+  int2* cm = cum + (int64_t)r * stride;
+  int b8 = 0, b3 = 0, bad = 0;
+  for (int c0 = 0; c0 < np; c0 += LIST_NT * LIST_KB) {
+    int tg[LIST_KB], id[LIST_KB];
+#pragma unroll
+    for (int j = 0; j < LIST_KB; ++j) {
+      const int p = c0 + LIST_KB * tid + j;
+      const int64_t i = (int64_t)r * max_pages + min(p, np - 1);
+      tg[j] = tags[i];
+      id[j] = bt[i];
+      if (p >= np) tg[j] = -1;
+    }
+    int v = 0;
+#pragma unroll
+    for (int j = 0; j < LIST_KB; ++j) v += tg[j] == TAG_S ? 1 << 16 : (tg[j] == TAG_R || tg[j] == TAG_A) ? 1 : 0;
+    int tot;
+    const int pre = block_excl_scan(v, scratch, &tot);
+    int r8 = b8 + (pre & 0xFFFF), r3 = b3 + (pre >> 16);
+#pragma unroll
+    for (int j = 0; j < LIST_KB; ++j) {
+      const int p = c0 + LIST_KB * tid + j;
+      if (tg[j] < 0) continue;
+      const bool is3 = tg[j] == TAG_S, is8 = tg[j] == TAG_R || tg[j] == TAG_A;
+      int2 e = make_int2(p, id[j]);
+      if (id[j] < 0 || id[j] >= (is3 ? n_tq3 : n_fp8)) {
+        if (is3 || is8) bad |= MKV_DEVERR_RANGE;
+        e = make_int2(CMASK_LP, 0);
+      }
+      if (is3) l3[r3++] = e;
+      else if (is8) l8[r8++] = e;
+      else bad |= MKV_DEVERR_BAD_TAG;
+      cm[p] = make_int2(r8, r3);
+      if (p == np - 1) {  // the masked partners of odd lists
+        l8[r8] = make_int2(CMASK_LP, 0);
+        l3[r3] = make_int2(CMASK_LP, 0);
+      }
+    }
+    b8 += tot & 0xFFFF;
+    b3 += tot >> 16;
+  }
+  if (bad) atomicOr(err, bad);
+}
+
+// Plan of a chunk call (one workgroup).
+// Row blocks: request r gets ceil(n_r G / 128) blocks of 128 rows (at least one,
+// and one for a request whose query range is invalid, so that its error is
+// reported).  Query ranges that do not overlap need at most `grid` blocks; ranges
+// that overlap and need more set the range error bit and the call writes nothing.
+// A block reads the pages up to its last row's position, so the pages of the
+// chunk that only later rows see are left out.
+// Cutting: a block's passes run one after the other on one CU, so a call with
+// fewer blocks than CUs, or of uneven lengths, leaves the chip idle (six chunks
+// of 1-300 queries after 0.5-8 K tokens: 691 us, the longest request's blocks
+// alone at the end).  With U the most cost units a part may hold, the blocks make
+// sum ceil(cost / U) parts; the plan tries eight sizes U for one and for two rounds
+// of the chip, estimates a round as U + CUT_COST (a part's own start, its
+// partial results' way through memory and the merge, measured) and takes the
+// best, or leaves the blocks whole where that is estimated as good.  Cost
+// units: 4 per TQ3 pair, 3 per FP8 pair (their measured ratio).
+// items: two int4 per work item, {request, block of the request, first TQ3 pair,
+// TQ3 pairs}, {first FP8 pair, FP8 pairs, part slot or -1, -}; splits: {request,
+// block of the request, first part slot, parts}.
+constexpr int COST3 = 4, COST8 = 3;
+constexpr int CUT_COST = 12 * COST3, MIN_PART = 4 * COST3;
+__global__ __launch_bounds__(1024) void chunk_plan_kernel(int n_req, const int32_t* cu_q, int n_q_total,
+                                                          const int32_t* seq_lens, int max_pages,
+                                                          int group, int grid, int share, int may_cut,
+                                                          int max_slots, int stride, const int2* cum,
+                                                          int32_t* rbo, int32_t* hdr, int4* items,
+                                                          int4* splits, int32_t* err) {
+  __shared__ int scratch[32];
+  __shared__ int s_rbo[1025];
+  __shared__ int s_r[MAX_ITEMS], s_x[MAX_ITEMS], s_t3[MAX_ITEMS], s_f8[MAX_ITEMS];
+  __shared__ int s_max, s_est[16], s_u[16];
+  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+  const int per = (n_req + 1023) / 1024;
+  const int ra = min(n_req, tid * per), rb = min(n_req, ra + per);
+  auto blocks = [&](int r) {
+    const int q0 = cu_q[r], q1 = cu_q[r + 1];
+    const bool ok = q0 >= 0 && q1 >= q0 && q1 <= n_q_total;
+    return ok ? max(1, (int)(((int64_t)(q1 - q0) * group + NSW * 32 - 1) / (NSW * 32))) : 1;
+  };
+  int sum = 0;
+  for (int r = ra; r < rb; ++r) sum += blocks(r);
+  int nblk;
+  int base = block_excl_scan(sum, scratch, &nblk);
+  const bool in_lds = n_req <= 1024;
+  for (int r = ra; r < rb; ++r) {
+    if (in_lds) s_rbo[r] = base;
+    else rbo[r] = base;
+    base += blocks(r);
+  }
+  if (tid == 0) s_max = 0;
+  __syncthreads();
+  if (nblk > grid) {  // workgroup-uniform
+    if (tid == 0) {
+      atomicOr(err, (int)MKV_DEVERR_RANGE);
+      hdr[0] = hdr[1] = 0;
+    }
+    return;
+  }
+  // block b -> request, block of the request, TQ3 and FP8 pairs it reads
+  auto locate = [&](int b, int& r, int& x, int& t3, int& f8) {
+    int lo = 0, hi = n_req - 1;  // the last request whose first block is <= b
+    while (lo < hi) {
+      const int mid = (lo + hi + 1) >> 1;
+      if ((in_lds ? s_rbo[mid] : rbo[mid]) <= b) lo = mid;
+      else hi = mid - 1;
+    }
+    r = lo;
+    x = b - (in_lds ? s_rbo[lo] : rbo[lo]);
+    t3 = f8 = 0;
+    const int q0 = cu_q[r], q1 = cu_q[r + 1], nq = q1 - q0, S = seq_lens[r];
+    if (q0 < 0 || nq < 1 || q1 > n_q_total || S < nq || S > (int64_t)max_pages * PAGE) return;
+    const int last = min(nq * group, (x + 1) * (NSW * 32)) - 1;  // the block's last row
+    const int2 c = cum[(int64_t)r * stride + (S - nq + last / group) / PAGE];
+    t3 = (c.y + 1) / 2;
+    f8 = (c.x + 1) / 2;
+  };
+  const bool cut = may_cut && nblk <= 2 * share;
+  if (!cut) {
+    for (int b = tid; b < nblk; b += 1024) {
+      int r, x, t3, f8;
+      locate(b, r, x, t3, f8);
+      items[2 * b] = make_int4(r, x, 0, t3);
+      items[2 * b + 1] = make_int4(0, f8, -1, 0);
+    }
+    if (tid == 0) {
+      hdr[0] = nblk;
+      hdr[1] = 0;
+    }
+    return;
+  }
+  int cost = 0;
+  if (tid < nblk) {  // nblk <= 2 * share <= MAX_ITEMS
+    locate(tid, s_r[tid], s_x[tid], s_t3[tid], s_f8[tid]);
+    cost = COST3 * s_t3[tid] + COST8 * s_f8[tid];
+    atomicMax(&s_max, cost);
+  }
+  int total;
+  block_excl_scan(cost, scratch, &total);  // its barriers also publish the blocks
+  const int cmax = s_max;
+  // wave w tries size k = w % 8 for 1 + w / 8 rounds
+  {
+    const int R = 1 + (wv >> 3), room = min(R * share, max_slots);
+    // (a part of at least half of MIN_PART: two passes or more)
+    const int U = max(max(MIN_PART, (cmax + MAX_PARTS - 1) / MAX_PARTS), (int)((int64_t)total * (16 + 3 * (wv & 7)) / (16LL * R * share)) + 1);
+    int n = 0;
+    for (int b = lane; b < nblk; b += 64) {
+      const int c = COST3 * s_t3[b] + COST8 * s_f8[b];
+      n += max(1, (c + U - 1) / U);
+    }
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) n += __shfl_xor(n, o, 64);
+    if (lane == 0) {
+      s_est[wv] = n <= room ? R * (min(U, cmax) + CUT_COST) : 0x7FFFFFFF;
+      s_u[wv] = U;
+    }
+  }
+  __syncthreads();
+  int U = max(1, cmax), best = (nblk + share - 1) / share * cmax;  // left whole
+  for (int w = 0; w < 16; ++w)
+    if (s_est[w] < best) {
+      best = s_est[w];
+      U = s_u[w];
+    }
+  // item and part slots
+  const int ns = tid < nblk ? max(1, (cost + U - 1) / U) : 0;
+  int n_items, n_slots, n_split;
+  const int it0 = block_excl_scan(ns, scratch, &n_items);
+  const int sl0 = block_excl_scan(ns > 1 ? ns : 0, scratch, &n_slots);
+  const int sp0 = block_excl_scan(ns > 1 ? 1 : 0, scratch, &n_split);
+  if (tid < nblk) {
+    const int r = s_r[tid], x = s_x[tid], t3 = s_t3[tid], f8 = s_f8[tid];
+    // cost units -> passes
+    auto pass_at = [&](int c) { return c <= COST3 * t3 ? c / COST3 : t3 + (c - COST3 * t3) / COST8; };
+    int j0 = 0;
+    for (int k = 0; k < ns; ++k) {
+      const int j1 = k + 1 == ns ? t3 + f8 : pass_at((int)((int64_t)cost * (k + 1) / ns));
+      const int a3 = min(j0, t3), b3 = min(j1, t3), a8 = max(j0 - t3, 0), b8 = max(j1 - t3, 0);
+      items[2 * (it0 + k)] = make_int4(r, x, a3, b3 - a3);
+      items[2 * (it0 + k) + 1] = make_int4(a8, b8 - a8, ns > 1 ? sl0 + k : -1, 0);
+      j0 = j1;
+    }
+    if (ns > 1) splits[sp0] = make_int4(r, x, sl0, ns);
+  }
+  if (tid == 0) {
+    hdr[0] = n_items;
+    hdr[1] = n_split;
+  }
 }
 
 // fp16 value with its low 3 significand bits cleared (8 significant bits left)
@@ -156,7 +363,7 @@ constexpr float CM_INIT = -1.0e30f;  // running max before the first score (fini
 // LDS of a chunk workgroup (bytes): the ring of raw stages, two buffers of
 // unpacked key operands, two of unpacked value operands, two of the weights
 // the score waves hand to the PV waves, the rows' softmax denominators for
-// the final normalization, and three blocks of the stage table.
+// the final normalization, and four blocks of the page lists.
 template <int D>
 struct ChunkLds {
   static constexpr int NK8 = D / 64, NMB = D / 32;
@@ -173,17 +380,19 @@ struct ChunkLds {
   static constexpr int VB0 = KB0 + 2 * KB;
   static constexpr int WB0 = VB0 + 2 * VB;
   static constexpr int LB0 = WB0 + 2 * NSW * WPW;     // row denominators [score wave][32]
-  static constexpr int LS0 = LB0 + NSW * 32 * 4;      // stage-table blocks [3][64 stages][16]
-  static constexpr int TOTAL = LS0 + 3 * 1024;
+  static constexpr int LS0 = LB0 + NSW * 32 * 4;      // page-list blocks [LBUF][64 pairs][16]
+  static constexpr int LBUF = 4;
+  static constexpr int TOTAL = LS0 + LBUF * 1024;
+  static_assert(CSLOTS8 * STAGE <= WB0, "the FP8 pairs' slots end before the weights");
   static_assert(KB % 16 == 0 && VB % 16 == 0 && STAGE % 16 == 0 && WPW % 16 == 0,
                 "16-byte aligned buffers");
   static_assert(TOTAL <= 160 * 1024, "one workgroup's LDS");
 };
 
-// One 128-row block xb of request r and KV head h (the body of a chunk
-// workgroup; every wave of the workgroup runs it).
+// One work item: passes of the 128-row block xb of request r and KV head h (the
+// body of a chunk workgroup; every wave of the workgroup runs it).
 template <int D>
-__device__ __forceinline__ void chunk_block(const ChunkArgs& a, int r, int h, int xb, uint8_t* smem) {
+__device__ __forceinline__ void chunk_block(const ChunkArgs& a, int4 it0, int4 it1, int h, uint8_t* smem) {
   constexpr int NDW = 3 * D / 128, CL = D / 16, QQ = D / 4;
   constexpr int NKS = D / 16;   // k-steps of the FP8-page score product (16 channels each)
   constexpr int NK8 = D / 64;   // k-steps of the TQ3 score product (64 channels each)
@@ -202,6 +411,10 @@ __device__ __forceinline__ void chunk_block(const ChunkArgs& a, int r, int h, in
   static_assert(CL == 2 * NMB, "a chunk row of V covers two channels per block");
   static_assert(CW == 2 * NSW, "one PV wave per score wave");
   const PoolView& P = a.P;
+  const int r = it0.x, xb = it0.y;
+  const int st3 = it0.w, n_f8 = it1.y;  // TQ3 and FP8 pairs of this item
+  const int n_st = st3 + n_f8;          // its passes
+  const int slot_out = it1.z;           // part slot of a cut block, else -1
   const int tid = threadIdx.x, lane = tid & 63;
   const int wid = __builtin_amdgcn_readfirstlane(tid >> 6);
   const bool score_wave = wid < NSW;
@@ -230,7 +443,6 @@ __device__ __forceinline__ void chunk_block(const ChunkArgs& a, int r, int h, in
     }
     return;
   }
-  if (xb * (NSW * 32) >= rows_r) return;  // whole workgroup past the rows (not with the row-block table)
   // Score waves whose rows all lie past the request's rows still take part
   // in the copies, the unpacking and the barriers; their scores are all
   // masked.
@@ -239,8 +451,7 @@ __device__ __forceinline__ void chunk_block(const ChunkArgs& a, int r, int h, in
   // position); -1 for rows past the request's rows (all masked)
   const int rho_l = rb + li;
   const int lim = rho_l < rows_r ? min(S - 1, P0 + rho_l / G) : -1;
-  const int n8 = a.counts[2 * r], n3 = a.counts[2 * r + 1];
-  const int st3 = (n3 + 1) / 2, n_st = st3 + n8;
+  float* const part = slot_out < 0 ? nullptr : a.parts + ((int64_t)slot_out * H + h) * chunk_part_floats(D);
   uint8_t* const kbuf = smem + LY::KB0;
   uint8_t* const vbuf = smem + LY::VB0;
   uint8_t* const wbuf = smem + LY::WB0;
@@ -256,11 +467,166 @@ __device__ __forceinline__ void chunk_block(const ChunkArgs& a, int r, int h, in
   // this pair's weight slot of stage j
   auto wslot = [&](int j) { return wbuf + ((j & 1) * NSW + sw) * LY::WPW; };
 
-  // Stage j of the loops below is a TQ3 pair for j < st3, else an FP8 page.
+  // Stage j of the loops below is a TQ3 pair for j < st3, else an FP8 pair.
   // Pass p (one barrier each, p = 0 .. n_st): the score waves issue stage
   // p's score product and finish stage p - 1 (scores, softmax, weights into
   // LDS) while the PV waves take stage p - 2 with the weights handed over in
   // pass p - 1.
+  // Ring units: a TQ3 pair is one unit (one slot), an FP8 pair two (page a, page
+  // b).  FP8 unit i = u - st3 follows the TQ3 units round the eight slots, then
+  // takes the four behind them, and so on round all twelve.
+  const int n_units = st3 + 2 * n_f8;
+  // a place in the ring: the unit's FP8 index modulo the twelve slots (0 for a TQ3
+  // unit), the byte of its slot
+  struct Place {
+    int k;
+    uint32_t so;
+  };
+  auto next8 = [&](Place& c) {  // the place of the next FP8 unit
+    if (++c.k == CSLOTS8) {
+      c.k = 0;
+      c.so = (uint32_t)(st3 % CSLOTS) * STAGE;
+    } else if (c.k == CSLOTS) {
+      c.so = CSLOTS * STAGE;
+    } else {
+      c.so += STAGE;
+      if (c.k < CSLOTS && c.so == CSLOTS * STAGE) c.so = 0;
+    }
+  };
+  const Place first8 = {0, (uint32_t)(st3 % CSLOTS) * STAGE};
+  // The item's pairs reach LDS in blocks of 64 (1 KiB), the TQ3 pairs' blocks
+  // first, four buffers, copied by every copying wave itself with the counted copies
+  // of the pages (so its own wait for a page makes the block visible to it, and
+  // the barrier of a pass to the other waves); block k + 2 is copied just
+  // before the first page of block k, as block k + 1 may be the last, short one of
+  // the TQ3 pairs.
+  const uint8_t* lsb = smem + LY::LS0;
+  const int nb3 = (st3 + 63) / 64, n_blk = nb3 + (n_f8 + 63) / 64;
+  // stage j -> {lp_a, id_a, lp_b, id_b}.  A reader keeps one block in registers, lane
+  // l holding its entry l, and takes an entry with lane reads: one LDS read per
+  // 64 stages.
+  struct Reader {
+    int4 v;
+    int k;
+  };
+  auto stage_at = [&](int j, Reader& rd) {
+    j = __builtin_amdgcn_readfirstlane(j);
+    if (j >= n_st) return make_int4(CMASK_LP, 0, CMASK_LP, 0);  // past the list: never used
+    if (j >= st3) j += 64 * nb3 - st3;
+    if ((j >> 6) != rd.k) {
+      rd.k = j >> 6;
+      rd.v = *reinterpret_cast<const int4*>(lsb + ((j >> 6) % LY::LBUF) * 1024 + lane * 16);
+      wait_lgkm0();  // here, so that the lane reads after the join wait for nothing
+    }
+    const int l = j & 63;
+    return make_int4(__builtin_amdgcn_readlane(rd.v.x, l), __builtin_amdgcn_readlane(rd.v.y, l),
+                     __builtin_amdgcn_readlane(rd.v.z, l), __builtin_amdgcn_readlane(rd.v.w, l));
+  };
+  // ---- the copies.  At d = 256 the PV waves' products bound a TQ3 pass, so the
+  // score waves copy; at d = 128 they have half the products and the score waves'
+  // chain of scores, softmax and weights bounds a pass, so the PV waves copy
+  // (measured per TQ3 pass: d = 256 1.93 us with the score waves copying, 2.09
+  // with the PV waves; d = 128 1.49 and 1.36).
+  constexpr bool COPY_PV = D == 128;
+  const int cwv = wid % NSW;
+  // This wave's share of a unit's copies: OPS_W whole KiB (TQ3: KiB w OPS_W ..
+  // of the two pages laid end to end, so waves 0 and 1 copy page a and waves
+  // 2 and 3 page b; FP8: copies w OPS_W .. of the page's 2 NI, waves 0 and 1 its
+  // K and waves 2 and 3 its V, block-permuted as in dma_fp8_page), and for the
+  // even waves one small copy (TQ3: the 32-byte tail of the wave's page; FP8:
+  // the two scales, copied by both so that every unit costs each wave the same
+  // number of copies).
+  const int layer = a.layer;
+  const int hw = cwv >> 1;  // page of a TQ3 pair; K or V of an FP8 page
+  const bool tail_wave = !(cwv & 1);
+  const uint32_t ring_lds = __builtin_amdgcn_readfirstlane(
+      (uint32_t)(uintptr_t)(__attribute__((address_space(3))) void*)smem);
+  const uint8_t* stab3 = reinterpret_cast<const uint8_t*>(a.list3 + (int64_t)r * a.stride + 2 * it0.z);
+  const uint8_t* stab8 = reinterpret_cast<const uint8_t*>(a.list8 + (int64_t)r * a.stride + 2 * it1.x);
+  const uint8_t* tq3_h = P.tq3 + ((int64_t)layer * P.n_tq3 * H + h) * R3;
+  const uint8_t* fp8_h = P.fp8 + ((int64_t)layer * P.n_fp8 * H + h) * R8 + hw * (16 * D) + (cwv & 1) * OPS_W * 16;
+  const uint8_t* scl_h = reinterpret_cast<const uint8_t*>(P.fp8_scales + ((int64_t)layer * P.n_fp8 * H + h) * 2);
+  const uint32_t v3 = 16u * lane + 1024u * (OPS_W * (cwv & 1));
+  const uint32_t v8 = 16u * (uint32_t)(hw ? (ln * 4 + l4) * NI : ln * (D / 16) + l4 * NI);
+  const uint32_t dst3 = ring_lds + hw * R3 + (cwv & 1) * OPS_W * 1024, tail3 = ring_lds + hw * R3 + 16 * D;
+  const uint32_t dst8 = ring_lds + hw * (16 * D) + (cwv & 1) * OPS_W * 1024, tail8 = ring_lds + R8;
+  const uint32_t lst_lds = ring_lds + LY::LS0;
+  static_assert(OPS_W * 2 == MAIN_KB && OPS_W * 2 == NI, "two waves copy one page, or one half of an FP8 page");
+  // unit at byte `so` of the ring: the TQ3 page of this wave, or its share of an FP8 page
+  auto issue3 = [&](uint32_t id, uint32_t so) {
+    const uint8_t* src = tq3_h + (uint64_t)id * (uint32_t)(H * R3);
+#pragma unroll
+    for (int i = 0; i < OPS_W; ++i) dma16<0>(v3 + 1024u * i, src, dst3 + so + 1024 * i);
+    if (tail_wave && lane < 8) dma4(16 * D + 4 * lane, src, tail3 + so);
+  };
+  auto issue8 = [&](uint32_t id, uint32_t so) {
+    const uint8_t* src = fp8_h + (uint64_t)id * (uint32_t)(H * R8);
+#pragma unroll
+    for (int i = 0; i < OPS_W; ++i) dma16<0>(v8, src + 16 * i, dst8 + so + 1024 * i);
+    if (tail_wave && lane < 2) dma4(4 * lane, scl_h + (uint64_t)id * (uint32_t)(8 * H), tail8 + so);
+  };
+  auto issue_list = [&](int k) {  // block k of the lists -> buffer k % LBUF
+    dma16<0>(16u * lane, k < nb3 ? stab3 + 1024 * k : stab8 + 1024 * (k - nb3), lst_lds + (k % LY::LBUF) * 1024);
+  };
+  // Ring bookkeeping: `issued` units have been copied so far.  The slot of
+  // TQ3 pair s is free from pass s + 2 on (its keys are unpacked in pass s - 1,
+  // its values and key-norm corrections read in pass s + 1), those of the FP8
+  // pair of pass s from pass s + 3 on (read by the score waves in pass s, by
+  // the copying waves in pass s + 2), the slots behind the ring from pass st3 + 2
+  // on (the last TQ3 values are read in pass st3 + 1).
+  int issued = 0;
+  auto stage_of_unit = [&](int u) { return u < st3 ? u : st3 + (u - st3) / 2; };
+  Reader rd_iss = {make_int4(0, 0, 0, 0), -1};
+  int4 e_iss = make_int4(0, 0, 0, 0);  // the entry of unit `issued`'s stage
+  Place pl = {0, 0};                   // its place
+  auto refill = [&](int pass) {
+    while (issued < n_units) {
+      const int i = issued - st3;
+      int ready;  // the pass from which the unit's slot is free
+      if (i < CSLOTS) ready = issued < CSLOTS ? -1 : issued - CSLOTS + 2;
+      else if (i < CSLOTS8) ready = st3 > 0 ? st3 + 2 : -1;
+      else ready = st3 + (i - CSLOTS8) / 2 + 3;
+      if (ready > pass) break;
+      // a masked page b reads page a (its weights are zero, its values have to be finite)
+      const int id_b = e_iss.z == CMASK_LP ? e_iss.y : e_iss.w;
+      const bool first = i < 0 || !(i & 1);  // the first unit of its stage
+      if (first) {
+        const int j = i < 0 ? issued : (i >> 1) + 64 * nb3;
+        if ((j & 63) == 0 && (j >> 6) + 2 < n_blk) issue_list((j >> 6) + 2);
+      }
+      ++issued;
+      if (i < 0) {
+        issue3(__builtin_amdgcn_readfirstlane(hw ? id_b : e_iss.y), pl.so);
+        pl.so += STAGE;
+        if (pl.so == CSLOTS * STAGE) pl.so = 0;
+      } else {
+        issue8(__builtin_amdgcn_readfirstlane(first ? e_iss.y : id_b), pl.so);
+        next8(pl);
+      }
+      if (i < 0 || (i & 1)) e_iss = stage_at(stage_of_unit(issued), rd_iss);
+    }
+  };
+  // before the barrier of pass p: pair p + 1 of the TQ3 pairs (its keys are
+  // unpacked in pass p), pair p of the FP8 pairs has landed; the copies after it
+  // (four units once the ring is full) stay in flight
+  auto wait_for = [&](int p) {
+    int u;
+    if (p + 1 < st3) u = p + 1;
+    else if (p >= st3 && p < n_st) u = st3 + 2 * (p - st3) + 1;
+    else return;
+    if (issued - 1 - u >= 4) {
+      if (tail_wave) wait_vmcnt<4 * (OPS_W + 1)>();
+      else wait_vmcnt<4 * OPS_W>();
+    } else {
+      wait_vmcnt<0>();
+    }
+  };
+  auto start_copies = [&]() {
+    for (int k = 0; k < min(n_blk, 2); ++k) issue_list(k);
+    wait_vmcnt<0>();
+    e_iss = stage_at(0, rd_iss);
+    refill(-1);
+  };
   if (score_wave) {
     // ======================= score waves =======================
     // The score waves' instructions go first on the SIMD (their weights gate
@@ -270,133 +636,7 @@ __device__ __forceinline__ void chunk_block(const ChunkArgs& a, int r, int h, in
     __asm__ __volatile__("" : "+v"(neg1));
     const int rho_c = min(rho_l, rows_r - 1);  // a valid row to load for masked lanes
     const uint16_t* qrow_ptr = a.q + ((int64_t)(q0 + rho_c / G) * Hq + h * G + rho_c % G) * D;
-    const uint8_t* stab = reinterpret_cast<const uint8_t*>(a.stages + (int64_t)r * mp);
-    // The stage table reaches LDS in blocks of 64 stages (1 KiB), three
-    // buffers, copied by every score wave itself with the counted copies of
-    // the pages (so its own wait for a page makes the block visible to it);
-    // block k + 1 is copied just before the first page of block k.
-    const uint8_t* lsb = smem + LY::LS0;
-    // stage j -> {lp_a, id_a, lp_b, id_b}; id_b < 0 marks an FP8 stage.  Two
-    // readers (c = 0: the stage being scored, c = 1: the next stage to copy)
-    // each keep one block in registers, lane l holding stage 64 k + l, and
-    // take an entry with lane reads: one LDS read per 64 stages.
-    int4 blk_v[2] = {make_int4(0, 0, 0, 0), make_int4(0, 0, 0, 0)};
-    int blk_k[2] = {-1, -1};
-    auto stage_at = [&](int j, int c) {
-      j = __builtin_amdgcn_readfirstlane(j);
-      if (j >= n_st) return make_int4(CMASK_LP, 0, CMASK_LP, 0);  // past the list: never used
-      if ((j >> 6) != blk_k[c]) {
-        blk_k[c] = j >> 6;
-        blk_v[c] = *reinterpret_cast<const int4*>(lsb + ((j >> 6) % 3) * 1024 + lane * 16);
-        wait_lgkm0();  // here, so that the lane reads after the join wait for nothing
-      }
-      const int l = j & 63;
-      return make_int4(__builtin_amdgcn_readlane(blk_v[c].x, l), __builtin_amdgcn_readlane(blk_v[c].y, l),
-                       __builtin_amdgcn_readlane(blk_v[c].z, l), __builtin_amdgcn_readlane(blk_v[c].w, l));
-    };
-    const int layer = a.layer;
-    const uint8_t* tq3_l = P.tq3 + (int64_t)layer * P.n_tq3 * H * R3;
-    const uint8_t* fp8_l = P.fp8 + (int64_t)layer * P.n_fp8 * H * R8;
-    const uint8_t* scl_l = reinterpret_cast<const uint8_t*>(P.fp8_scales + (int64_t)layer * P.n_fp8 * H * 2);
-    const uint32_t ring_lds = __builtin_amdgcn_readfirstlane(
-        (uint32_t)(uintptr_t)(__attribute__((address_space(3))) void*)smem);
-    // FP8 pages land block-permuted (see dma_fp8_page): per-lane source offsets
-    const uint32_t vk = 16u * (uint32_t)(ln * (D / 16) + l4 * NI);
-    const uint32_t vv = 16u * (uint32_t)((ln * 4 + l4) * NI);
-    // This wave's share of stage e's copies into ring slot `slot`: OPS_W
-    // whole KiB (TQ3: KiB w OPS_W .. of the two pages laid end to end; FP8:
-    // copies w OPS_W .. of the page's 2 NI), and for waves 0 and 1 one small
-    // copy (TQ3: the 32-byte tail of page a resp. b; FP8: the two scales,
-    // copied by both so that every stage costs each wave the same number of
-    // copies).  Only the score waves copy.
-    auto issue = [&](int4 e, int slot) {
-      // wave-uniform by construction; said so for the scalar operands of the copies
-      slot = __builtin_amdgcn_readfirstlane(slot);
-      e.y = __builtin_amdgcn_readfirstlane(e.y);
-      e.w = __builtin_amdgcn_readfirstlane(e.w);
-      const uint32_t dst = ring_lds + slot * STAGE;
-      if (e.w >= 0) {
-#pragma unroll
-        for (int i = 0; i < OPS_W; ++i) {
-          const int g = wid * OPS_W + i, pg = g / MAIN_KB, kb = g % MAIN_KB;
-          const int id = pg ? e.w : e.y;
-          dma16<0>(16u * lane + 1024u * kb, tq3_l + ((int64_t)id * H + h) * R3,
-                   dst + pg * R3 + 1024 * kb);
-        }
-        if (wid < 2) {
-          const int id = wid ? e.w : e.y;
-          if (lane < 8) dma4(16 * D + 4 * lane, tq3_l + ((int64_t)id * H + h) * R3, dst + wid * R3 + 16 * D);
-        }
-      } else {
-        const uint8_t* src = fp8_l + ((int64_t)e.y * H + h) * R8;
-#pragma unroll
-        for (int i = 0; i < OPS_W; ++i) {
-          const int op = wid * OPS_W + i;
-          if (op < NI)
-            dma16<0>(vk, src + 16 * op, dst + 1024 * op);
-          else
-            dma16<0>(vv, src + 16 * D + 16 * (op - NI), dst + 16 * D + 1024 * (op - NI));
-        }
-        if (wid < 2 && lane < 2) dma4(4 * lane, scl_l + ((int64_t)e.y * H + h) * 8, dst + R8);
-      }
-    };
-    // Ring bookkeeping: stage s sits in slot s % CSLOTS; `issued` stages have
-    // been copied so far.  The slot of a TQ3 pair s is free from pass s + 2
-    // on (its keys are unpacked in pass s - 1, its values and key-norm
-    // corrections read in pass s + 1), that of an FP8 page s from pass s + 3
-    // on (read by the score waves in pass s, by the PV waves in pass
-    // s + 2).  A wait for stage s lets the copies of the
-    // stages after it stay in flight (every stage costs a wave the same
-    // copies).
-    const uint32_t lst_lds = ring_lds + LY::LS0;
-    auto issue_list = [&](int k) {  // block k of the stage table -> buffer k % 3
-      dma16<0>(16u * lane, stab + 1024 * k, lst_lds + (k % 3) * 1024);
-    };
-    const int n_blk = (n_st + 63) / 64;
-    int issued = 0;
-    issue_list(0);
-    if (n_blk > 1) issue_list(1);
-    wait_vmcnt<0>();
-    int4 e_iss = stage_at(0, 1);  // the entries of stage `issued`
-    auto refill = [&](int pass) {
-      bool fresh = true;  // e_iss holds stage `issued`
-      while (issued < n_st) {
-        const int prev = issued - CSLOTS;
-        if (prev >= 0 && (prev < st3 ? prev + 2 : prev + 3) > pass) break;
-        if (!fresh) e_iss = stage_at(issued, 1);
-        if ((issued & 63) == 0 && issued > 0 && (issued >> 6) + 1 < n_blk) issue_list((issued >> 6) + 1);
-        issue(e_iss, issued % CSLOTS);
-        ++issued;
-        fresh = false;
-      }
-    };
-    // entries of the next stage to copy, loaded at the end of a pass (the
-    // barrier's wait covers their latency)
-    auto prefetch_iss = [&]() { e_iss = stage_at(issued, 1); };
-    auto wait_for = [&](int s) {
-      const int later = max(0, min(issued - 1 - s, CSLOTS - 1));
-#define MKV_CHUNK_WAIT(n)                                   \
-  case n:                                                  \
-    if (wid < 2) wait_vmcnt<(n) * (OPS_W + 1)>();          \
-    else wait_vmcnt<(n) * OPS_W>();                        \
-    break;
-      switch (later) {
-        MKV_CHUNK_WAIT(1)
-        MKV_CHUNK_WAIT(2)
-        MKV_CHUNK_WAIT(3)
-        MKV_CHUNK_WAIT(4)
-        MKV_CHUNK_WAIT(5)
-        MKV_CHUNK_WAIT(6)
-        MKV_CHUNK_WAIT(7)
-        default: wait_vmcnt<0>(); break;
-      }
-#undef MKV_CHUNK_WAIT
-    };
-    static_assert(CSLOTS <= 8 && (CSLOTS - 1) * (OPS_W + 1) < 64,
-                  "wait_for covers up to seven stages in flight");
-    refill(-1);
-    prefetch_iss();
-
+    if constexpr (!COPY_PV) start_copies();
     // ---- rotated query of this lane's row, q_rot = R q (R = d^-1/2 H
     // diag(sigma)), times the softmax scale log2(e)/sqrt(d) (scores come out
     // in base 2) and a power-of-two row scale qsc that puts the row's
@@ -763,11 +1003,12 @@ __device__ __forceinline__ void chunk_block(const ChunkArgs& a, int r, int h, in
       __builtin_amdgcn_sched_barrier(0);
       mf(11);
     };
-    if (st3 > 0) wait_for(0);
-    barrier();
+    Reader rd_prev = {make_int4(0, 0, 0, 0), -1};
+    if constexpr (!COPY_PV) wait_for(-1);
+    barrier();  // pair 0 has landed
     if (st3 > 0 && wid < 2) unpack_k(smem, kbuf);
     for (int p = 0; p < st3; ++p) {
-      if (p + 1 < st3) wait_for(p + 1);
+      if constexpr (!COPY_PV) wait_for(p);
       barrier();  // keys of pair p unpacked; raw pair p + 1 landed
       // (in the last pass the key unpacking reads a slot that holds no pair
       // and writes a buffer nobody reads any more)
@@ -790,20 +1031,20 @@ __device__ __forceinline__ void chunk_block(const ChunkArgs& a, int r, int h, in
         else
           tq3_pass(p, st, std::true_type{}, std::false_type{});
       }
-      refill(p);
+      if constexpr (!COPY_PV) refill(p);
       st_prev = st;
-      e_prev = stage_at(p, 0);
-      prefetch_iss();
+      e_prev = stage_at(p, rd_prev);
     }
-    // ---- passes over the FP8 pages: pass p scores page p with plain
-    // queries as fp16 (bf16 -> fp16 is exact for the query range) against
-    // its FP8 keys, straight from the ring, and finishes the weights of
-    // stage p - 1 (for p = st3 the last TQ3 pair, whose values it also
-    // unpacks); the last pass only finishes.  Lane (li, lg) holds, for
-    // k-step s, channels (D/2) lg + 8 s + b (b < 8) of its row.
+    // ---- passes over the FP8 pairs: pass p scores pair p with plain queries as
+    // fp16 (bf16 -> fp16 is exact for the query range) against its FP8 keys,
+    // straight from the ring, and between those MFMAs finishes the weights of
+    // stage p - 1 (for p = st3 the last TQ3 pair, whose values it also unpacks);
+    // the last pass only finishes.  Score rows 0-15 are page a's tokens, 16-31
+    // page b's; lane (li, lg) holds, for k-step s, channels (D/2) lg + 8 s + b
+    // (b < 8) of its row.
     {
       half8 qop[NKS];
-      if (st3 < n_st) {
+      if (n_f8 > 0) {
         const uint16_t* qrow = qrow_ptr + (D / 2) * lg;
 #pragma unroll
         for (int s = 0; s < NKS; ++s) {
@@ -813,35 +1054,42 @@ __device__ __forceinline__ void chunk_block(const ChunkArgs& a, int r, int h, in
           for (int j = 0; j < 8; ++j) qop[s][j] = (_Float16)bf16_to_f32(hb[j]);
         }
       }
-      float2 ks_prev = make_float2(0.0f, 0.0f);  // key and value scales of FP8 stage p - 1
+      // key and value scales of the pages of FP8 stage p - 1
+      float2 ksa_prev = make_float2(0.0f, 0.0f), ksb_prev = ksa_prev;
+      Place pl8 = first8;  // of the next pair's page a
       for (int p = st3; p <= n_st; ++p) {
-        if (p < n_st) wait_for(p);
-        barrier();  // page p visible
-        refill(p);
+        const uint32_t so_a = pl8.so;
+        next8(pl8);
+        const uint32_t so_b = pl8.so;
+        next8(pl8);
+        if constexpr (!COPY_PV) wait_for(p);
+        barrier();  // pair p visible
+        if constexpr (!COPY_PV) refill(p);
+        // (in the last pass the product reads slots that hold no pair and is not used)
         float16v st = {};
-        float2 ksv = make_float2(0.0f, 0.0f);
-        if (p < n_st) {
-          const uint8_t* ra = smem + (p % CSLOTS) * STAGE;
-          // block-permuted page (see dma_fp8_page): 16-byte block 64 w + 16
-          // Q + t holds bytes 16 w .. of token t's channel quarter Q (K);
-          // score rows 0-15 are the page's tokens, 16-31 zero
-          const uint2* pk = reinterpret_cast<const uint2*>(ra);
-          ksv = *reinterpret_cast<const float2*>(ra + R8);
+        uint4 kw[NKS / 2];  // this lane's key bytes: 16-byte block w holds k-steps 2 w, 2 w + 1
+        const uint8_t* ra = smem + so_a;
+        const uint8_t* rb_ = smem + so_b;
+        // block-permuted page (see dma_fp8_page): 16-byte block 64 w + 16
+        // Q + t holds bytes 16 w .. of token t's channel quarter Q (K)
+        const uint4* pk = reinterpret_cast<const uint4*>(li < 16 ? ra : rb_) + 32 * lg + (li & 15);
 #pragma unroll
-          for (int s = 0; s < NKS; ++s) {
-            const int Q = 2 * lg + s / KPC, off = 8 * (s % KPC);
-            half8 K = {};
-            if (li < 16) {
-              const uint2 kw = pk[2 * (64 * (off / 16) + 16 * Q + li) + (off / 8) % 2];
-              K = h8(cvt_lo(kw.x), cvt_hi(kw.x), cvt_lo(kw.y), cvt_hi(kw.y));
-            }
+        for (int w = 0; w < NKS / 2; ++w) kw[w] = pk[64 * (w % (KPC / 2)) + 16 * (w / (KPC / 2))];
+        const float2 ksa = *reinterpret_cast<const float2*>(ra + R8), ksb = *reinterpret_cast<const float2*>(rb_ + R8);
+        auto mf = [&](int s) {
+          if (s < NKS) {
+            const uint32_t k0 = s & 1 ? kw[s / 2].z : kw[s / 2].x, k1 = s & 1 ? kw[s / 2].w : kw[s / 2].y;
+            const half8 K = h8(cvt_lo(k0), cvt_hi(k0), cvt_lo(k1), cvt_hi(k1));
             st = __builtin_amdgcn_mfma_f32_32x32x16_f16(K, qop[s], st, 0, 0, 0);
           }
-        }
-        if (p > 0) {
-          TqW w;
-          float alpha;
-          if (p == st3) {  // the last TQ3 pair
+          __builtin_amdgcn_sched_barrier(0);
+        };
+        if (p == st3) {
+#pragma unroll
+          for (int s = 0; s < NKS; ++s) mf(s);
+          if (p > 0) {  // the last TQ3 pair
+            TqW w;
+            float alpha;
             const uint8_t* rs_prev = smem + ((p + CSLOTS - 1) % CSLOTS) * STAGE;
             uint8_t* vb_prev = vbuf + ((p + 1) & 1) * LY::VB;
             if (unmasked(e_prev))
@@ -850,37 +1098,78 @@ __device__ __forceinline__ void chunk_block(const ChunkArgs& a, int r, int h, in
               tq3_scores(rs_prev, st_prev, e_prev, w, alpha, std::true_type{});
             if (wid >= 2) unpack_v(rs_prev, vb_prev);
             unpack_side(rs_prev, vb_prev);
-          } else {
-            float sc[16];
-            const float kk = ks_prev.x * smk;
+            put_weights(p - 1, w, alpha);
+          }
+        } else {
+          TqW w;
+          float sc[16], alpha, lsum = 0.0f, m_new;
+          auto scores = [&](int e4) {
+            const int t0 = (e4 < 2 ? e_prev.x : e_prev.z) * PAGE + 8 * (e4 & 1) + 4 * lg;
+            const float kk = (e4 < 2 ? ksa_prev.x : ksb_prev.x) * smk;
 #pragma unroll
-            for (int e4 = 0; e4 < 4; ++e4) {
-              const int t0 = e_prev.x * PAGE + 8 * (e4 & 1) + 4 * lg;
+            for (int u = 0; u < 4; ++u) sc[4 * e4 + u] = t0 + u <= lim ? st_prev[4 * e4 + u] * kk : -INFINITY;
+          };
+          auto ex = [&](int k0) {
 #pragma unroll
-              for (int u = 0; u < 4; ++u)
-                sc[4 * e4 + u] = (e4 < 2 && t0 + u <= lim) ? st_prev[4 * e4 + u] * kk : -INFINITY;
+            for (int k = k0; k < k0 + 4; ++k) {
+              sc[k] = __builtin_amdgcn_exp2f(sc[k] - m_new);  // -inf -> 0
+              lsum += sc[k];
             }
-            softmax(sc, alpha);
-            // the page's V scale folded into the weights
+          };
+          // weights of page a (k0 = 0) or b (k0 = 8), the page's V scale folded in
+          auto split = [&](int k0, float vs, half8& hi, half8& lo) {
             float pw[8];
 #pragma unroll
-            for (int k = 0; k < 8; ++k) pw[k] = sc[k] * ks_prev.y;
-            split8(pw, w.ha, w.la);
-            w.hb = w.la;
-            w.lb = w.la;
-            w.z = w.la;
+            for (int k = 0; k < 8; ++k) pw[k] = sc[k0 + k] * vs;
+            split8(pw, hi, lo);
+          };
+          mf(0);
+          scores(0);
+          scores(1);
+          mf(1);
+          scores(2);
+          scores(3);
+          mf(2);
+          {
+            float mx = sc[0];
+#pragma unroll
+            for (int k = 1; k < 16; ++k) mx = fmaxf(mx, sc[k]);
+            mx = fmaxf(mx, lane_xor<32>(mx, lane));
+            m_new = mx > m_run + 8.0f ? mx : m_run;
+            alpha = __builtin_amdgcn_exp2f(m_run - m_new);
+            m_run = m_new;
           }
+          mf(3);
+          ex(0);
+          mf(4);
+          ex(4);
+          mf(5);
+          split(0, ksa_prev.y, w.ha, w.la);
+          mf(6);
+          ex(8);
+          mf(7);
+          ex(12);
+          l_run = fmaf(l_run, alpha, lsum);
+          mf(8);
+          split(8, ksb_prev.y, w.hb, w.lb);
+          mf(9);
+          w.z = w.la;
           put_weights(p - 1, w, alpha);
+#pragma unroll
+          for (int s = 10; s < NKS; ++s) mf(s);
         }
         st_prev = st;
-        ks_prev = ksv;
-        e_prev = stage_at(p, 0);
-        prefetch_iss();
+        ksa_prev = ksa;
+        ksb_prev = ksb;
+        e_prev = stage_at(p, rd_prev);
       }
     }
     barrier();  // the PV waves' last pass
     const float L = l_run + lane_xor<32>(l_run, lane);
-    if (lg == 0) lbuf[sw * 32 + li] = L;
+    if (lg == 0) {
+      if (part) reinterpret_cast<float2*>(part + 128 * D)[sw * 32 + li] = make_float2(m_run, L);
+      else lbuf[sw * 32 + li] = L;
+    }
     barrier();
   } else {
     // ========================= PV waves =========================
@@ -918,14 +1207,7 @@ __device__ __forceinline__ void chunk_block(const ChunkArgs& a, int r, int h, in
           for (int g = 0; g < NSW; ++g) acc[b][g] *= al[g];  // column = this lane's row
       }
     };
-    auto ld_w = [&](int j, int g, TqW& w) {
-      const uint8_t* ws = wsl(j, g);
-      w.ha = *reinterpret_cast<const half8*>(ws + 0 * 1024 + 16 * lane);
-      w.la = *reinterpret_cast<const half8*>(ws + 1 * 1024 + 16 * lane);
-      w.hb = *reinterpret_cast<const half8*>(ws + 2 * 1024 + 16 * lane);
-      w.lb = *reinterpret_cast<const half8*>(ws + 3 * 1024 + 16 * lane);
-      w.z = *reinterpret_cast<const half8*>(ws + 4 * 1024 + 16 * lane);
-    };
+    constexpr int REFILL_AT = 1;
     // O^T += V^T P^T for the TQ3 pair of stage j (values unpacked in vb),
     // with exact V operands: v = zero + scale * code is split as scale_hi *
     // code + scale_lo * code + zero.  The products that reach fp32 accuracy:
@@ -933,93 +1215,173 @@ __device__ __forceinline__ void chunk_block(const ChunkArgs& a, int r, int h, in
     // scale_lo sits below 2^-19 of the value), and the zero term as zero_a
     // (sum of weights over page a) + zero_b (same for b), whose sums the
     // MFMA completes across the two lane groups.
+    // Order: page a's products for each score wave's rows, then page b's, then the
+    // zero terms, so the first product waits for page a's operands only; page b's
+    // are built between page a's products (a few VALU instructions in the shadow
+    // of each MFMA), and the weights are read two steps ahead.
+    struct VOp {
+      half2v h[4], l[4];
+    };
+    struct W2 {
+      half8 h, l;
+    };
+    // weights (hi, lo) of step t = 4 p + g: page p, score wave g
+    auto ld_w2 = [&](int j, int t, W2& w) {
+      const uint8_t* ws = wsl(j, t % NSW) + 2 * (t / NSW) * 1024 + 16 * lane;
+      w.h = *reinterpret_cast<const half8*>(ws);
+      w.l = *reinterpret_cast<const half8*>(ws + 1024);
+    };
     auto tq3_pv = [&](int j) {
       const uint8_t* vb = vbuf + (j & 1) * LY::VB;
       const _Float16* zx = reinterpret_cast<const _Float16*>(vb + LY::VX + LY::SX);
-      struct Ops {
-        half8 A1[2], A2[2], Az;
-      };
-      // the weights of score wave g + 1 are read while the products of g run
-      TqW wb[2];
-      ld_w(j, 0, wb[0]);
-      Ops op[NBW];
+      uint2 cw[2][NBW];
+      half2v s2[2][NBW];
 #pragma unroll
-      for (int b = 0; b < NBW; ++b) {
-        const int mb = NBW * pv + b;
+      for (int p = 0; p < 2; ++p)
 #pragma unroll
-        for (int p = 0; p < 2; ++p) {
-          const uint2 cw = *reinterpret_cast<const uint2*>(vb + ((p * NMB + mb) * 64 + lane) * 8);
-          const half2v s2 = *reinterpret_cast<const half2v*>(vb + LY::VX + ((p * NMB + mb) * 32 + li) * 4);
-          const half2v sh = bcast(s2[0]), sl = bcast(s2[1]);
-          const half2v c01 = cvt_code<false>(cw.x), c23 = cvt_code<true>(cw.x);
-          const half2v c45 = cvt_code<false>(cw.y), c67 = cvt_code<true>(cw.y);
-          op[b].A1[p] = h8(c01 * sh, c23 * sh, c45 * sh, c67 * sh);
-          op[b].A2[p] = h8(c01 * sl, c23 * sl, c45 * sl, c67 * sl);
+        for (int b = 0; b < NBW; ++b) {
+          const int mb = NBW * pv + b;
+          cw[p][b] = *reinterpret_cast<const uint2*>(vb + ((p * NMB + mb) * 64 + lane) * 8);
+          s2[p][b] = *reinterpret_cast<const half2v*>(vb + LY::VX + ((p * NMB + mb) * 32 + li) * 4);
         }
-        const _Float16 za = zx[mb * 32 + li], zb = zx[(NMB + mb) * 32 + li];
-        op[b].Az = half8{za, zb, za, zb, (_Float16)0.0f, (_Float16)0.0f, (_Float16)0.0f, (_Float16)0.0f};
-      }
+      W2 w[3];
+      ld_w2(j, 0, w[0]);
+      ld_w2(j, 1, w[1]);
       rescale(j);
+      // quarter q (two tokens) of the operand of (page p, block b)
+      auto build = [&](VOp& o, int p, int b, int q) {
+        const half2v sh = bcast(s2[p][b][0]), sl = bcast(s2[p][b][1]);
+        const uint32_t c4 = q < 2 ? cw[p][b].x : cw[p][b].y;
+        const half2v c = q & 1 ? cvt_code<true>(c4) : cvt_code<false>(c4);
+        o.h[q] = c * sh;
+        o.l[q] = c * sl;
+      };
+      VOp op[2][NBW];
 #pragma unroll
-      for (int g = 0; g < NSW; ++g) {
-        if (g + 1 < NSW) ld_w(j, g + 1, wb[(g + 1) & 1]);
+      for (int b = 0; b < NBW; ++b)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) build(op[0][b], 0, b, q);
+      half8 zw[2], Az[NBW];
+      auto ld_z = [&](int g) { zw[g & 1] = *reinterpret_cast<const half8*>(wsl(j, g) + 4 * 1024 + 16 * lane); };
+#pragma unroll
+      for (int t = 0; t < 2 * NSW; ++t) {
+        const int p = t / NSW, g = t % NSW;
+        if (t + 2 < 2 * NSW) ld_w2(j, t + 2, w[(t + 2) % 3]);
+        if (t == 2 * NSW - 2) {
+#pragma unroll
+          for (int b = 0; b < NBW; ++b) {
+            const int mb = NBW * pv + b;
+            const _Float16 za = zx[mb * 32 + li], zb = zx[(NMB + mb) * 32 + li];
+            Az[b] = half8{za, zb, za, zb, (_Float16)0.0f, (_Float16)0.0f, (_Float16)0.0f, (_Float16)0.0f};
+          }
+          ld_z(0);
+        }
+        if (t == 2 * NSW - 1) ld_z(1);
         __builtin_amdgcn_sched_barrier(0);
-        const TqW& w = wb[g & 1];
-        // the blocks' chains interleaved
-#define MKV_PV(A, B)                                                                     \
-  _Pragma("unroll") for (int b = 0; b < NBW; ++b) acc[b][g] =                            \
-      __builtin_amdgcn_mfma_f32_32x32x16_f16(op[b].A, w.B, acc[b][g], 0, 0, 0);
-        MKV_PV(A1[0], ha)
-        MKV_PV(A2[0], ha)
-        MKV_PV(A1[0], la)
-        MKV_PV(A1[1], hb)
-        MKV_PV(A2[1], hb)
-        MKV_PV(A1[1], lb)
-        MKV_PV(Az, z)
-#undef MKV_PV
-      }
-    };
-    // O^T += V^T P^T for the FP8 page of stage j in ring slot ra (weights hi +
-    // lo, the page's V scale already folded in): lane-chunks (rrow, lg) and
-    // (rrow, lg + 2) of V, dword m = tokens 4 g' .. 4 g' + 3 of channel CL
-    // rrow + m
-    auto fp8_pv = [&](const uint8_t* ra, int j) {
-      const int rrow = li & 15, hh = li >> 4;
-      const uint2* pvp = reinterpret_cast<const uint2*>(ra + PAGE * D);
-      half8 Av[NBW];
 #pragma unroll
-      for (int b = 0; b < NBW; ++b) {
-        const int mb = NBW * pv + b;
-        const int blk = 64 * (mb / 2);
-        const uint2 v0 = pvp[2 * (blk + 16 * lg + rrow) + (mb & 1)];
-        const uint2 v2 = pvp[2 * (blk + 16 * (lg + 2) + rrow) + (mb & 1)];
-        const uint32_t w0 = hh ? v0.y : v0.x, w2 = hh ? v2.y : v2.x;
-        Av[b] = h8(cvt_lo(w0), cvt_hi(w0), cvt_lo(w2), cvt_hi(w2));
+        for (int k = 0; k < 3; ++k)
+#pragma unroll
+          for (int b = 0; b < NBW; ++b) {
+            const VOp& o = op[p][b];
+            const half8 A = k == 1 ? h8(o.l[0], o.l[1], o.l[2], o.l[3]) : h8(o.h[0], o.h[1], o.h[2], o.h[3]);
+            acc[b][g] = __builtin_amdgcn_mfma_f32_32x32x16_f16(A, k == 2 ? w[t % 3].l : w[t % 3].h, acc[b][g], 0, 0, 0);
+            if (p == 0 && k == 0) build(op[1][b], 1, b, g);
+            __builtin_amdgcn_sched_barrier(0);
+          }
+        if constexpr (COPY_PV)
+          if (t == REFILL_AT) refill(j + 2);  // the slots this pass frees
       }
-      rescale(j);
 #pragma unroll
       for (int g = 0; g < NSW; ++g) {
-        const uint8_t* ws = wsl(j, g);
-        const half8 ha = *reinterpret_cast<const half8*>(ws + 0 * 1024 + 16 * lane);
-        const half8 la = *reinterpret_cast<const half8*>(ws + 1 * 1024 + 16 * lane);
+        const half8 z = zw[g & 1];
+        if (g + 2 < NSW) ld_z(g + 2);
 #pragma unroll
-        for (int b = 0; b < NBW; ++b) acc[b][g] = __builtin_amdgcn_mfma_f32_32x32x16_f16(Av[b], ha, acc[b][g], 0, 0, 0);
-#pragma unroll
-        for (int b = 0; b < NBW; ++b) acc[b][g] = __builtin_amdgcn_mfma_f32_32x32x16_f16(Av[b], la, acc[b][g], 0, 0, 0);
+        for (int b = 0; b < NBW; ++b)
+          acc[b][g] = __builtin_amdgcn_mfma_f32_32x32x16_f16(Az[b], z, acc[b][g], 0, 0, 0);
+        __builtin_amdgcn_sched_barrier(0);
       }
     };
-    barrier();  // the score waves' first key unpacking
-    barrier();  // pass 0: the score product of stage 0
-    barrier();  // pass 1: the weights of stage 0
+    // O^T += V^T P^T for the FP8 pair of stage j (weights hi + lo, the pages' V
+    // scales already folded in): lane-chunks (rrow, lg) and (rrow, lg + 2) of V,
+    // dword m = tokens 4 g' .. 4 g' + 3 of channel CL rrow + m
+    Place pl8 = first8;  // of the next FP8 pair's page a
+    auto fp8_pv = [&](int j) {
+      const int rrow = li & 15, hh = li >> 4;
+      uint32_t vw[2][NBW][2];
+#pragma unroll
+      for (int p = 0; p < 2; ++p) {
+        const uint2* pvp = reinterpret_cast<const uint2*>(smem + pl8.so + PAGE * D);
+        next8(pl8);
+#pragma unroll
+        for (int b = 0; b < NBW; ++b) {
+          const int mb = NBW * pv + b;
+          const int blk = 64 * (mb / 2);
+          const uint2 v0 = pvp[2 * (blk + 16 * lg + rrow) + (mb & 1)];
+          const uint2 v2 = pvp[2 * (blk + 16 * (lg + 2) + rrow) + (mb & 1)];
+          vw[p][b][0] = hh ? v0.y : v0.x;
+          vw[p][b][1] = hh ? v2.y : v2.x;
+        }
+      }
+      W2 w[3];
+      ld_w2(j, 0, w[0]);
+      ld_w2(j, 1, w[1]);
+      rescale(j);
+      auto op_of = [&](int p, int b) {
+        return h8(cvt_lo(vw[p][b][0]), cvt_hi(vw[p][b][0]), cvt_lo(vw[p][b][1]), cvt_hi(vw[p][b][1]));
+      };
+      half8 A[2][NBW];
+#pragma unroll
+      for (int b = 0; b < NBW; ++b) A[0][b] = op_of(0, b);
+#pragma unroll
+      for (int t = 0; t < 2 * NSW; ++t) {
+        const int p = t / NSW, g = t % NSW;
+        if (t + 2 < 2 * NSW) ld_w2(j, t + 2, w[(t + 2) % 3]);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int k = 0; k < 2; ++k)
+#pragma unroll
+          for (int b = 0; b < NBW; ++b) {
+            acc[b][g] = __builtin_amdgcn_mfma_f32_32x32x16_f16(A[p][b], k ? w[t % 3].l : w[t % 3].h, acc[b][g], 0, 0, 0);
+            if (t == 0 && k == 0) A[1][b] = op_of(1, b);
+            __builtin_amdgcn_sched_barrier(0);
+          }
+        if constexpr (COPY_PV)
+          if (t == REFILL_AT) refill(j + 2);
+      }
+    };
+    if constexpr (COPY_PV) {
+      start_copies();
+      wait_for(-1);
+    }
+    barrier();  // pair 0 has landed
+    for (int p = 0; p < 2; ++p) {  // the score product, then the weights of stage 0
+      if constexpr (COPY_PV) wait_for(p);
+      barrier();
+      if constexpr (COPY_PV) refill(p);
+    }
     for (int j = 0; j < st3; ++j) {  // pass j + 2
+      if constexpr (COPY_PV) wait_for(j + 2);
       barrier();
       tq3_pv(j);
     }
     for (int j = st3; j < n_st; ++j) {
+      if constexpr (COPY_PV) wait_for(j + 2);
       barrier();
-      fp8_pv(smem + (j % CSLOTS) * STAGE, j);
+      fp8_pv(j);
     }
     barrier();  // the rows' denominators
+    if (part) {  // a part of a cut block: the accumulators as they stand
+      float4* o = reinterpret_cast<float4*>(part) + (int64_t)pv * NBW * NSW * 256 + lane;
+#pragma unroll
+      for (int b = 0; b < NBW; ++b)
+#pragma unroll
+        for (int g = 0; g < NSW; ++g)
+#pragma unroll
+          for (int k = 0; k < 4; ++k)
+            o[((b * NSW + g) * 4 + k) * 64] = make_float4(acc[b][g][4 * k], acc[b][g][4 * k + 1],
+                                                          acc[b][g][4 * k + 2], acc[b][g][4 * k + 3]);
+      return;
+    }
     // ---- normalize and store: tile row rr = 8 kk + 4 lg + u (kk, u: the
     // lane's elements 4 kk + u and 8 + 4 kk + u) is chunk row rr % 16 = rr
     // for both halves hh = 0, 1 of every block, so this wave's channels
@@ -1050,64 +1412,76 @@ __device__ __forceinline__ void chunk_block(const ChunkArgs& a, int r, int h, in
   }
 }
 
-// Row blocks of a chunk call: request r gets ceil(n_r G / 128) blocks of 128
-// rows (at least one, and one for a request whose query range is invalid, so
-// that its error is reported); rbo[r] = the blocks before request r,
-// rbo[n_req] = all of them.  Query ranges that do not overlap need at most
-// `grid` blocks (the launch's width); ranges that overlap and need more set
-// the range error bit and rbo[n_req] = 0: the call writes nothing.  One
-// workgroup.
-__global__ __launch_bounds__(256) void chunk_rows_kernel(int n_req, const int32_t* cu_q, int n_q_total,
-                                                         int group, int grid, int32_t* rbo,
-                                                         int32_t* err) {
-  __shared__ int part[256];
-  const int t = threadIdx.x;
-  const int per = (n_req + 255) / 256;
-  const int r0 = min(n_req, t * per), r1 = min(n_req, r0 + per);
-  auto blocks = [&](int r) {
-    const int q0 = cu_q[r], q1 = cu_q[r + 1];
-    const bool ok = q0 >= 0 && q1 >= q0 && q1 <= n_q_total;
-    return ok ? max(1, (int)(((int64_t)(q1 - q0) * group + NSW * 32 - 1) / (NSW * 32))) : 1;
-  };
-  int sum = 0;
-  for (int r = r0; r < r1; ++r) sum += blocks(r);
-  part[t] = sum;
-  __syncthreads();
-  for (int o = 1; o < 256; o <<= 1) {  // inclusive scan of the thread sums
-    const int v = t >= o ? part[t - o] : 0;
-    __syncthreads();
-    part[t] += v;
-    __syncthreads();
-  }
-  int base = part[t] - sum;
-  for (int r = r0; r < r1; ++r) {
-    rbo[r] = base;
-    base += blocks(r);
-  }
-  if (t == 255) {
-    const bool fits = part[255] <= grid;
-    rbo[n_req] = fits ? part[255] : 0;
-    if (!fits) atomicOr(err, (int)MKV_DEVERR_RANGE);
-  }
-}
-
-// Grid (row block over all requests, KV head): workgroup x takes global row
-// block x and finds its request in the row-block table (workgroups past the
-// last block return at once).
+// Grid (work item, KV head).
 template <int D>
 __global__ __launch_bounds__(64 * CW, 1) void chunk_kernel(ChunkArgs a) {
   extern __shared__ __align__(16) uint8_t smem[];
   const int gb = blockIdx.x;
-  if (gb >= a.rbo[a.n_req]) return;
-  int lo = 0, hi = a.n_req - 1;  // the last request whose first block is <= gb
-  while (lo < hi) {
-    const int mid = (lo + hi + 1) >> 1;
-    if (a.rbo[mid] <= gb)
-      lo = mid;
-    else
-      hi = mid - 1;
+  const int4 it0 = a.items[2 * gb], it1 = a.items[2 * gb + 1];  // (in the table whether planned or not)
+  if (gb >= a.hdr[0]) return;
+  chunk_block<D>(a, it0, it1, blockIdx.y, smem);
+}
+
+// Merge of the parts of cut blocks (Eq. softmax-merge): grid (cut block, KV
+// head, score wave), one thread per lane of a PV wave, with its accumulators' layout.
+template <int D>
+__global__ __launch_bounds__(64 * NSW) void chunk_merge_kernel(ChunkArgs a, const int4* splits) {
+  constexpr int CL = D / 16, NBW = D / 32 / NSW;
+  if ((int)blockIdx.x >= a.hdr[1]) return;
+  const int4 sp = splits[blockIdx.x];
+  const int r = sp.x, xb = sp.y, n = sp.w, h = blockIdx.y, g = blockIdx.z;
+  const int lane = threadIdx.x & 63, pv = threadIdx.x >> 6, li = lane & 31, lg = lane >> 5;
+  const int G = a.P.group, H = a.P.n_kv_heads, Hq = H * G;
+  const int q0 = a.cu_q[r], rows_r = (a.cu_q[r + 1] - q0) * G;
+  const int rho = xb * (NSW * 32) + g * 32 + li;
+  if (xb * (NSW * 32) + g * 32 >= rows_r) return;
+  const float* base = a.parts + ((int64_t)sp.z * H + h) * chunk_part_floats(D);
+  const int64_t step = (int64_t)H * chunk_part_floats(D);
+  float M = -INFINITY;
+  for (int k = 0; k < n; ++k) {
+    const float2 ml = reinterpret_cast<const float2*>(base + k * step + 128 * D)[g * 32 + li];
+    if (ml.y > 0.0f) M = fmaxf(M, ml.x);
   }
-  chunk_block<D>(a, lo, blockIdx.y, gb - a.rbo[lo], smem);
+  float L = 0.0f;
+  float4 o[NBW][4];
+#pragma unroll
+  for (int b = 0; b < NBW; ++b)
+#pragma unroll
+    for (int k = 0; k < 4; ++k) o[b][k] = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll 2
+  for (int k = 0; k < n; ++k) {
+    const float2 ml = reinterpret_cast<const float2*>(base + k * step + 128 * D)[g * 32 + li];
+    const float f = ml.y > 0.0f ? __builtin_amdgcn_exp2f(ml.x - M) : 0.0f;
+    L = fmaf(f, ml.y, L);
+    const float4* src = reinterpret_cast<const float4*>(base + k * step) + (int64_t)pv * NBW * NSW * 256 + lane;
+#pragma unroll
+    for (int b = 0; b < NBW; ++b)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const float4 x = src[((b * NSW + g) * 4 + e) * 64];
+        o[b][e].x = fmaf(f, x.x, o[b][e].x);
+        o[b][e].y = fmaf(f, x.y, o[b][e].y);
+        o[b][e].z = fmaf(f, x.z, o[b][e].z);
+        o[b][e].w = fmaf(f, x.w, o[b][e].w);
+      }
+  }
+  if (rho >= rows_r) return;
+  const float inv = L > 0.0f ? 1.0f / L : 0.0f;
+  float* dst = a.out + ((int64_t)(q0 + rho / G) * Hq + h * G + rho % G) * D + 2 * NBW * pv;
+  // element 4 k' + u of block b is tile row 8 k' + 4 lg + u: chunk row rr = 8 kk +
+  // 4 lg + u of half hh, k' = kk + 2 hh, channel CL rr + 2 b + hh of this wave's
+  auto el = [](const float4& v, int u) { return u == 0 ? v.x : u == 1 ? v.y : u == 2 ? v.z : v.w; };
+#pragma unroll
+  for (int kk = 0; kk < 2; ++kk)
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int rr = 8 * kk + 4 * lg + u;
+      if constexpr (NBW == 2)
+        *reinterpret_cast<float4*>(dst + CL * rr) = make_float4(el(o[0][kk], u) * inv, el(o[0][kk + 2], u) * inv,
+                                                                el(o[1][kk], u) * inv, el(o[1][kk + 2], u) * inv);
+      else
+        *reinterpret_cast<float2*>(dst + CL * rr) = make_float2(el(o[0][kk], u) * inv, el(o[0][kk + 2], u) * inv);
+    }
 }
 
 hipError_t launch_chunk(const PoolView& P, int layer, int n_req, const uint16_t* q,
@@ -1125,42 +1499,59 @@ hipError_t launch_chunk(const PoolView& P, int layer, int n_req, const uint16_t*
   a.seq_lens = seq_lens;
   a.out = out;
   uint8_t* w = reinterpret_cast<uint8_t*>(ws);
-  const ChunkWs wl = chunk_ws(n_req, max_pages);
-  int32_t* list8 = reinterpret_cast<int32_t*>(w + wl.list8);
-  int32_t* list3 = reinterpret_cast<int32_t*>(w + wl.list3);
-  int32_t* counts = reinterpret_cast<int32_t*>(w + wl.counts);
-  int4* stages = reinterpret_cast<int4*>(w + wl.stages);
+  const ChunkWs wl = chunk_ws(n_req, max_pages, n_q_total, P.n_kv_heads, P.group, P.d);
+  int2* list8 = reinterpret_cast<int2*>(w + wl.list8);
+  int2* list3 = reinterpret_cast<int2*>(w + wl.list3);
+  int2* cum = reinterpret_cast<int2*>(w + wl.cum);
   int32_t* rbo = reinterpret_cast<int32_t*>(w + wl.rbo);
+  int32_t* hdr = reinterpret_cast<int32_t*>(w + wl.hdr);
+  int4* items = reinterpret_cast<int4*>(w + wl.items);
+  int4* splits = reinterpret_cast<int4*>(w + wl.splits);
+  a.stride = wl.stride;
   a.list8 = list8;
   a.list3 = list3;
-  a.counts = counts;
-  a.stages = stages;
-  a.rbo = rbo;
+  a.hdr = hdr;
+  a.items = items;
+  a.parts = reinterpret_cast<float*>(w + wl.parts);
   a.sm_log2 = 1.4426950408889634f / sqrtf((float)P.d);
-  hipError_t e = launch_partition(n_req, bt, tags, max_pages, seq_lens, list8, list3, counts,
-                                  P.ctrl + CTRL_ERR, s);
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(chunk_stages_kernel, dim3((max_pages + 255) / 256, n_req), dim3(256), 0, s,
-                     max_pages, P.n_tq3, P.n_fp8, list8, list3, counts, stages, P.ctrl + CTRL_ERR);
-  e = hipGetLastError();
+  hipLaunchKernelGGL(chunk_lists_kernel, dim3(n_req), dim3(LIST_NT), 0, s, bt, tags, max_pages, wl.stride,
+                     seq_lens, P.n_fp8, P.n_tq3, list8, list3, cum, P.ctrl + CTRL_ERR);
+  hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   // row blocks of all requests: at most ceil(n_q_total G / 128) + n_req when
   // the query ranges do not overlap
-  const int64_t rows = (int64_t)n_q_total * P.group;
-  const int wg_rows = NSW * 32;
-  const int blocks = (int)((rows + wg_rows - 1) / wg_rows) + n_req;
-  hipLaunchKernelGGL(chunk_rows_kernel, dim3(1), dim3(256), 0, s, n_req, cu_q, n_q_total, P.group, blocks,
-                     rbo, P.ctrl + CTRL_ERR);
+  const int blocks = (int)chunk_blocks(n_q_total, P.group) + n_req;
+  const bool cut = chunk_may_cut(n_q_total, P.group, P.n_kv_heads);
+  const int share = cu_share(P.n_kv_heads);
+  const int max_slots = (int)((wl.total - wl.parts) / (P.n_kv_heads * chunk_part_floats(P.d) * sizeof(float)));
+  hipLaunchKernelGGL(chunk_plan_kernel, dim3(1), dim3(1024), 0, s, n_req, cu_q, n_q_total, seq_lens, max_pages,
+                     P.group, blocks, share, cut ? 1 : 0, max_slots, wl.stride, cum, rbo, hdr, items, splits,
+                     P.ctrl + CTRL_ERR);
   e = hipGetLastError();
   if (e != hipSuccess) return e;
   const size_t lds = P.d == 256 ? (size_t)ChunkLds<256>::TOTAL : (size_t)ChunkLds<128>::TOTAL;
   const void* kern = P.d == 256 ? (const void*)chunk_kernel<256> : (const void*)chunk_kernel<128>;
-  e = hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+  // the dynamic-LDS limit is raised once per kernel instance and device
+  static std::atomic<uint32_t> attr_done[64];
+  int dev = 0;
+  e = hipGetDevice(&dev);
   if (e != hipSuccess) return e;
-  dim3 grid(blocks, P.n_kv_heads);
+  const uint32_t bit = P.d == 256 ? 2u : 1u;
+  if (dev < 0 || dev >= 64 || !(attr_done[dev].load() & bit)) {
+    e = hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    if (e != hipSuccess) return e;
+    if (dev >= 0 && dev < 64) attr_done[dev].fetch_or(bit);
+  }
+  const int n_items = cut && blocks < 2 * share ? 2 * share : blocks;
+  dim3 grid(n_items, P.n_kv_heads);
   void* args[] = {&a};
   e = hipLaunchKernel(kern, grid, dim3(64 * CW), args, lds, s);
-  if (e != hipSuccess) return e;
+  if (e != hipSuccess || !cut) return e;
+  const dim3 mgrid(blocks < share ? blocks : share, P.n_kv_heads, NSW);
+  if (P.d == 256)
+    hipLaunchKernelGGL(chunk_merge_kernel<256>, mgrid, dim3(64 * NSW), 0, s, a, splits);
+  else
+    hipLaunchKernelGGL(chunk_merge_kernel<128>, mgrid, dim3(64 * NSW), 0, s, a, splits);
   return hipGetLastError();
 }
 

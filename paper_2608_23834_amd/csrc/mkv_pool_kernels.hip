@@ -210,8 +210,8 @@ __device__ __forceinline__ uint32_t pack_e4m3(float a, float b, float c, float d
 // channel, the four tokens of a group; four consecutive dwords per group, see
 // fp8_off): all stores are whole dwords.  A page that already holds tokens
 // (t0 > 0) has its old dwords loaded beside the new rows.  The bound is memory:
-// 32 K tokens x 4 heads x 4 layers read 134 MB and write 67 MB per tensor pair
-// and layer; storing V byte by byte the launch took 367 us.
+// 32 K tokens x 4 heads x 4 layers at d = 256 read and write 0.8 GB; storing V
+// byte by byte the launch took 367 us, now 160 us (5.0 TB/s).
 template <int D, bool kv>
 __device__ __forceinline__ void quant_task(uint8_t* reg, float* sc, const uint16_t* src, int64_t row0,
                                            int t0, int t1, int H, int h, int lane) {
