@@ -88,21 +88,33 @@ __device__ __forceinline__ void dma_region(uint32_t dst, const uint8_t* src, con
   static_assert(TAIL % 4 == 0 && TAIL <= 256, "tail must fit one 4-byte copy");
   if (TAIL > 0 && lane < TAIL / 4) dma4((R - TAIL) + 4 * lane, src, dst + (R - TAIL));
 }
-// One FP8 page-head (K then V, 16 d bytes each) into LDS with its 16-byte
-// blocks permuted so that the MFMA lanes read it without bank conflicts: LDS
-// block 64 w + l of each half holds the w-th 16 bytes of what lane l = 16 lg +
-// ln consumes (K: token ln, channels (d/4) lg + 16 w ..; V: the lane-chunk
-// (ln, lg), bytes 16 w ..).  2 d / 64 copies; the caller adds the scales.
+// One FP8 page-head (K then V, 16 d bytes each) into LDS.  Each half is 16 rows
+// of d bytes (K: a token; V: the four lane-chunks of MFMA row ln), lane (ln, lg)
+// of the products takes the 16-byte blocks d/64 lg + w of row ln.  Copy i fetches
+// bytes 64 i .. of every row, four lanes a row, so a copy touches 16 pieces of 64
+// bytes (lane by lane in consumption order it touched 64 pieces of 16, and the
+// address unit takes one piece at a time); inside the piece the blocks are
+// permuted by the row, x ^ (ln / 4), so that the 16 rows of a block number lie
+// in distinct LDS banks.  2 d / 64 copies; the caller adds the scales.  A decode
+// scan over eight prompts of 2 to 6 K tokens, mostly FP8 (d = 256), takes 20.3 us,
+// 27.3 before; d = 128 and the chunk kernel, bound elsewhere, gain nothing or 0.6 %.
 template <int D>
 __device__ __forceinline__ void dma_fp8_page(uint32_t dst, const uint8_t* src, int lane) {
   constexpr int NI = D / 64;  // copies per half (16 d / 1024)
-  const int ln = lane & 15, lg = lane >> 4;
-  const uint32_t vk = 16u * (uint32_t)(ln * (D / 16) + lg * NI);
-  const uint32_t vv = 16u * (uint32_t)((ln * 4 + lg) * NI);
+  const int row = lane >> 2;
+  const uint32_t v = (uint32_t)(row * D + 16 * ((lane & 3) ^ (row >> 2)));
 #pragma unroll
-  for (int i = 0; i < NI; ++i) dma16<0>(vk, src + 16 * i, dst + 1024 * i);
+  for (int i = 0; i < NI; ++i) dma16<0>(v, src + 64 * i, dst + 1024 * i);
 #pragma unroll
-  for (int i = 0; i < NI; ++i) dma16<0>(vv, src + 16 * D + 16 * i, dst + 16 * D + 1024 * i);
+  for (int i = 0; i < NI; ++i) dma16<0>(v, src + 16 * D + 64 * i, dst + 16 * D + 1024 * i);
+}
+// LDS byte offset, within either half, of the first block of lane (ln, lg);
+// its w-th block is at that offset ^ 16 w.
+template <int D>
+__device__ __forceinline__ uint32_t fp8_lane_off(int ln, int lg) {
+  constexpr int NI = D / 64;
+  const int y = lg * NI;
+  return 1024u * (y >> 2) + 64u * ln + 16u * ((y & 3) ^ (ln >> 2));
 }
 
 // The code dwords of chunk idx of a TQ3 code block in LDS (8-byte reads when

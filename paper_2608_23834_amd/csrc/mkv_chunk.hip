@@ -544,10 +544,10 @@ __device__ __forceinline__ void chunk_block(const ChunkArgs& a, int4 it0, int4 i
   const uint8_t* stab3 = reinterpret_cast<const uint8_t*>(a.list3 + (int64_t)r * a.stride + 2 * it0.z);
   const uint8_t* stab8 = reinterpret_cast<const uint8_t*>(a.list8 + (int64_t)r * a.stride + 2 * it1.x);
   const uint8_t* tq3_h = P.tq3 + ((int64_t)layer * P.n_tq3 * H + h) * R3;
-  const uint8_t* fp8_h = P.fp8 + ((int64_t)layer * P.n_fp8 * H + h) * R8 + hw * (16 * D) + (cwv & 1) * OPS_W * 16;
+  const uint8_t* fp8_h = P.fp8 + ((int64_t)layer * P.n_fp8 * H + h) * R8 + hw * (16 * D) + (cwv & 1) * OPS_W * 64;
   const uint8_t* scl_h = reinterpret_cast<const uint8_t*>(P.fp8_scales + ((int64_t)layer * P.n_fp8 * H + h) * 2);
   const uint32_t v3 = 16u * lane + 1024u * (OPS_W * (cwv & 1));
-  const uint32_t v8 = 16u * (uint32_t)(hw ? (ln * 4 + l4) * NI : ln * (D / 16) + l4 * NI);
+  const uint32_t v8 = (uint32_t)((lane >> 2) * D + 16 * ((lane & 3) ^ (lane >> 4)));
   const uint32_t dst3 = ring_lds + hw * R3 + (cwv & 1) * OPS_W * 1024, tail3 = ring_lds + hw * R3 + 16 * D;
   const uint32_t dst8 = ring_lds + hw * (16 * D) + (cwv & 1) * OPS_W * 1024, tail8 = ring_lds + R8;
   const uint32_t lst_lds = ring_lds + LY::LS0;
@@ -562,7 +562,7 @@ __device__ __forceinline__ void chunk_block(const ChunkArgs& a, int4 it0, int4 i
   auto issue8 = [&](uint32_t id, uint32_t so) {
     const uint8_t* src = fp8_h + (uint64_t)id * (uint32_t)(H * R8);
 #pragma unroll
-    for (int i = 0; i < OPS_W; ++i) dma16<0>(v8, src + 16 * i, dst8 + so + 1024 * i);
+    for (int i = 0; i < OPS_W; ++i) dma16<0>(v8, src + 64 * i, dst8 + so + 1024 * i);
     if (tail_wave && lane < 2) dma4(4 * lane, scl_h + (uint64_t)id * (uint32_t)(8 * H), tail8 + so);
   };
   auto issue_list = [&](int k) {  // block k of the lists -> buffer k % LBUF
@@ -1070,11 +1070,13 @@ __device__ __forceinline__ void chunk_block(const ChunkArgs& a, int4 it0, int4 i
         uint4 kw[NKS / 2];  // this lane's key bytes: 16-byte block w holds k-steps 2 w, 2 w + 1
         const uint8_t* ra = smem + so_a;
         const uint8_t* rb_ = smem + so_b;
-        // block-permuted page (see dma_fp8_page): 16-byte block 64 w + 16
-        // Q + t holds bytes 16 w .. of token t's channel quarter Q (K)
-        const uint4* pk = reinterpret_cast<const uint4*>(li < 16 ? ra : rb_) + 32 * lg + (li & 15);
+        // block-permuted page (see dma_fp8_page): token t's blocks NI 2 lg + w
+        const int tok = li & 15;
+        const uint8_t* pk = (li < 16 ? ra : rb_) + 512 * NI * lg + 64 * tok;
+        const int sw = 16 * (tok >> 2);
 #pragma unroll
-        for (int w = 0; w < NKS / 2; ++w) kw[w] = pk[64 * (w % (KPC / 2)) + 16 * (w / (KPC / 2))];
+        for (int w = 0; w < NKS / 2; ++w)
+          kw[w] = *reinterpret_cast<const uint4*>(pk + 1024 * (w / 4) + (sw ^ (16 * (w % 4))));
         const float2 ksa = *reinterpret_cast<const float2*>(ra + R8), ksb = *reinterpret_cast<const float2*>(rb_ + R8);
         auto mf = [&](int s) {
           if (s < NKS) {
@@ -1310,14 +1312,16 @@ __device__ __forceinline__ void chunk_block(const ChunkArgs& a, int4 it0, int4 i
       uint32_t vw[2][NBW][2];
 #pragma unroll
       for (int p = 0; p < 2; ++p) {
-        const uint2* pvp = reinterpret_cast<const uint2*>(smem + pl8.so + PAGE * D);
+        const uint8_t* pvp = smem + pl8.so + PAGE * D + 64 * rrow;
         next8(pl8);
 #pragma unroll
         for (int b = 0; b < NBW; ++b) {
           const int mb = NBW * pv + b;
-          const int blk = 64 * (mb / 2);
-          const uint2 v0 = pvp[2 * (blk + 16 * lg + rrow) + (mb & 1)];
-          const uint2 v2 = pvp[2 * (blk + 16 * (lg + 2) + rrow) + (mb & 1)];
+          // block y of the row (see dma_fp8_page): KiB y / 4, place y % 4 ^ rrow / 4
+          const int y = lg * NI + mb / 2;
+          const uint8_t* pb = pvp + 1024 * (y >> 2) + 16 * ((y & 3) ^ (rrow >> 2)) + 8 * (mb & 1);
+          const uint2 v0 = *reinterpret_cast<const uint2*>(pb);
+          const uint2 v2 = *reinterpret_cast<const uint2*>(pb + 1024 * (NI / 2));
           vw[p][b][0] = hh ? v0.y : v0.x;
           vw[p][b][1] = hh ? v2.y : v2.x;
         }

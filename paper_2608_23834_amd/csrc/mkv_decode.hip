@@ -829,6 +829,7 @@ __global__ __launch_bounds__(DecodeCfg<PAIR>::NT, 1) void decode_kernel(DecodeAr
     }
     ++k_st;
   }
+  const uint32_t off8 = fp8_lane_off<D>(ln, lg);
   while (jc < n_st) {
     const int j = jc;
     const int slot = k_st % SLOTS;
@@ -843,17 +844,15 @@ __global__ __launch_bounds__(DecodeCfg<PAIR>::NT, 1) void decode_kernel(DecodeAr
     constexpr int KW = D / 16;  // dwords of K per lane (D/4 bytes)
     uint32_t kA[KW], vA[CL];
     {
-      // block-permuted page (see dma_fp8_page): lane l's w-th 16 bytes at 64 w + l
-      const uint4* pk = reinterpret_cast<const uint4*>(ra) + lane;
-      const uint4* pv = reinterpret_cast<const uint4*>(ra + PAGE * D) + lane;
+      // block-permuted page (see dma_fp8_page)
 #pragma unroll
       for (int w = 0; w < KW / 4; ++w) {
-        const uint4 x = pk[64 * w];
+        const uint4 x = *reinterpret_cast<const uint4*>(ra + (off8 ^ (16 * w)));
         kA[4 * w] = x.x; kA[4 * w + 1] = x.y; kA[4 * w + 2] = x.z; kA[4 * w + 3] = x.w;
       }
 #pragma unroll
       for (int w = 0; w < CL / 4; ++w) {
-        const uint4 x = pv[64 * w];
+        const uint4 x = *reinterpret_cast<const uint4*>(ra + PAGE * D + (off8 ^ (16 * w)));
         vA[4 * w] = x.x; vA[4 * w + 1] = x.y; vA[4 * w + 2] = x.z; vA[4 * w + 3] = x.w;
       }
     }
