@@ -1014,29 +1014,34 @@ __global__ __launch_bounds__(DecodeCfg<PAIR>::NT, 1) void decode_kernel(DecodeAr
   }
 }
 
-// Merge stage (Eq. softmax-merge): one single-wave workgroup per (query head
-// of the group, KV head, request), one thread per four channels.  The O_j
-// rows of up to 32 chunk slots and, in lane j, slot j's (m_j, l_j) are loaded
-// together (one memory round trip for the usual grid); the batch maximum and
-// the weights 2^(m_j - M) l_j come from wave reductions, and every weight is
-// read into a scalar register, so each thread's fold is 32 FMAs per channel.
-// Slots with l_j = 0 contribute nothing; a running (M, L, O) is rescaled once
-// per batch.
+// Merge stage (Eq. softmax-merge): one workgroup of W waves per (query head of
+// the group, KV head, request), D / 64 channels per lane.  Each wave folds up
+// to B chunk slots per round, a contiguous share: their O_j rows and, in lane
+// j, slot j's (m_j, l_j) are loaded together, the round's maximum and the
+// weights 2^(m_j - M) l_j come from wave reductions, and every weight is read
+// into a scalar register.  The waves' (M, L, O) meet in LDS.  The bound is one
+// memory round trip and the launch itself, so W and B follow the slot count (see
+// launch_decode): up to W B slots take a single round.
+// Slots with l_j = 0 contribute nothing.
 // With the fused append (app_rec non-null) the workgroups of query head 0 and
 // KV head 0 also publish their request's fresh page and, for request 0, the
 // FP8 free-list top, from the records the scan left.
-template <int D>
-__global__ __launch_bounds__(D / 4) void decode_merge_kernel(int G, int H, int max_chunks,
-                                                            const float* partials, float* out,
-                                                            float* lse, const int32_t* app_rec,
-                                                            int32_t* bt_w, uint8_t* tags_w,
-                                                            int max_pages, const int32_t* seq_lens,
-                                                            int32_t* ctrl, int32_t* rc8) {
-  constexpr int B = 32;
-  static_assert(D / 4 >= B && D / 4 <= 64, "one wave; lane j holds slot j's (m, l)");
-  const int n = blockIdx.x, h = blockIdx.y, r = blockIdx.z, c4 = threadIdx.x;
+template <int D, int W, int B>
+__global__ __launch_bounds__(64 * W) void decode_merge_kernel(int G, int H, int max_chunks,
+                                                             const float* partials, float* out,
+                                                             float* lse, const int32_t* app_rec,
+                                                             int32_t* bt_w, uint8_t* tags_w,
+                                                             int max_pages, const int32_t* seq_lens,
+                                                             int32_t* ctrl, int32_t* rc8) {
+  constexpr int NC = D / 64;
+  typedef float vec __attribute__((ext_vector_type(NC)));
+  static_assert(B <= 64, "lane j holds slot j's (m, l)");
+  __shared__ __align__(16) float s_o[W][D];
+  __shared__ float s_m[W], s_l[W];
+  const int n = blockIdx.x, h = blockIdx.y, r = blockIdx.z;
+  const int lane = threadIdx.x & 63, wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int Hq = H * G;
-  if (app_rec && n == 0 && h == 0 && c4 == 0) {
+  if (app_rec && n == 0 && h == 0 && threadIdx.x == 0) {
     const int id = app_rec[r];
     if (id >= 0) {
       const int64_t ix = (int64_t)r * max_pages + seq_lens[r] / PAGE;
@@ -1048,58 +1053,94 @@ __global__ __launch_bounds__(D / 4) void decode_merge_kernel(int G, int H, int m
   }
   const int stride = part_stride(G, D);
   const float* base = partials + ((int64_t)r * H + h) * max_chunks * stride;
+  const int per = min(B, (max_chunks + W - 1) / W);  // slots per wave and round
   float M = -INFINITY, L = 0.0f;
-  float4 O = make_float4(0.f, 0.f, 0.f, 0.f);
+  vec O = 0.0f;
   bool poisoned = false;  // a slot with l < 0: a failed fused append, write zeros
-  for (int k0 = 0; k0 < max_chunks; k0 += B) {
-    float4 ok[B];
+  for (int k0 = wid * per; k0 < max_chunks; k0 += W * per) {
+    const int nk = min(per, max_chunks - k0);
+    vec ok[B];
 #pragma unroll
-    for (int j = 0; j < B; ++j) {
-      const int k = min(k0 + j, max_chunks - 1);
-      ok[j] = reinterpret_cast<const float4*>(base + (int64_t)k * stride + n * D)[c4];
-    }
-    const bool mine = c4 < B && k0 + c4 < max_chunks;
-    const float* pk = base + (int64_t)min(k0 + c4, max_chunks - 1) * stride;
+    for (int j = 0; j < B; ++j)
+      ok[j] = reinterpret_cast<const vec*>(base + (int64_t)(k0 + min(j, nk - 1)) * stride + n * D)[lane];
+    const float* pk = base + (int64_t)(k0 + min(lane, nk - 1)) * stride;
     const float mj = pk[G * D + n];
-    const float lj = mine ? pk[G * D + G + n] : 0.0f;
+    const float lr = pk[G * D + G + n];
+    const float lj = lane < nk ? lr : 0.0f;
     poisoned |= __any(lj < 0.0f);
     float mb = lj > 0.0f ? mj : -INFINITY;
-#pragma unroll
-    for (int o = 1; o < D / 4; o <<= 1) mb = fmaxf(mb, __shfl_xor(mb, o, D / 4));
+    mb = fmaxf(mb, lane_xor<1>(mb, lane));
+    if constexpr (B > 2) mb = fmaxf(mb, lane_xor<2>(mb, lane));
+    if constexpr (B > 4) mb = fmaxf(mb, lane_xor<4>(mb, lane));
+    if constexpr (B > 8) mb = fmaxf(mb, lane_xor<8>(mb, lane));
+    mb = __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, mb)));
     const float Mb = fmaxf(M, mb);
-    if (Mb != -INFINITY) {  // else nothing in this batch, nothing before it (wave-uniform)
+    if (Mb != -INFINITY) {  // else nothing in this round, nothing before it (wave-uniform)
       const float f = M == -INFINITY ? 0.0f : exp2f(M - Mb);
       const float wj = lj > 0.0f ? exp2f(mj - Mb) * lj : 0.0f;
-      float ws = wj;
-#pragma unroll
-      for (int o = 1; o < D / 4; o <<= 1) ws += __shfl_xor(ws, o, D / 4);
-      L = L * f + ws;
-      O.x *= f;
-      O.y *= f;
-      O.z *= f;
-      O.w *= f;
+      L *= f;
+      O *= f;
 #pragma unroll
       for (int j = 0; j < B; ++j) {
         const float w = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, wj), j));
         // an empty slot's O rows were never written (they may hold any bits,
         // NaN included): skip the slot rather than multiply them by 0
         if (w != 0.0f) {
-          O.x = fmaf(w, ok[j].x, O.x);
-          O.y = fmaf(w, ok[j].y, O.y);
-          O.z = fmaf(w, ok[j].z, O.z);
-          O.w = fmaf(w, ok[j].w, O.w);
+          L += w;
+#pragma unroll
+          for (int i = 0; i < NC; ++i) O[i] = fmaf(w, ok[j][i], O[i]);
         }
       }
       M = Mb;
     }
   }
+  if constexpr (W > 1) {
+    *reinterpret_cast<vec*>(&s_o[wid][NC * lane]) = O;
+    if (lane == 0) {
+      s_m[wid] = M;
+      s_l[wid] = poisoned ? -1.0f : L;
+    }
+    __syncthreads();
+    if (wid != 0) return;
+    float mw[W], lw[W];
+    vec ow[W];
+#pragma unroll
+    for (int w = 0; w < W; ++w) {
+      mw[w] = s_m[w];
+      lw[w] = s_l[w];
+      ow[w] = *reinterpret_cast<const vec*>(&s_o[w][NC * lane]);
+    }
+    M = -INFINITY;
+#pragma unroll
+    for (int w = 0; w < W; ++w) {
+      poisoned |= lw[w] < 0.0f;
+      M = fmaxf(M, lw[w] > 0.0f ? mw[w] : -INFINITY);
+    }
+    L = 0.0f;
+    O = 0.0f;
+#pragma unroll
+    for (int w = 0; w < W; ++w) {
+      const float f = lw[w] > 0.0f ? exp2f(mw[w] - M) : 0.0f;
+      L = fmaf(f, lw[w], L);
+#pragma unroll
+      for (int i = 0; i < NC; ++i) O[i] = fmaf(f, ow[w][i], O[i]);
+    }
+  }
   const int64_t row = (int64_t)r * Hq + h * G + n;
   if (poisoned) L = 0.0f;
   const float inv = L > 0.0f ? 1.0f / L : 0.0f;
-  const float4 res = L > 0.0f ? make_float4(O.x * inv, O.y * inv, O.z * inv, O.w * inv)
-                              : make_float4(0.f, 0.f, 0.f, 0.f);
-  reinterpret_cast<float4*>(out + row * D)[c4] = res;
-  if (lse && c4 == 0) lse[row] = L > 0.0f ? (M + log2f(L)) * 0.69314718055994531f : -INFINITY;
+  vec res = 0.0f;
+  if (L > 0.0f) {
+#pragma unroll
+    for (int i = 0; i < NC; ++i) res[i] = O[i] * inv;
+  }
+  reinterpret_cast<vec*>(out + row * D)[lane] = res;
+  if (lse && lane == 0) lse[row] = L > 0.0f ? (M + log2f(L)) * 0.69314718055994531f : -INFINITY;
+}
+
+template <int W, int B>
+static const void* merge_instance(int d) {
+  return d == 256 ? (const void*)decode_merge_kernel<256, W, B> : (const void*)decode_merge_kernel<128, W, B>;
 }
 
 // Device scratch for callers that cannot allocate (paged_attn_decode_noalloc):
@@ -1233,8 +1274,16 @@ hipError_t launch_decode(const PoolView& P, int layer, int n_req, const uint16_t
   int32_t* ctrl = P.ctrl;
   int32_t* rc8 = P.rc8;
   void* margs[] = {&G, &H, &mc, &pa, &out, &lse, &rec, &bt_w, &tags_w, &mpg, &seq_lens, &ctrl, &rc8};
-  const void* mk = P.d == 256 ? (const void*)decode_merge_kernel<256> : (const void*)decode_merge_kernel<128>;
-  const dim3 mblock(P.d / 4);
+  // merge shape: one round trip for the slots of one call, and no more waves
+  // than that takes.  One wave with rounds of 32 slots took 6.0 us on 63 slots
+  // (24 rows), 4.6 on 32 (48 rows); so 4.6 and 4.0.  Few slots stay at one or two
+  // waves (4.8 us either way on 2 and 8 slots: the launch and one round trip)
+  const int mw = mc <= 4 ? 1 : mc <= 16 ? 2 : mc <= 32 ? 4 : 8;
+  const void* mk = mw == 1 ? merge_instance<1, 4>(P.d)
+                   : mw == 2 ? merge_instance<2, 8>(P.d)
+                   : mw == 4 ? merge_instance<4, 8>(P.d)
+                             : merge_instance<8, 16>(P.d);
+  const dim3 mblock(64 * mw);
   return ev ? hipExtLaunchKernel(mk, mgrid, mblock, margs, 0, s, ev[2], ev[3], 0)
             : hipLaunchKernel(mk, mgrid, mblock, margs, 0, s);
 }
