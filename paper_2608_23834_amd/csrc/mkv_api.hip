@@ -410,7 +410,7 @@ mkv_status paged_attn_decode_cohort_key(const mkv_pool* pool, int32_t n_req, int
   if (!pool || !key || n_req < 1 || max_pages < 1) return MKV_EINVAL;
   if (n_req > 65535 || max_pages > 1024 * 256) return MKV_ERANGE;
   if (pool->n_tq3 < 1 || pool->timing) return MKV_ESTATE;
-  const DecodeShape sh = decode_shape(n_req, max_pages, pool->n_kv_heads, pool->recent);
+  const DecodeShape sh = decode_shape(n_req, max_pages, pool->n_kv_heads, pool->recent, pool->group, pool->d);
   const uint64_t fields[] = {(uint64_t)(uintptr_t)pool, (uint64_t)(uintptr_t)pool->ctrl,
                              (uint64_t)pool->n_layers, (uint64_t)pool->n_q_heads,
                              (uint64_t)pool->n_kv_heads, (uint64_t)pool->d, (uint64_t)PAGE,

@@ -5,10 +5,11 @@
 // 8 wave64s with one ring slot each when a KV head's query group has at most
 // 8 heads (two pages share a score tile), else 8 waves with two slots.  Chunks
 // are ranges of logical pages of equal cost: a page wholly outside the Recent
-// window costs 2 units, a Recent (FP8) page 5 (its scattered 16-byte copies
-// make it cost the scan about 2.5 times a TQ3 page, measured); the unit count
-// per chunk is chosen so that the launch is about one workgroup per CU.  Each
-// workgroup
+// window costs 2 units, a Recent (FP8) page 3 (twice the bytes, and it goes
+// alone through a stage that takes a pair of TQ3 pages; measured on short ragged
+// requests at d = 128 and d = 256: 27.2 and 18.9 us per scan with 3 units, 28.5
+// and 19.5 with 4, 30.6 and 20.3 with 5); the unit count per chunk is chosen so
+// that the launch fills the chip (decode_fill).  Each workgroup
 //  1. loads its chunk's tags and page ids and the request's length together,
 //     and meanwhile builds the query operands in LDS: the plain query as fp16
 //     (FP8 pages) and the rotated query q_rot = R q (exact algebra: k_hat =
@@ -73,7 +74,7 @@ constexpr int NW_MAX = MKV_PAIR_NW > 8 ? MKV_PAIR_NW : 8;
 #define NCH_OF(pair) ((pair) ? 8 : 16)
 constexpr int MAX_CHUNK_PAGES = 256;   // pages a chunk may span
 // cost of a page in chunk units: wholly outside the Recent window / Recent
-constexpr int COST_OLD = 2, COST_REC = 5;
+constexpr int COST_OLD = 2, COST_REC = 3;
 constexpr int COST_MIN = COST_OLD < COST_REC ? COST_OLD : COST_REC;
 constexpr int MASK_LP = 0x3FFFFFFF / PAGE;  // logical page whose tokens are all masked
 
@@ -122,21 +123,27 @@ __device__ inline int page_at_cost(int64_t c, int n_old) {
   return n_old + (int)((c - co + COST_REC - 1) / COST_REC);
 }
 
-// Units per chunk: about one workgroup per CU for the whole launch when the
-// requests fill their tables (256 CUs), never below 16 old pages' worth and
-// never spanning more than MAX_CHUNK_PAGES pages.
-DecodeShape decode_shape(int n_req, int max_pages, int n_kv_heads, int recent) {
+// Workgroups that fill the chip when the requests fill their tables: one per CU
+// (256 CUs), two with d = 128 and the paired score layout, whose registers (128)
+// and LDS (49 KB) leave room for two on a CU.  Twice the waves keep more copies in
+// flight, and chunks half as long level out uneven requests (24 requests of 131
+// to 3,977 tokens, 8 KV heads: the scan takes 29.3 us instead of 39.5; at d = 256,
+// where one workgroup fits, two rounds of half the chunk take 20.1 instead of 12.9
+// us at 16 K tokens).
+constexpr int decode_fill(int d, int group) { return d == 128 && group <= 8 ? 512 : 256; }
+// Units per chunk: about that many workgroups for the whole launch, never below
+// 16 old pages' worth and never spanning more than MAX_CHUNK_PAGES pages.
+static DecodeShape shape_for(int64_t fill, int n_req, int max_pages, int n_kv_heads, int recent) {
   DecodeShape s;
   const int64_t tmax = request_cost(max_pages, old_pages((int64_t)max_pages * PAGE, recent));
   const int64_t pairs = (int64_t)n_req * n_kv_heads;
-  int64_t u = (tmax * pairs + 255) / 256;
+  int64_t u = (tmax * pairs + fill - 1) / fill;
   if (u < 16 * COST_OLD) u = 16 * COST_OLD;
   if (u > (int64_t)(MAX_CHUNK_PAGES - 1) * COST_MIN) u = (int64_t)(MAX_CHUNK_PAGES - 1) * COST_MIN;
   s.cunits = (int)u;
   s.max_chunks = (int)((tmax + u - 1) / u);
   return s;
 }
-
 // workspace: the partials, one (O_j[G][d], m_j[G], l_j[G]) block per chunk
 // slot, padded to a multiple of 4 floats (16-byte aligned O rows); every slot
 // of the grid is written on every call (l_j = 0 when the chunk is empty or
@@ -147,9 +154,18 @@ __host__ __device__ constexpr int part_stride(int G, int D) { return (G * (D + 2
 static size_t decode_part_bytes(const DecodeShape& s, int n_req, int n_kv_heads, int group, int d) {
   return (size_t)n_req * n_kv_heads * s.max_chunks * part_stride(group, d) * sizeof(float);
 }
+static size_t decode_rec_bytes(int n_req) { return ((size_t)(n_req + 1) * 4 + 15) / 16 * 16; }
+
+DecodeShape decode_shape(int n_req, int max_pages, int n_kv_heads, int recent, int group, int d) {
+  const DecodeShape s = shape_for(decode_fill(d, group), n_req, max_pages, n_kv_heads, recent);
+  // a call that fits the library's own scratch with one workgroup per CU keeps fitting
+  if (decode_part_bytes(s, n_req, n_kv_heads, group, d) + decode_rec_bytes(n_req) <= (size_t)MKV_DECODE_SCRATCH_BYTES) return s;
+  return shape_for(256, n_req, max_pages, n_kv_heads, recent);
+}
+
 size_t decode_ws_bytes(int n_req, int max_pages, int n_kv_heads, int group, int d, int recent) {
-  DecodeShape s = decode_shape(n_req, max_pages, n_kv_heads, recent);
-  return decode_part_bytes(s, n_req, n_kv_heads, group, d) + ((size_t)(n_req + 1) * 4 + 15) / 16 * 16;
+  const DecodeShape s = decode_shape(n_req, max_pages, n_kv_heads, recent, group, d);
+  return decode_part_bytes(s, n_req, n_kv_heads, group, d) + decode_rec_bytes(n_req);
 }
 
 template <int D>
@@ -236,7 +252,7 @@ __device__ __forceinline__ void p_operand(const float* p, bool row_is_b, half8& 
 // columns [0, 8) scoring page a and [8, 16) page b.  G6: at most six heads
 // (see head_of_col).
 template <int D, bool PAIR, bool G6, bool APP, bool SCORE = false>
-__global__ __launch_bounds__(DecodeCfg<PAIR>::NT, 1) void decode_kernel(DecodeArgs a) {
+__global__ __launch_bounds__(DecodeCfg<PAIR>::NT, PAIR && D == 128 ? 4 : 2) void decode_kernel(DecodeArgs a) {
   static_assert(!(APP && SCORE), "the scoring instance has no fused append");
   constexpr int NW = DecodeCfg<PAIR>::NW, NT = DecodeCfg<PAIR>::NT, SLOTS = DecodeCfg<PAIR>::SLOTS;
   constexpr int NCH = NCH_OF(PAIR);  // query heads a score tile holds
@@ -1213,7 +1229,7 @@ hipError_t launch_decode(const PoolView& P, int layer, int n_req, const uint16_t
   const bool app = k_new != nullptr;
   const bool score = page_mass != nullptr;
   if (app && score) return hipErrorInvalidValue;
-  const DecodeShape sh = decode_shape(n_req, max_pages, P.n_kv_heads, P.recent);
+  const DecodeShape sh = decode_shape(n_req, max_pages, P.n_kv_heads, P.recent, P.group, P.d);
   DecodeArgs a;
   a.P = P;
   a.layer = layer;

@@ -93,7 +93,7 @@ hipError_t launch_pages_release(const PoolView& P, int n, const int32_t* ids, co
 struct DecodeShape {
   int cunits, max_chunks;
 };
-DecodeShape decode_shape(int n_req, int max_pages, int n_kv_heads, int recent);
+DecodeShape decode_shape(int n_req, int max_pages, int n_kv_heads, int recent, int group, int d);
 size_t decode_ws_bytes(int n_req, int max_pages, int n_kv_heads, int group, int d, int recent);
 // the fixed device scratch of paged_attn_decode_noalloc: resolve its address on
 // device dev (dev must be current; once per device), and look it up

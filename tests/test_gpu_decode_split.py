@@ -18,8 +18,8 @@ RECENT = 16
 
 def _pages(slots):
     """The widest table that one request and one KV head cut into `slots` chunks: 2
-    cost units per page outside the window, 5 for the window's one, 32 per chunk."""
-    return (32 * slots - 5) // 2 + 1
+    cost units per page outside the window, 3 for the window's one, 32 per chunk."""
+    return (32 * slots - 3) // 2 + 1
 
 
 @pytest.mark.parametrize("d", [128, 256])
