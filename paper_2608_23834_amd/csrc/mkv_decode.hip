@@ -363,7 +363,10 @@ __global__ __launch_bounds__(DecodeCfg<PAIR>::NT, PAIR && D == 128 ? 4 : 2) void
   //  qf8[t][S][lane] holds term t of channels (D/4) lg + 32 S + j, j < 32 (the
   //  f8f6f4 MFMA pairs byte j of lane l in A with byte j of lane l' in B
   //  whenever l / 16 = l' / 16, so any channel order common to both operands
-  //  works; this one matches the key quads)
+  //  works; this one matches the key quads).  With page pairs only columns
+  //  [0, 8) are stored; column ln + 8 scores page b with head ln and reads them
+  //  too (qlane).  The lanes of a store share a few LDS banks, so the number of
+  //  stores is what this part costs: element by element it took 1.6 us of a launch
   {
     _Float16* qp = reinterpret_cast<_Float16*>(qpl);
     // R = d^-1/2 H diag(sigma); the rotated query also carries the softmax
@@ -405,8 +408,12 @@ __global__ __launch_bounds__(DecodeCfg<PAIR>::NT, PAIR && D == 128 ? 4 : 2) void
       float amax = 0.0f;
 #pragma unroll
       for (int i = 0; i < QV; ++i) amax = fmaxf(amax, fabsf(xr[i] * qscale));
-#pragma unroll
-      for (int o = 1; o < 64; o <<= 1) amax = fmaxf(amax, __shfl_xor(amax, o, 64));
+      amax = fmaxf(amax, lane_xor<1>(amax, lane));
+      amax = fmaxf(amax, lane_xor<2>(amax, lane));
+      amax = fmaxf(amax, lane_xor<4>(amax, lane));
+      amax = fmaxf(amax, lane_xor<8>(amax, lane));
+      amax = fmaxf(amax, lane_xor<16>(amax, lane));
+      amax = fmaxf(amax, lane_xor<32>(amax, lane));
       int ex = 0;
       (void)frexpf(amax, &ex);  // amax in [2^(ex-1), 2^ex)
       const float qsc = (ok && amax > 0.0f) ? ldexpf(1.0f, 7 - ex + 1) : 1.0f;
@@ -414,25 +421,26 @@ __global__ __launch_bounds__(DecodeCfg<PAIR>::NT, PAIR && D == 128 ? 4 : 2) void
         s_qinv[n] = 1.0f / qsc;
         if (pair) s_qinv[n + 8] = 1.0f / qsc;
       }
+      // the lane's QV channels are neighbours in both operands: one store each
+      const int c = QV * lane, lgc = c / (D / 4), cc = c % (D / 4);
+      typedef _Float16 hvec __attribute__((ext_vector_type(QV)));
+      hvec vp;
 #pragma unroll
-      for (int i = 0; i < QV; ++i) {
-        const int c = QV * lane + i;
-        const int lgc = c / (D / 4), sc = (c % (D / 4)) / 8, j = c % 8;
-        const _Float16 vp = (_Float16)(ok ? qx[ps][i] : 0.0f);
-        const int e0 = ((sc * 64) + lgc * 16 + n) * 8 + j;
-        qp[e0] = vp;
-        if (pair) qp[e0 + 8 * 8] = vp;  // column n + 8 scores page b with the same head
-        // rotated query times its scale as three E4M3 terms (exact residuals)
-        float x = ok ? xr[i] * qscale * qsc : 0.0f;
-        const int S = (c % (D / 4)) / 32, slot = c % 32;
+      for (int i = 0; i < QV; ++i) vp[i] = (_Float16)(ok ? qx[ps][i] : 0.0f);
+      *reinterpret_cast<hvec*>(qp + ((cc / 8 * 64) + lgc * 16 + n) * 8 + c % 8) = vp;
+      // rotated query times its scale as three E4M3 terms (exact residuals)
+      float x[QV];
 #pragma unroll
-        for (int t = 0; t < QF8_TERMS; ++t) {
-          const uint32_t b = f32_to_e4m3(x);
-          x -= e4m3_to_f32(b);
-          const int e8 = ((t * NK8 + S) * 64 + lgc * 16 + n) * 32 + slot;
-          qf8[e8] = (uint8_t)b;
-          if (pair) qf8[e8 + 8 * 32] = (uint8_t)b;
-        }
+      for (int i = 0; i < QV; ++i) x[i] = ok ? xr[i] * qscale * qsc : 0.0f;
+      uint8_t* q8 = qf8 + ((cc / 32 * 64) + lgc * 16 + n) * 32 + c % 32;
+#pragma unroll
+      for (int t = 0; t < QF8_TERMS; ++t) {
+        uint32_t w = f32_to_e4m3(x[0]) | f32_to_e4m3(x[1]) << 8;
+        if constexpr (QV == 4) w |= f32_to_e4m3(x[2]) << 16 | f32_to_e4m3(x[3]) << 24;
+#pragma unroll
+        for (int i = 0; i < QV; ++i) x[i] -= e4m3_to_f32(w >> (8 * i) & 0xFFu);
+        if constexpr (QV == 4) *reinterpret_cast<uint32_t*>(q8 + t * NK8 * 64 * 32) = w;
+        else *reinterpret_cast<uint16_t*>(q8 + t * NK8 * 64 * 32) = (uint16_t)w;
       }
     }
   }
@@ -532,6 +540,7 @@ __global__ __launch_bounds__(DecodeCfg<PAIR>::NT, PAIR && D == 128 ? 4 : 2) void
   st.m_run = M_INIT;
   st.l_run = 0.0f;
   const int ln = lane & 15, lg = lane >> 4;
+  const int qlane = pair ? lane & ~8 : lane;  // this lane's place in the query operands
   const int col_head = head_of_col<G6>(pair ? (ln & 7) : ln);
   const bool col_valid = col_head >= 0 && col_head < G;
   const bool col_b = pair && ln >= 8;  // this column scores page b
@@ -788,7 +797,7 @@ __global__ __launch_bounds__(DecodeCfg<PAIR>::NT, PAIR && D == 128 ? 4 : 2) void
       }
 #pragma unroll
       for (int t = 0; t < QF8_TERMS; ++t) {
-        const v8i qv = *reinterpret_cast<const v8i*>(qf8 + ((t * NK8 + S) * 64 + lane) * 32);
+        const v8i qv = *reinterpret_cast<const v8i*>(qf8 + ((t * NK8 + S) * 64 + qlane) * 32);
         sa = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(Ka, qv, sa, 0, 0, 0, 0, 0, 0);
         if (pair) sb = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(Kb, qv, sb, 0, 0, 0, 0, 0, 0);
       }
@@ -880,7 +889,7 @@ __global__ __launch_bounds__(DecodeCfg<PAIR>::NT, PAIR && D == 128 ? 4 : 2) void
     for (int s = 0; s < NS; ++s)
       sa = __builtin_amdgcn_mfma_f32_16x16x32_f16(
           h8(cvt_lo(kA[2 * s]), cvt_hi(kA[2 * s]), cvt_lo(kA[2 * s + 1]), cvt_hi(kA[2 * s + 1])),
-          qpl[s * 64 + lane], sa, 0, 0, 0);
+          qpl[s * 64 + qlane], sa, 0, 0, 0);
     float sc[4];
     {
       const float kk = ksv.x * smk;
