@@ -614,6 +614,64 @@ __device__ __forceinline__ void mig_load(MigBatch& m, int64_t f0, int64_t N, int
     if (++p == max_pages) { p = 0; ++r; }
   }
 }
+// The table as one batch of N <= MIG_BATCH entries, entry j MIG_NT + tid in slot j
+// of thread tid: neighbouring threads load neighbouring entries (a single
+// workgroup is bound by its CU's address unit, and slots past the table cost
+// nothing).  Retier's list of one request's 128 and 1,030 pages takes 3.4 and 5.1 us,
+// 5.2 and 9.8 with MIG_KB consecutive entries per thread; Promote's of 8 x 376 pages
+// 8.4 us, 15.7.
+__device__ __forceinline__ void mig_load_striped(MigBatch& m, int N, int max_pages, const int32_t* bt,
+                                                 const uint8_t* tags, const uint8_t* anchor,
+                                                 const int32_t* seq_lens) {
+#pragma unroll
+  for (int j = 0; j < MIG_KB; ++j) {
+    m.rq[j] = -1;
+    m.pg[j] = m.sl[j] = m.id[j] = 0;
+    m.tg[j] = TAG_NONE;
+    m.an[j] = 0;
+    if (j * MIG_NT < N) {  // workgroup-uniform
+      const bool in = j * MIG_NT + (int)threadIdx.x < N;
+      const uint32_t f = in ? j * MIG_NT + threadIdx.x : 0;
+      const uint32_t r = f / (uint32_t)max_pages;
+      m.rq[j] = in ? (int)r : -1;
+      m.pg[j] = (int)(f - r * (uint32_t)max_pages);
+      m.tg[j] = tags[f];
+      m.an[j] = anchor ? anchor[f] : 0;
+      m.id[j] = bt[f];
+      m.sl[j] = seq_lens[r];
+    }
+  }
+}
+// Exclusive sums, in entry order, of the counts that the 16 waves of a workgroup
+// hold for their 64 entries of each slot: base[j] for this wave's slot j; returns
+// the total.  s_cnt: 16 KB + 1 words; two barriers, whatever KB is.
+template <int KB>
+__device__ __forceinline__ int striped_bases(const int (&cnt)[KB], int (&base)[KB], int* s_cnt) {
+  static_assert(16 * KB % 64 == 0, "a wave sums the counts");
+  constexpr int PER = 16 * KB / 64;
+  const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+#pragma unroll
+  for (int j = 0; j < KB; ++j)
+    if (lane == 0) s_cnt[16 * j + wid] = cnt[j];
+  __syncthreads();
+  if (wid == 0) {
+    int v[PER], x = 0;
+#pragma unroll
+    for (int i = 0; i < PER; ++i) x += v[i] = s_cnt[PER * lane + i];
+    const int incl = wave_incl_scan(x, lane);
+    int e = incl - x;
+#pragma unroll
+    for (int i = 0; i < PER; ++i) {
+      s_cnt[PER * lane + i] = e;
+      e += v[i];
+    }
+    if (lane == 63) s_cnt[16 * KB] = incl;
+  }
+  __syncthreads();
+#pragma unroll
+  for (int j = 0; j < KB; ++j) base[j] = s_cnt[16 * j + wid];
+  return s_cnt[16 * KB];
+}
 // The reference counts a migration plan needs: only a Recent page that has
 // left the window and is not an anchor can migrate, and only then does its
 // count decide (a shared page stays FP8); every other entry skips the gather.
@@ -696,21 +754,21 @@ __global__ __launch_bounds__(MIG_NT) void migrate_list_kernel(
     const int32_t* seq_lens, int W, int32_t* ctrl, const int32_t* tq3_stack, int32_t* list,
     const int32_t* mig, int64_t per_blk, int nb, int n_fp8, RcView rv) {
   __shared__ int scratch[32];
+  __shared__ int s_cnt[16 * MIG_KB + 1];
   __shared__ int s_err, s_tot, s_pre;
   const int tid = threadIdx.x, b = blockIdx.x;
   if (tid == 0) { s_err = 0; s_tot = 0; s_pre = 0; }
   __syncthreads();
   const int top3 = ONE ? ctrl[CTRL_TQ3_TOP] : mig[2 * MIG_BLOCKS];
   if constexpr (ONE) {
-    const int64_t N = (int64_t)n_req * max_pages;  // <= MIG_BATCH
     MigBatch m;
-    mig_load(m, (int64_t)tid * MIG_KB, N, max_pages, bt, tags, anchor, seq_lens);
-    mig_load_rc_candidates(m, rv, W);
-    int err = 0, k[MIG_KB], c = 0;
+    mig_load_striped(m, n_req * max_pages, max_pages, bt, tags, anchor, seq_lens);
+    int err = 0, k[MIG_KB], cnt[MIG_KB], base[MIG_KB];
     for (int r = tid; r < n_req; r += MIG_NT) {
       const int S = seq_lens[r];
       if (S < 0 || (S + PAGE - 1) / PAGE > max_pages) err |= MKV_DEVERR_RANGE;
     }
+    mig_load_rc_candidates(m, rv, W);
 #pragma unroll
     for (int j = 0; j < MIG_KB; ++j) {
       const int p = m.pg[j], S = m.sl[j];
@@ -718,11 +776,10 @@ __global__ __launch_bounds__(MIG_NT) void migrate_list_kernel(
                          (p + 1) * PAGE <= S - W && !m.an[j];
       if (old_r && (m.id[j] < 0 || m.id[j] >= n_fp8)) err |= MKV_DEVERR_RANGE;
       k[j] = mig_kind(m, j, W);
-      c += k[j] == 1;
+      cnt[j] = __popcll(__ballot(k[j] == 1));
     }
     if (err) atomicOr(&s_err, err);
-    int total;
-    int e = block_excl_scan(c, scratch, &total);  // its barriers also publish s_err
+    const int total = striped_bases<MIG_KB>(cnt, base, s_cnt);  // its barriers also publish s_err
     err = s_err;
     if (err == 0 && total > top3) err |= MKV_DEVERR_TQ3_EXHAUSTED;
     if (err == 0 && total > n_fp8) err |= MKV_DEVERR_RANGE;
@@ -734,17 +791,17 @@ __global__ __launch_bounds__(MIG_NT) void migrate_list_kernel(
       }
       return;
     }
-    const int64_t f0 = (int64_t)tid * MIG_KB;
+    const uint64_t below = (1ull << (tid & 63)) - 1ull;
 #pragma unroll
     for (int j = 0; j < MIG_KB; ++j) {
-      if (k[j] == 2) tags[f0 + j] = TAG_A;  // Anchor: tag only, stays FP8
+      const int e = base[j] + __popcll(__ballot(k[j] == 1) & below);
+      if (k[j] == 2) tags[j * MIG_NT + tid] = TAG_A;  // Anchor: tag only, stays FP8
       if (k[j] == 1) {
         int32_t* le = list + 4LL * e;
         le[0] = m.rq[j];
         le[1] = m.pg[j];
         le[2] = m.id[j];
         le[3] = tq3_stack[top3 - 1 - e];
-        e++;
       }
     }
     if (tid == 0) {
@@ -1121,7 +1178,9 @@ __global__ __launch_bounds__(1024) void migrate_publish_kernel(int32_t* bt, uint
 // ===========================================================================
 
 // Plan of a promotion: one workgroup walks the table twice (count and
-// validate, then list in (request, page) order with one block scan per batch).
+// validate, then list in (request, page) order with one block scan per batch), or
+// once when the table is one batch (ONE: up to MIG_BATCH entries, kept in
+// registers and ranked by wave ballots).
 // A page is promoted when it is Stale, its mask entry is set and it lies below
 // the request's length.  A failing call (bad length, out-of-range TQ3 id, FP8
 // free list too short) sets the error word and the abort flag and lists
@@ -1132,15 +1191,67 @@ __device__ __forceinline__ bool pro_hit(const MigBatch& m, int j) {
   return m.pg[j] < (m.sl[j] + PAGE - 1) / PAGE;
 }
 
+template <bool ONE>
 __global__ __launch_bounds__(MIG_NT) void promote_plan_kernel(
     int n_req, const int32_t* bt, const uint8_t* tags, int max_pages, const uint8_t* mask,
     const int32_t* seq_lens, int32_t* ctrl, const int32_t* fp8_stack, int32_t* list, int n_tq3,
     RcView rv) {
   __shared__ int scratch[32];
+  __shared__ int s_cnt[16 * MIG_KB + 1];
   __shared__ int s_err, s_tot;
   const int tid = threadIdx.x;
   if (tid == 0) { s_err = 0; s_tot = 0; }
   __syncthreads();
+  if constexpr (ONE) {
+    const int top8 = ctrl[CTRL_FP8_TOP];
+    MigBatch m;
+    mig_load_striped(m, n_req * max_pages, max_pages, bt, tags, mask, seq_lens);
+    int err = 0, wcnt[MIG_KB], base[MIG_KB];
+    for (int r = tid; r < n_req; r += MIG_NT) {
+      const int S = seq_lens[r];
+      if (S < 0 || (S + PAGE - 1) / PAGE > max_pages) err |= MKV_DEVERR_RANGE;
+    }
+    mig_load_rc(m, rv);
+    bool hit[MIG_KB];
+#pragma unroll
+    for (int j = 0; j < MIG_KB; ++j) {
+      if (m.rq[j] >= 0 && m.tg[j] == TAG_S && m.an[j] && m.pg[j] < (m.sl[j] + PAGE - 1) / PAGE &&
+          (m.id[j] < 0 || m.id[j] >= n_tq3))
+        err |= MKV_DEVERR_RANGE;
+      hit[j] = pro_hit(m, j);
+      wcnt[j] = __popcll(__ballot(hit[j]));
+    }
+    if (err) atomicOr(&s_err, err);
+    const int total = striped_bases<MIG_KB>(wcnt, base, s_cnt);  // its barriers also publish s_err
+    err = s_err;
+    if (err == 0 && total > top8) err |= MKV_DEVERR_FP8_EXHAUSTED;
+    if (err) {
+      if (tid == 0) {
+        atomicOr(&ctrl[CTRL_ERR], err);
+        ctrl[CTRL_ABORT] = 1;
+        ctrl[CTRL_NLIST] = 0;
+      }
+      return;
+    }
+    const uint64_t below = (1ull << (tid & 63)) - 1ull;
+#pragma unroll
+    for (int j = 0; j < MIG_KB; ++j) {
+      const int e = base[j] + __popcll(__ballot(hit[j]) & below);
+      if (hit[j]) {
+        int32_t* le = list + 4LL * e;
+        le[0] = m.rq[j];
+        le[1] = m.pg[j];
+        le[2] = m.id[j];                   // TQ3 source
+        le[3] = fp8_stack[top8 - 1 - e];   // FP8 destination
+      }
+    }
+    if (tid == 0) {
+      ctrl[CTRL_FP8_TOP] = top8 - total;
+      ctrl[CTRL_NLIST] = total;
+      ctrl[CTRL_ABORT] = 0;
+    }
+    return;
+  }
   const int64_t N = (int64_t)n_req * max_pages;
   int err = 0, cnt = 0;
   for (int r = tid; r < n_req; r += MIG_NT) {
@@ -1389,26 +1500,84 @@ __global__ __launch_bounds__(1024) void pages_acquire_kernel(int n, const int32_
 // the rows of the listed requests (entry j * max_pages + p = row reqs[j], page
 // p, mapped entries only).  Each entry drops one reference, in entry order: a
 // page whose count reaches zero is pushed onto its free list at its last
-// entry.  Pass 1 counts each page's entries and finds its last one (scratch
-// occ / last, 0 / -1 at rest); a page with more entries than references, a
-// bad tag or id, or a bad request list fails the call (scratch restored,
-// nothing else changed).  Pass 2 walks the entries in order, ranks the
-// freeing ones with a block scan and applies the counts; table rows are then
-// unmapped.
-__global__ __launch_bounds__(1024) void pages_release_kernel(int n, const int32_t* ids,
-                                                             const uint8_t* tags, int n_fin,
-                                                             const int32_t* reqs, int n_req,
-                                                             int32_t* bt, uint8_t* bt_tags,
-                                                             int max_pages, PoolView P) {
-  __shared__ int scratch[32];
+// entry.  Pass 1 counts each page's entries and finds its last one; a page with
+// more entries than references, a bad tag or id, or a bad request list fails the
+// call (nothing changed).  Pass 2 ranks the freeing entries in order, applies the
+// counts and unmaps the table rows.
+// Bound by the pages' scattered words, one address a cycle for the workgroup's CU,
+// and by memory round trips in a row.  So REL_KB entries per thread are in flight
+// (entry b0 + j NT + tid in slot j), and a call of one batch (REL_BATCH entries)
+// keeps its entries in registers and finds counts and last entries in an LDS hash
+// table of the pages: only the reference counts are scattered.  A longer call
+// does that in the pool's scratch (occ / last, 0 / -1 at rest, restored when the
+// call fails) and loads its entries again in every pass.  16 rows of 214 pages take
+// 8.8 us, 22 us with the scratch, and 28 us entry by entry.
+constexpr int REL_NT = 1024, REL_KB = 4;
+constexpr int64_t REL_BATCH = (int64_t)REL_NT * REL_KB;
+constexpr int REL_SLOTS = (int)REL_BATCH * 3 / 2;  // hash slots: two thirds full at most
+__global__ __launch_bounds__(REL_NT) void pages_release_kernel(int n, const int32_t* ids,
+                                                               const uint8_t* tags, int n_fin,
+                                                               const int32_t* reqs, int n_req,
+                                                               int32_t* bt, uint8_t* bt_tags,
+                                                               int max_pages, PoolView P) {
+  __shared__ int s_cnt[16 * REL_KB + 1];
   __shared__ int s_err;
+  __shared__ int s_key[REL_SLOTS], s_occ[REL_SLOTS];
   const int tid = threadIdx.x;
   const bool table = reqs != nullptr;
   const int64_t N = table ? (int64_t)n_fin * max_pages : n;
+  const bool one = N <= REL_BATCH;
+  const int top8 = P.ctrl[CTRL_FP8_TOP], top3 = P.ctrl[CTRL_TQ3_TOP];
   if (tid == 0) s_err = 0;
+  if (one)
+    for (int i = tid; i < REL_SLOTS; i += REL_NT) {
+      s_key[i] = -1;
+      s_occ[i] = 0;
+    }
   __syncthreads();
+  // a batch's entries: where they stand, page id, format; REL_NO: no entry or an
+  // unmapped one, REL_BAD: names no page
+  enum { REL_FP8 = 0, REL_TQ3 = 1, REL_NO = 2, REL_BAD = 3 };
+  int id[REL_KB], fm[REL_KB];
+  int64_t at[REL_KB];  // index of the table entry, -1: none
+  auto load = [&](int64_t b0) {
+    uint8_t tg[REL_KB];
+#pragma unroll
+    for (int j = 0; j < REL_KB; ++j) {
+      const int64_t k = b0 + j * REL_NT + tid;
+      at[j] = -1;
+      id[j] = -1;
+      tg[j] = TAG_NONE;
+      fm[j] = REL_NO;
+      if (b0 + j * REL_NT < N) {  // workgroup-uniform
+        const bool in = k < N;
+        if (table) {
+          const int64_t kk = in ? k : 0;
+          const int64_t q = N >> 32 ? kk / max_pages : (int64_t)((uint32_t)kk / (uint32_t)max_pages);
+          const int r = reqs[q];
+          // (a row out of range fails the call before anything is applied)
+          if (in && r >= 0 && r < n_req) at[j] = (int64_t)r * max_pages + (kk - q * max_pages);
+        } else if (in) {
+          at[j] = k;
+        }
+      }
+    }
+#pragma unroll
+    for (int j = 0; j < REL_KB; ++j)
+      if (b0 + j * REL_NT < N && at[j] >= 0) {
+        id[j] = table ? bt[at[j]] : ids[at[j]];
+        tg[j] = table ? bt_tags[at[j]] : tags[at[j]];
+      }
+#pragma unroll
+    for (int j = 0; j < REL_KB; ++j)
+      if (at[j] >= 0 && !(table && id[j] < 0)) {
+        int f;
+        fm[j] = ref_of(tg[j], id[j], P.n_fp8, P.n_tq3, f) ? f : REL_BAD;
+      }
+  };
+  load(0);
   if (table) {
-    for (int j = tid; j < n_fin; j += blockDim.x) {
+    for (int j = tid; j < n_fin; j += REL_NT) {
       const int r = reqs[j];
       if (r < 0 || r >= n_req || (j > 0 && reqs[j - 1] >= r)) atomicOr(&s_err, (int)MKV_DEVERR_RANGE);
     }
@@ -1418,93 +1587,135 @@ __global__ __launch_bounds__(1024) void pages_release_kernel(int n, const int32_
       return;
     }
   }
-  // entry k -> (mapped, fmt, id); false for an unmapped table entry
-  auto entry = [&](int64_t k, int& fmt, int& id, bool& ok) {
-    uint8_t tg;
-    if (table) {
-      const int64_t i = (int64_t)reqs[k / max_pages] * max_pages + k % max_pages;
-      id = bt[i];
-      tg = bt_tags[i];
-      if (id < 0) {
-        ok = false;
-        return false;
-      }
-    } else {
-      id = ids[k];
-      tg = tags[k];
+  int occ[REL_KB], rc[REL_KB], lst[REL_KB];
+  if (one) {
+    int slot[REL_KB];
+#pragma unroll
+    for (int j = 0; j < REL_KB; ++j) {
+      occ[j] = rc[j] = slot[j] = 0;
+      lst[j] = -1;
+      if (fm[j] < REL_NO) rc[j] = (fm[j] ? P.rc3 : P.rc8)[id[j]];
+      if (fm[j] == REL_BAD) atomicOr(&s_err, (int)MKV_DEVERR_REFCOUNT);
     }
-    ok = ref_of(tg, id, P.n_fp8, P.n_tq3, fmt);
-    return true;
+#pragma unroll
+    for (int j = 0; j < REL_KB; ++j)
+      if (fm[j] < REL_NO) {  // the page's slot: there are more slots than entries, so one is found
+        const int key = (int)((uint32_t)id[j] << 1) | fm[j];
+        int h = (int)__umulhi((uint32_t)key * 2654435761u, (uint32_t)REL_SLOTS);
+        for (int old; (old = atomicCAS(&s_key[h], -1, key)) != -1 && old != key;) h = h + 1 == REL_SLOTS ? 0 : h + 1;
+        atomicAdd(&s_occ[h], 1);
+        slot[j] = h;
+      }
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < REL_KB; ++j)
+      if (fm[j] < REL_NO) {
+        occ[j] = s_occ[slot[j]];
+        s_key[slot[j]] = 0;  // from here on the slot's largest entry index
+        if (occ[j] > rc[j]) atomicOr(&s_err, (int)MKV_DEVERR_REFCOUNT);
+      }
+    __syncthreads();
+    if (s_err) {
+      if (tid == 0) atomicOr(&P.ctrl[CTRL_ERR], s_err);
+      return;
+    }
+#pragma unroll
+    for (int j = 0; j < REL_KB; ++j)
+      if (fm[j] < REL_NO) atomicMax(&s_key[slot[j]], j * REL_NT + tid);
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < REL_KB; ++j)
+      if (fm[j] < REL_NO) lst[j] = s_key[slot[j]];
+  } else {
+    for (int64_t b0 = 0; b0 < N; b0 += REL_BATCH) {
+      if (b0 > 0) load(b0);
+#pragma unroll
+      for (int j = 0; j < REL_KB; ++j) {
+        if (fm[j] == REL_BAD) atomicOr(&s_err, (int)MKV_DEVERR_REFCOUNT);
+        if (fm[j] < REL_NO) {
+          atomicAdd(&(fm[j] ? P.occ3 : P.occ8)[id[j]], 1);
+          atomicMax(&(fm[j] ? P.last3 : P.last8)[id[j]], (int)(b0 + j * REL_NT + tid));
+        }
+      }
+    }
+    __syncthreads();
+  }
+  auto counts = [&]() {
+#pragma unroll
+    for (int j = 0; j < REL_KB; ++j) {
+      occ[j] = rc[j] = 0;
+      lst[j] = -1;
+      if (fm[j] < REL_NO) {
+        occ[j] = (fm[j] ? P.occ3 : P.occ8)[id[j]];
+        rc[j] = (fm[j] ? P.rc3 : P.rc8)[id[j]];
+        lst[j] = (fm[j] ? P.last3 : P.last8)[id[j]];
+      }
+    }
   };
-  for (int64_t k = tid; k < N; k += blockDim.x) {
-    int fmt, id;
-    bool ok;
-    if (!entry(k, fmt, id, ok)) continue;
-    if (!ok) {
-      atomicOr(&s_err, (int)MKV_DEVERR_REFCOUNT);
-      continue;
+  if (!one) {
+    for (int64_t b0 = 0; b0 < N; b0 += REL_BATCH) {
+      load(b0);
+      counts();
+#pragma unroll
+      for (int j = 0; j < REL_KB; ++j)
+        if (occ[j] > rc[j]) atomicOr(&s_err, (int)MKV_DEVERR_REFCOUNT);
     }
-    atomicAdd(&(fmt ? P.occ3 : P.occ8)[id], 1);
-    atomicMax(&(fmt ? P.last3 : P.last8)[id], (int)k);
-  }
-  __syncthreads();
-  for (int64_t k = tid; k < N; k += blockDim.x) {
-    int fmt, id;
-    bool ok;
-    if (!entry(k, fmt, id, ok) || !ok) continue;
-    if ((fmt ? P.occ3 : P.occ8)[id] > (fmt ? P.rc3 : P.rc8)[id]) atomicOr(&s_err, (int)MKV_DEVERR_REFCOUNT);
-  }
-  __syncthreads();
-  const int err = s_err;
-  if (err) {
-    for (int64_t k = tid; k < N; k += blockDim.x) {
-      int fmt, id;
-      bool ok;
-      if (!entry(k, fmt, id, ok) || !ok) continue;
-      (fmt ? P.occ3 : P.occ8)[id] = 0;
-      (fmt ? P.last3 : P.last8)[id] = -1;
+    __syncthreads();
+    const int err = s_err;
+    if (err) {
+      for (int64_t b0 = 0; b0 < N; b0 += REL_BATCH) {
+        load(b0);
+#pragma unroll
+        for (int j = 0; j < REL_KB; ++j)
+          if (fm[j] < REL_NO) {
+            (fm[j] ? P.occ3 : P.occ8)[id[j]] = 0;
+            (fm[j] ? P.last3 : P.last8)[id[j]] = -1;
+          }
+      }
+      if (tid == 0) atomicOr(&P.ctrl[CTRL_ERR], err);
+      return;
     }
-    if (tid == 0) atomicOr(&P.ctrl[CTRL_ERR], err);
-    return;
   }
-  const int top8 = P.ctrl[CTRL_FP8_TOP], top3 = P.ctrl[CTRL_TQ3_TOP];
+  const uint64_t below = (1ull << (tid & 63)) - 1ull;
   int base8 = 0, base3 = 0;
-  for (int64_t b0 = 0; b0 < N; b0 += blockDim.x) {
-    const int64_t k = b0 + tid;
-    int fmt = 0, id = 0;
-    bool ok = false;
-    bool last = false, freed = false;
-    if (k < N && entry(k, fmt, id, ok) && ok) {
-      int32_t* lastv = fmt ? P.last3 : P.last8;
-      last = lastv[id] == (int)k;
+  for (int64_t b0 = 0; b0 < N; b0 += REL_BATCH) {
+    if (!one) {
+      load(b0);
+      counts();
+    }
+    // waves' counts of the freeing entries, FP8 in the low and TQ3 in the high half
+    bool freed[REL_KB];
+    int cnt[REL_KB], base[REL_KB];
+#pragma unroll
+    for (int j = 0; j < REL_KB; ++j) {
+      const bool last = fm[j] < REL_NO && lst[j] == (int)(b0 + j * REL_NT + tid);
+      freed[j] = last && rc[j] == occ[j];
+      cnt[j] = __popcll(__ballot(freed[j] && fm[j] == REL_FP8)) | __popcll(__ballot(freed[j] && fm[j] == REL_TQ3)) << 16;
       if (last) {
-        int32_t* rc = fmt ? P.rc3 : P.rc8;
-        int32_t* occ = fmt ? P.occ3 : P.occ8;
-        const int left = rc[id] - occ[id];
-        freed = left == 0;
-        rc[id] = left;
-        occ[id] = 0;
-        lastv[id] = -1;
+        (fm[j] ? P.rc3 : P.rc8)[id[j]] = rc[j] - occ[j];
+        if (!one) {
+          (fm[j] ? P.occ3 : P.occ8)[id[j]] = 0;
+          (fm[j] ? P.last3 : P.last8)[id[j]] = -1;
+        }
+      }
+      if (table && at[j] >= 0) {
+        bt[at[j]] = -1;
+        bt_tags[at[j]] = TAG_NONE;
       }
     }
-    // ranks of the freeing entries, FP8 in the low and TQ3 in the high half
-    const int v = freed ? (fmt ? (1 << 16) : 1) : 0;
-    int tot;
-    const int pre = block_excl_scan(v, scratch, &tot);
-    if (freed) {
-      if (fmt) P.tq3_stack[top3 + base3 + (pre >> 16)] = id;
-      else P.fp8_stack[top8 + base8 + (pre & 0xFFFF)] = id;
+    const int tot = striped_bases<REL_KB>(cnt, base, s_cnt);
+#pragma unroll
+    for (int j = 0; j < REL_KB; ++j) {
+      const uint64_t m8 = __ballot(freed[j] && fm[j] == REL_FP8), m3 = __ballot(freed[j] && fm[j] == REL_TQ3);
+      if (freed[j]) {
+        if (fm[j]) P.tq3_stack[top3 + base3 + (base[j] >> 16) + __popcll(m3 & below)] = id[j];
+        else P.fp8_stack[top8 + base8 + (base[j] & 0xFFFF) + __popcll(m8 & below)] = id[j];
+      }
     }
     base8 += tot & 0xFFFF;
     base3 += tot >> 16;
+    __syncthreads();  // s_cnt is free for the next batch
   }
-  __syncthreads();
-  if (table)
-    for (int64_t k = tid; k < N; k += blockDim.x) {
-      const int64_t i = (int64_t)reqs[k / max_pages] * max_pages + k % max_pages;
-      bt[i] = -1;
-      bt_tags[i] = TAG_NONE;
-    }
   if (tid == 0) {
     P.ctrl[CTRL_FP8_TOP] = top8 + base8;
     P.ctrl[CTRL_TQ3_TOP] = top3 + base3;
@@ -1522,7 +1733,7 @@ hipError_t launch_pages_release(const PoolView& P, int n, const int32_t* ids, co
                                 int n_fin, const int32_t* reqs, int n_req, int32_t* bt,
                                 uint8_t* bt_tags, int max_pages, hipStream_t s) {
   if ((reqs ? n_fin : n) == 0) return hipSuccess;
-  hipLaunchKernelGGL(pages_release_kernel, dim3(1), dim3(1024), 0, s, n, ids, tags, n_fin, reqs,
+  hipLaunchKernelGGL(pages_release_kernel, dim3(1), dim3(REL_NT), 0, s, n, ids, tags, n_fin, reqs,
                      n_req, bt, bt_tags, max_pages, P);
   return hipGetLastError();
 }
@@ -1652,9 +1863,9 @@ hipError_t launch_migrate(const PoolView& P, int n_req, int32_t* bt, uint8_t* ta
 
 hipError_t launch_promote(const PoolView& P, int n_req, int32_t* bt, uint8_t* tags, int max_pages,
                           const uint8_t* mask, const int32_t* seq_lens, hipStream_t s) {
-  hipLaunchKernelGGL(promote_plan_kernel, dim3(1), dim3(MIG_NT), 0, s, n_req, bt, tags, max_pages,
-                     mask, seq_lens, P.ctrl, P.fp8_stack, P.list, P.n_tq3,
-                     RcView{P.rc8, P.rc3, P.n_fp8, P.n_tq3});
+  const auto plan = (int64_t)n_req * max_pages <= MIG_BATCH ? promote_plan_kernel<true> : promote_plan_kernel<false>;
+  hipLaunchKernelGGL(plan, dim3(1), dim3(MIG_NT), 0, s, n_req, bt, tags, max_pages, mask, seq_lens, P.ctrl,
+                     P.fp8_stack, P.list, P.n_tq3, RcView{P.rc8, P.rc3, P.n_fp8, P.n_tq3});
   int64_t bound = (int64_t)n_req * max_pages;
   if (bound > P.n_fp8) bound = P.n_fp8;
   if (bound > P.n_tq3) bound = P.n_tq3;
