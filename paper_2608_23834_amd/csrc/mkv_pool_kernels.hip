@@ -1322,115 +1322,159 @@ __global__ __launch_bounds__(MIG_NT) void promote_plan_kernel(
   }
 }
 
-// Rebuild one listed page-head (layer, KV head) from its TQ3 region into its
-// new FP8 region; 256 threads, thread (t, l) = (tid / 16, tid % 16) owns token
-// t and channels l + 16 j.
-//  keys: codes -> 8 * codebook level (integers), the Walsh-Hadamard transform
-//        of each token row in int32 (exact), then
-//        k = fp32((gamma * sigma_c * (y_c / 8)) / sqrt(D)) -- the products are
-//        exact in fp64, the division the only fp64 rounding;
-//  values: v = fp32(zero_c + scale_c * code), exact in fp64 before the
-//        conversion;
-//  FP8: per K and per V, s = amax / 448 over the 16 x D values, code =
-//        E4M3(x / s) (0 when s = 0), the page written in the FP8 layout.
+// One half of a rebuilt page-head: the lane's D/4 values, neighbours in the FP8
+// layout, and the page's scale.  s = amax / 448 over the 16 x D values, code =
+// E4M3(x / s) (0 when s = 0).
 template <int D>
-__global__ __launch_bounds__(256) void promote_build_kernel(PoolView P) {
+__device__ __forceinline__ void dec_store(const float (&x)[D / 4], uint8_t* dst, float* scale, int lane) {
+  float amax = 0.0f;
+#pragma unroll
+  for (int i = 0; i < D / 4; ++i) amax = fmaxf(amax, fabsf(x[i]));
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) amax = fmaxf(amax, __shfl_xor(amax, o, 64));
+  const float s = amax / 448.0f;
+  uint32_t w[D / 16];
+  if (__builtin_amdgcn_readfirstlane(div_fast(s))) {
+    const float y = 1.0f / s;
+#pragma unroll
+    for (int i = 0; i < D / 16; ++i)
+      w[i] = pack_e4m3(div_by(x[4 * i], s, y), div_by(x[4 * i + 1], s, y), div_by(x[4 * i + 2], s, y),
+                       div_by(x[4 * i + 3], s, y));
+  } else {
+#pragma unroll
+    for (int i = 0; i < D / 16; ++i)
+      w[i] = s > 0.0f ? pack_e4m3(x[4 * i] / s, x[4 * i + 1] / s, x[4 * i + 2] / s, x[4 * i + 3] / s) : 0u;
+  }
+#pragma unroll
+  for (int i = 0; i < D / 64; ++i)
+    reinterpret_cast<uint4*>(dst)[i] = make_uint4(w[4 * i], w[4 * i + 1], w[4 * i + 2], w[4 * i + 3]);
+  if (lane == 0) *scale = s;
+}
+// the quads of the chunk at c
+template <int NDW>
+__device__ __forceinline__ void load_chunk(uint32_t* dw, const uint8_t* c) {
+  if constexpr (NDW % 2 == 0) {
+#pragma unroll
+    for (int j = 0; j < NDW / 2; ++j) {
+      const uint2 v = reinterpret_cast<const uint2*>(c)[j];
+      dw[2 * j] = v.x;
+      dw[2 * j + 1] = v.y;
+    }
+  } else {
+#pragma unroll
+    for (int j = 0; j < NDW; ++j) dw[j] = reinterpret_cast<const uint32_t*>(c)[j];
+  }
+}
+// Keys of a page-head: lane 4 t + g owns K chunk (t, g), channels D/4 g .. of token
+// t.  codes -> 8 * codebook level (integers), the Walsh-Hadamard transform (sums of
+// integers below 2^13, exact in fp32), then k = fp32((gamma * sigma_c * (y_c / 8)) /
+// sqrt(D)): gamma (11 bits) times y is exact in fp32, so the division is the only
+// rounding (D = 256: a power of two, none before the conversion).
+template <int D>
+__device__ __forceinline__ void dec_keys(const uint32_t* sgn, const uint8_t* reg, uint8_t* f8, float* scale,
+                                         int lane) {
+  constexpr int QK = D / 4, NDW = 3 * D / 128, CB = 3 * D / 32;
+  const int t = lane >> 2, g = lane & 3;
+  uint32_t dw[NDW];
+  load_chunk<NDW>(dw, reg + (g * 16 + t) * CB);
+  const float gam = (float)reinterpret_cast<const _Float16*>(reg + 12 * D)[t];
+  float y[QK];
+#pragma unroll
+  for (int q = 0; q < QK / 4; ++q) {
+    // levels -18, -11, -6, -2, 2, 6, 11, 18 by code
+    const uint32_t l = __builtin_amdgcn_perm(0x120B0602u, 0xFEFAF5EEu, quad_sel<NDW>(dw, q));
+#pragma unroll
+    for (int b = 0; b < 4; ++b) y[4 * q + b] = (float)(int)(int8_t)(l >> (8 * b));
+  }
+#pragma unroll
+  for (int st = 1; st < QK; st <<= 1)
+#pragma unroll
+    for (int i = 0; i < QK; ++i)
+      if (!(i & st)) {
+        const float a0 = y[i], a1 = y[i + st];
+        y[i] = a0 + a1;
+        y[i + st] = a0 - a1;
+      }
+  // strides D/4 and D/2: lanes g ^ 1 and g ^ 2
+  const float m1 = (g & 1) ? -1.0f : 1.0f, m2 = (g & 2) ? -1.0f : 1.0f;
+  auto dpp = [](float v, auto ctl) {
+    return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), decltype(ctl)::value, 0xF, 0xF, false));
+  };
+#pragma unroll
+  for (int i = 0; i < QK; ++i) {
+    y[i] = __builtin_fmaf(m1, y[i], dpp(y[i], std::integral_constant<int, 0xB1>{}));
+    y[i] = __builtin_fmaf(m2, y[i], dpp(y[i], std::integral_constant<int, 0x4E>{}));
+  }
+  const double rd = sqrt((double)D);
+#pragma unroll
+  for (int i = 0; i < QK; ++i) {
+    const uint32_t flip = (sgn[i / 4] << (24 - 8 * (i % 4))) & 0x80000000u;
+    const float a = __uint_as_float(__float_as_uint(gam) ^ flip) * (y[i] * 0.125f);  // exact
+    if constexpr (D == 256) y[i] = a * 0.0625f;
+    else y[i] = (float)((double)a / rd);
+  }
+  dec_store<D>(y, f8 + t * D + QK * g, scale, lane);
+}
+// Values: lane 16 g + r owns V chunk (r, g), whose quad m is the FP8 layout's dword
+// m of lane-chunk (r, g) (tokens 4 g .. of channel CL r + m).  v = fp32(zero_c +
+// scale_c * code): one fused multiply-add, the product and sum exact before its
+// rounding.
+template <int D>
+__device__ __forceinline__ void dec_values(const uint8_t* reg, uint8_t* f8, float* scale, int lane) {
+  constexpr int CL = D / 16, NDW = 3 * D / 128, CB = 3 * D / 32;
+  const int g = lane >> 4, r = lane & 15;
+  uint32_t dw[NDW];
+  load_chunk<NDW>(dw, reg + 6 * D + (g * 16 + r) * CB);
+  half8 sc[CL / 8], zr[CL / 8];
+#pragma unroll
+  for (int i = 0; i < CL / 8; ++i) {
+    sc[i] = reinterpret_cast<const half8*>(reg + 12 * D + 32 + 2 * CL * r)[i];
+    zr[i] = reinterpret_cast<const half8*>(reg + 14 * D + 32 + 2 * CL * r)[i];
+  }
+  float v[D / 4];
+#pragma unroll
+  for (int m = 0; m < CL; ++m) {
+    const uint32_t q = quad_sel<NDW>(dw, m);
+#pragma unroll
+    for (int b = 0; b < 4; ++b)
+      v[4 * m + b] = __builtin_fmaf((float)sc[m / 8][m % 8], (float)((q >> (8 * b)) & 0xFFu), (float)zr[m / 8][m % 8]);
+  }
+  dec_store<D>(v, f8 + PAGE * D + (r * 4 + g) * (D / 4), scale, lane);
+}
+
+// Rebuild every listed page-head (layer, KV head) from its TQ3 region into its new
+// FP8 region, two waves to a page-head, one its keys and one its values, roles
+// swapped from one page-head to the next (as in the encode).  Everything stays in
+// registers and there is no barrier: 95 pages x 4 heads x 4 layers at d = 256 took
+// 36 us with a workgroup and an LDS transform per page-head, now 16.5 us.
+template <int D>
+__global__ __launch_bounds__(64 * ENC_WG, 2) void promote_build_kernel(PoolView P) {
   if (P.ctrl[CTRL_ABORT]) return;
-  constexpr int NDW = 3 * D / 128, CB = 3 * D / 32, CL = D / 16, NJ = D / 16;
-  constexpr int R3W = (int)tq3_region_bytes(D) / 4;
-  constexpr int R8W = (int)fp8_region_bytes(D) / 4;
-  __shared__ uint32_t src[R3W];
-  __shared__ int32_t y[PAGE * D];
-  __shared__ uint32_t dst[R8W];
-  __shared__ float s_red[2][4];
   const int H = P.n_kv_heads, L = P.n_layers;
   const int64_t n_items = (int64_t)P.ctrl[CTRL_NLIST] * L * H;
-  const int tid = threadIdx.x, t = tid >> 4, l16 = tid & 15, lane = tid & 63, wv = tid >> 6;
-  // 8 * codebook level of each 3-bit code (levels +-0.25, 0.75, 1.375, 2.25)
-  const int lvl8[8] = {-18, -11, -6, -2, 2, 6, 11, 18};
-  for (int64_t item = blockIdx.x; item < n_items; item += gridDim.x) {
+  const int lane = threadIdx.x & 63, wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int64_t pair0 = (int64_t)blockIdx.x * (ENC_WG / 2) + (wid >> 1);
+  if (pair0 >= n_items) return;
+  // sign bits of the rotation's diagonal at the bytes of this lane's key channels
+  uint32_t sgn[D / 16];
+  {
+    const uint32_t* sg = reinterpret_cast<const uint32_t*>(P.sigma + (D / 4) * (lane & 3));
+#pragma unroll
+    for (int i = 0; i < D / 16; ++i) sgn[i] = sg[i] & 0x80808080u;
+  }
+  int role = (wid + blockIdx.x) & 1;
+  for (int64_t item = pair0; item < n_items; item += (int64_t)gridDim.x * (ENC_WG / 2), role ^= 1) {
     const int e = (int)(item / (L * H));
     const int lh = (int)(item % (L * H));
     const int layer = lh / H, h = lh % H;
-    const int sid = P.list[4 * e + 2], did = P.list[4 * e + 3];
-    const uint32_t* reg3 = reinterpret_cast<const uint32_t*>(
-        P.tq3 + (((int64_t)layer * P.n_tq3 + sid) * H + h) * tq3_region_bytes(D));
-    for (int w = tid; w < R3W; w += 256) src[w] = reg3[w];
-    __syncthreads();
-    const uint8_t* sb = reinterpret_cast<const uint8_t*>(src);
-    // key codes of token t, channels l16 + 16 j: chunk (t, g), quad q, byte b
-#pragma unroll
-    for (int j = 0; j < NJ; ++j) {
-      const int c = l16 + 16 * j;
-      const int g = c / (D / 4), cc = c % (D / 4);
-      const uint32_t* ch = reinterpret_cast<const uint32_t*>(sb + (g * 16 + t) * CB);
-      uint32_t dw[NDW];
-#pragma unroll
-      for (int k = 0; k < NDW; ++k) dw[k] = ch[k];
-      const uint32_t code = (quad_sel<NDW>(dw, cc >> 2) >> (8 * (cc & 3))) & 7u;
-      y[t * D + c] = lvl8[code];
-    }
-    __syncthreads();
-    for (int st = 1; st < D; st <<= 1) {
-      for (int b = l16; b < D / 2; b += 16) {
-        const int i = (b / st) * 2 * st + (b % st);
-        const int32_t a0 = y[t * D + i], a1 = y[t * D + i + st];
-        y[t * D + i] = a0 + a1;
-        y[t * D + i + st] = a0 - a1;
-      }
-      __syncthreads();
-    }
-    const double gam = f16_bits_to_f64(reinterpret_cast<const uint16_t*>(sb + 12 * D)[t]);
-    const double rd = sqrt((double)D);
-    float kx[NJ], vx[NJ];
-    float kmax = 0.0f, vmax = 0.0f;
-#pragma unroll
-    for (int j = 0; j < NJ; ++j) {
-      const int c = l16 + 16 * j;
-      const double hc = (double)y[t * D + c] * 0.125;  // exact
-      const double a = (gam * (double)P.sigma[c]) * hc;
-      kx[j] = (float)(a / rd);
-      kmax = fmaxf(kmax, fabsf(kx[j]));
-      // value code of (t, c): V chunk (c / CL, t / 4), quad c % CL, byte t % 4
-      const uint32_t* ch = reinterpret_cast<const uint32_t*>(sb + 6 * D + ((t >> 2) * 16 + c / CL) * CB);
-      uint32_t dw[NDW];
-#pragma unroll
-      for (int k = 0; k < NDW; ++k) dw[k] = ch[k];
-      const uint32_t vc = (quad_sel<NDW>(dw, c % CL) >> (8 * (t & 3))) & 7u;
-      const double sc = f16_bits_to_f64(reinterpret_cast<const uint16_t*>(sb + 12 * D + 32)[c]);
-      const double zr = f16_bits_to_f64(reinterpret_cast<const uint16_t*>(sb + 14 * D + 32)[c]);
-      vx[j] = (float)(zr + sc * (double)vc);
-      vmax = fmaxf(vmax, fabsf(vx[j]));
-    }
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-      kmax = fmaxf(kmax, __shfl_xor(kmax, o, 64));
-      vmax = fmaxf(vmax, __shfl_xor(vmax, o, 64));
-    }
-    if (lane == 0) {
-      s_red[0][wv] = kmax;
-      s_red[1][wv] = vmax;
-    }
-    __syncthreads();
-    const float ka = fmaxf(fmaxf(s_red[0][0], s_red[0][1]), fmaxf(s_red[0][2], s_red[0][3]));
-    const float va = fmaxf(fmaxf(s_red[1][0], s_red[1][1]), fmaxf(s_red[1][2], s_red[1][3]));
-    const float sK = ka / 448.0f, sV = va / 448.0f;
-    uint8_t* db = reinterpret_cast<uint8_t*>(dst);
-#pragma unroll
-    for (int j = 0; j < NJ; ++j) {
-      const int c = l16 + 16 * j;
-      db[fp8_off<D>(0, t, c)] = (uint8_t)(sK > 0.0f ? f32_to_e4m3(kx[j] / sK) : 0u);
-      db[fp8_off<D>(1, t, c)] = (uint8_t)(sV > 0.0f ? f32_to_e4m3(vx[j] / sV) : 0u);
-    }
-    __syncthreads();
-    const int64_t ph = ((int64_t)layer * P.n_fp8 + did) * H + h;
-    uint32_t* reg8 = reinterpret_cast<uint32_t*>(P.fp8 + ph * fp8_region_bytes(D));
-    for (int w = tid; w < R8W; w += 256) reg8[w] = dst[w];
-    if (tid == 0) {
-      P.fp8_scales[ph * 2] = sK;
-      P.fp8_scales[ph * 2 + 1] = sV;
-    }
-    __syncthreads();
+    const int src = P.list[4 * e + 2], dst = P.list[4 * e + 3];
+    const uint8_t* reg = P.tq3 + (((int64_t)layer * P.n_tq3 + src) * H + h) * tq3_region_bytes(D);
+    const int64_t ph = ((int64_t)layer * P.n_fp8 + dst) * H + h;
+    uint8_t* f8 = P.fp8 + ph * fp8_region_bytes(D);
+    if (role == 0)
+      dec_keys<D>(sgn, reg, f8, P.fp8_scales + ph * 2, lane);
+    else
+      dec_values<D>(reg, f8, P.fp8_scales + ph * 2 + 1, lane);
   }
 }
 
@@ -1869,11 +1913,11 @@ hipError_t launch_promote(const PoolView& P, int n_req, int32_t* bt, uint8_t* ta
   int64_t bound = (int64_t)n_req * max_pages;
   if (bound > P.n_fp8) bound = P.n_fp8;
   if (bound > P.n_tq3) bound = P.n_tq3;
-  const int grid = grid_for(bound * P.n_layers * P.n_kv_heads, 2048);
+  const int grid = grid_for((bound * P.n_layers * P.n_kv_heads + ENC_WG / 2 - 1) / (ENC_WG / 2), 1024);
   if (P.d == 256)
-    hipLaunchKernelGGL(promote_build_kernel<256>, dim3(grid), dim3(256), 0, s, P);
+    hipLaunchKernelGGL(promote_build_kernel<256>, dim3(grid), dim3(64 * ENC_WG), 0, s, P);
   else
-    hipLaunchKernelGGL(promote_build_kernel<128>, dim3(grid), dim3(256), 0, s, P);
+    hipLaunchKernelGGL(promote_build_kernel<128>, dim3(grid), dim3(64 * ENC_WG), 0, s, P);
   hipLaunchKernelGGL(promote_publish_kernel, dim3(1), dim3(1024), 0, s, bt, tags, max_pages, P.ctrl,
                      P.tq3_stack, P.list, P.rc8, P.rc3);
   return hipGetLastError();
