@@ -202,11 +202,13 @@ __global__ __launch_bounds__(LIST_NT) void chunk_lists_kernel(const int32_t* bt,
 // of the chip, estimates a round as U + CUT_COST (a part's own start, its
 // partial results' way through memory and the merge, measured) and takes the
 // best, or leaves the blocks whole where that is estimated as good.  Cost
-// units: 4 per TQ3 pair, 3 per FP8 pair (their measured ratio).
+// units: 4 per pass, of either format (1.80 us per TQ3 pair and 1.87 per FP8 pair at
+// d = 256; with 3 per FP8 pair a 6,001-token prefill's twelve calls took 2,738 us,
+// now 2,688).
 // items: two int4 per work item, {request, block of the request, first TQ3 pair,
 // TQ3 pairs}, {first FP8 pair, FP8 pairs, part slot or -1, -}; splits: {request,
 // block of the request, first part slot, parts}.
-constexpr int COST3 = 4, COST8 = 3;
+constexpr int COST3 = 4, COST8 = 4;
 constexpr int CUT_COST = 12 * COST3, MIN_PART = 4 * COST3;
 __global__ __launch_bounds__(1024) void chunk_plan_kernel(int n_req, const int32_t* cu_q, int n_q_total,
                                                           const int32_t* seq_lens, int max_pages,
