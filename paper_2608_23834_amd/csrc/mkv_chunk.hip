@@ -197,7 +197,7 @@ __global__ __launch_bounds__(LIST_NT) void chunk_lists_kernel(const int32_t* bt,
 // Cutting: a block's passes run one after the other on one CU, so a call with
 // fewer blocks than CUs, or of uneven lengths, leaves the chip idle (six chunks
 // of 1-300 queries after 0.5-8 K tokens: 691 us, the longest request's blocks
-// alone at the end).  With U the most cost units a part may hold, the blocks make
+// alone at the end; cut, and with FP8 pages in pairs, 415).  With U the most cost units a part may hold, the blocks make
 // sum ceil(cost / U) parts; the plan tries eight sizes U for one and for two rounds
 // of the chip, estimates a round as U + CUT_COST (a part's own start, its
 // partial results' way through memory and the merge, measured) and takes the

@@ -1,8 +1,8 @@
 // Mixed-format paged decode attention (Sec. 3.3, Eq. softmax-merge; Sec. 4.1
 // direct fused decode) for gfx950.
 //
-// One launch per layer.  Grid (chunk, KV head, request); one workgroup per CU:
-// 8 wave64s with one ring slot each when a KV head's query group has at most
+// One launch per layer.  Grid (chunk, KV head, request); one workgroup per CU (two
+// at d = 128 with at most 8 heads per KV head): 8 wave64s with one ring slot each when a KV head's query group has at most
 // 8 heads (two pages share a score tile), else 8 waves with two slots.  Chunks
 // are ranges of logical pages of equal cost: a page wholly outside the Recent
 // window costs 2 units, a Recent (FP8) page 3 (twice the bytes, and it goes
@@ -52,11 +52,12 @@ namespace mkv {
 // Workgroup shape per instance: with the paired score layout (G <= 8) 8
 // waves, each with a one-stage ring slot (a stage is moved into registers as
 // soon as it lands and the slot refilled at once); otherwise 8 waves with two
-// slots.  One workgroup per CU either way.  Eight one-slot waves beat twelve
+// slots.  Eight one-slot waves beat twelve
 // on the long pair (29.7 against 31.0 us per scan): the stage loop is not
 // issue-bound with two waves per SIMD, and fewer copies in flight per CU let
-// the memory system deliver more (a further L2 prefetch of later stages, or
-// four waves, were slower still).
+// the memory system deliver more (a further L2 prefetch of later stages, four
+// waves, or a second slot per wave -- 32.0 against 30.2 us, and 541 against 498 on
+// 64 long requests -- were slower still).
 #ifndef MKV_PAIR_NW
 #define MKV_PAIR_NW 8
 #define MKV_PAIR_SLOTS 1
