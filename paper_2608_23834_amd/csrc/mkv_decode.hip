@@ -133,9 +133,12 @@ __device__ inline int page_at_cost(int64_t c, int n_old) {
 // us at 16 K tokens).
 constexpr int decode_fill(int d, int group) { return d == 128 && group <= 8 ? 512 : 256; }
 // Units per chunk: about that many workgroups for the whole launch, never below
-// 16 old pages' worth and never spanning more than MAX_CHUNK_PAGES pages.
-static DecodeShape shape_for(int64_t fill, int n_req, int max_pages, int n_kv_heads, int recent) {
+// 16 old pages' worth and never spanning more than MAX_CHUNK_PAGES pages.  (Where the
+// partials come near the library's own scratch, MAX_CHUNK_PAGES sets the units: the
+// fill does not decide which calls fit it.)
+DecodeShape decode_shape(int n_req, int max_pages, int n_kv_heads, int recent, int group, int d) {
   DecodeShape s;
+  const int64_t fill = decode_fill(d, group);
   const int64_t tmax = request_cost(max_pages, old_pages((int64_t)max_pages * PAGE, recent));
   const int64_t pairs = (int64_t)n_req * n_kv_heads;
   int64_t u = (tmax * pairs + fill - 1) / fill;
@@ -156,13 +159,6 @@ static size_t decode_part_bytes(const DecodeShape& s, int n_req, int n_kv_heads,
   return (size_t)n_req * n_kv_heads * s.max_chunks * part_stride(group, d) * sizeof(float);
 }
 static size_t decode_rec_bytes(int n_req) { return ((size_t)(n_req + 1) * 4 + 15) / 16 * 16; }
-
-DecodeShape decode_shape(int n_req, int max_pages, int n_kv_heads, int recent, int group, int d) {
-  const DecodeShape s = shape_for(decode_fill(d, group), n_req, max_pages, n_kv_heads, recent);
-  // a call that fits the library's own scratch with one workgroup per CU keeps fitting
-  if (decode_part_bytes(s, n_req, n_kv_heads, group, d) + decode_rec_bytes(n_req) <= (size_t)MKV_DECODE_SCRATCH_BYTES) return s;
-  return shape_for(256, n_req, max_pages, n_kv_heads, recent);
-}
 
 size_t decode_ws_bytes(int n_req, int max_pages, int n_kv_heads, int group, int d, int recent) {
   const DecodeShape s = decode_shape(n_req, max_pages, n_kv_heads, recent, group, d);
