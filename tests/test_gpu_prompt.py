@@ -110,3 +110,21 @@ def test_encode_special_pages(torch_cuda, d):
     t.check_tables()
     n8, n3 = t.check_pages()
     assert n3 >= 2 * (n // 16 - 1)
+
+
+@pytest.mark.parametrize("d", [128, 256])
+def test_promote_special_pages(torch_cuda, d):
+    """The same pages back to FP8: zero scales, scales without a fast division, saturated
+    and subnormal metadata; every byte as the oracle's."""
+    rng = np.random.default_rng(d + 1)
+    h = 3
+    x = _special_pages(d, h, rng)
+    n = x.shape[0]
+    t = _twin(d, h, [n, n], recent=16, n_layers=2)
+    k = wl.bf16_round(np.concatenate([x, x[::-1]]))
+    v = wl.bf16_round(np.concatenate([x[::-1], x]))
+    t.append([n, n], layer_kv=(np.stack([k, v]), np.stack([v, k])))
+    t.migrate(np.zeros((2, t.max_pages), np.uint8))
+    assert t.promote((t.otags == 2).astype(np.uint8)) >= 2 * (n // 16 - 1)
+    t.check_tables()
+    t.check_pages()
