@@ -75,7 +75,14 @@ __global__ __launch_bounds__(PLAN_NT) void append_plan_kernel(int n_req, int32_t
     __syncthreads();
     return total;
   };
-  int e_r[PLAN_KB], e_p[PLAN_KB], e_id[PLAN_KB];  // request (-1: no entry), page, table entry
+  // request (-1: no entry, and none before a batch is loaded: a call without tokens
+  // loads none), page, table entry
+  int e_r[PLAN_KB], e_p[PLAN_KB], e_id[PLAN_KB];
+#pragma unroll
+  for (int j = 0; j < PLAN_KB; ++j) {
+    e_r[j] = -1;
+    e_p[j] = e_id[j] = 0;
+  }
   // entries e0 + PLAN_KB tid .. of the run; counts the unmapped ones
   auto load_batch = [&](int r0, int e0, int total) {
     const int f0 = e0 + PLAN_KB * tid;

@@ -66,6 +66,26 @@ def test_append_plan_sizes(torch_cuda, n_req, n):
     t.check_pages()
 
 
+@pytest.mark.parametrize("n_req", [257, 1024, 1025])
+def test_append_no_tokens(torch_cuda, n_req):
+    """A call without new tokens, of more requests than a decode-step append takes:
+    the plan lists nothing and nothing changes."""
+    lens = [1 + r % 3 for r in range(n_req)]
+    t = _twin(128, 1, lens)
+    rng = np.random.default_rng(n_req)
+    k = wl.bf16_round(_rows(rng, sum(lens), 1, 128))[None]
+    t.append(lens, layer_kv=(k, k))
+    state = lambda: [x.clone() for x in (t.gpu.fp8, t.gpu.fp8_scales, t.gpu.tq3, t.gpu.ctrl, t.bt, t.tags)]
+    none = np.zeros((1, 0, 1, 128), np.uint16)
+    t.append([0] * n_req, layer_kv=(none, none))  # (the second call meets the first one's empty list)
+    before = state()
+    t.append([0] * n_req, layer_kv=(none, none))
+    assert all(torch_cuda.equal(a, b) for a, b in zip(state(), before))
+    t.check_tables()
+    t.check_pages()
+    t.check_refcounts()
+
+
 def _special_pages(d, h, rng):
     """Blocks of 16 tokens whose codes sit on decision boundaries."""
     blocks = []
