@@ -289,7 +289,12 @@ mkv_status paged_attn_decode_noalloc(mkv_pool* pool, int32_t layer, int32_t n_re
  * [n_q_total][n_q_heads][d]; cu_q: device int32 [n_req+1]; out: device fp32
  * [n_q_total][n_q_heads][d]; ws >= paged_attn_workspace_bytes(..., n_q_total)
  * (it holds the per-format page lists, the work items and the partial
- * outputs of row blocks that are cut along their pages).  q, out and ws must be
+ * outputs of row blocks that are cut along their pages: 2 * max(1, 256 /
+ * n_kv_heads) * n_kv_heads blocks of 512 d + 1024 bytes at most, 68 MB at d =
+ * 256).  The size never falls as n_req, max_pages or n_q_total grow, so a
+ * workspace sized for the largest call serves every smaller one; the call also
+ * runs with the size of any other n_q_total >= 1 (with less room it cuts fewer
+ * blocks, or none).  q, out and ws must be
  * 16-byte aligned (MKV_EINVAL otherwise).  A request whose query range or
  * length is invalid sets the error word and its locatable rows get zeros.
  * Query ranges are expected not to overlap (cu_q nondecreasing); ranges that

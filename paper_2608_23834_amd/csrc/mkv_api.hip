@@ -395,10 +395,9 @@ mkv_status paged_attn_chunk(mkv_pool* pool, int32_t layer, int32_t n_req, const 
   if (layer < 0 || layer >= pool->n_layers) return MKV_ERANGE;
   if (n_req > 65535 || max_pages > 1024 * 256) return MKV_ERANGE;
   if ((int64_t)n_q_total * pool->group > ((int64_t)1 << 31) / 2) return MKV_ERANGE;
-  if (ws_bytes < chunk_ws_bytes(n_req, max_pages, n_q_total, pool->n_kv_heads, pool->group, pool->d))
-    return MKV_ENOMEM;
+  if (ws_bytes < chunk_ws_least(n_req, max_pages)) return MKV_ENOMEM;
   hipError_t e = launch_chunk(view_of(pool), layer, n_req, q, cu_q, n_q_total, block_table, tags,
-                              max_pages, seq_lens, out, ws, stream);
+                              max_pages, seq_lens, out, ws, ws_bytes, stream);
   if (e == hipErrorNotSupported) return MKV_EUNSUP;
   mkv_status st = hip_status(e);
   if (st == MKV_OK) pool->chunk_routes++;

@@ -91,35 +91,50 @@ __host__ __device__ constexpr int64_t chunk_part_floats(int d) { return 128LL * 
 
 // workspace: the two page lists (even rows with room for a masked last page;
 // the kernel copies them in 1 KiB blocks, so 1 KiB of slack follows), the pages'
-// running counts, the row blocks, the work items and the parts of cut blocks
+// running counts, the row blocks, the cut blocks, the work items and the parts of
+// cut blocks.  Only what lies before the items and MAX_ITEMS of them is needed:
+// where the room ends the parts end (fewer blocks are cut, or none) and before them
+// the items (the blocks go in several launches).  So any workspace that a call of
+// these requests and pages was sized for serves every other one.
 struct ChunkWs {
-  size_t list8, list3, cum, rbo, hdr, items, splits, parts, total;
-  int stride;
+  size_t list8, list3, cum, rbo, hdr, splits, items, parts, total;
+  int stride, n_items, n_parts;
 };
-static ChunkWs chunk_ws(int n_req, int max_pages, int n_q_total, int n_kv_heads, int group, int d) {
+static size_t chunk_part_bytes(int n_kv_heads, int d) { return n_kv_heads * (size_t)chunk_part_floats(d) * sizeof(float); }
+static ChunkWs chunk_ws(int n_req, int max_pages, int n_q_total, int n_kv_heads, int group, int d, size_t room) {
   ChunkWs w;
   w.stride = (max_pages + 2) & ~1;
   const size_t lb = al256((size_t)n_req * w.stride * sizeof(int2) + 1024);
-  const bool cut = chunk_may_cut(n_q_total, group, n_kv_heads);
-  const size_t n_items = (size_t)chunk_blocks(n_q_total, group) + n_req + (cut ? MAX_ITEMS : 0);
   w.list8 = 0;
   w.list3 = lb;
   w.cum = 2 * lb;
   w.rbo = 3 * lb;
   w.hdr = w.rbo + al256((size_t)(n_req + 1) * sizeof(int32_t));
-  w.items = w.hdr + 256;
-  w.splits = w.items + al256(n_items * 2 * sizeof(int4));
-  w.parts = w.splits + (cut ? MAX_ITEMS * sizeof(int4) : 0);
-  // a part holds at least one pass: short tables cannot be cut into many
+  w.splits = w.hdr + 256;
+  w.items = w.splits + MAX_ITEMS * sizeof(int4);
+  const int64_t blocks = chunk_blocks(n_q_total, group) + n_req;
+  int64_t n_items = blocks < MAX_ITEMS ? MAX_ITEMS : blocks;
+  const int64_t items_fit = room < w.items ? 0 : (int64_t)((room - w.items) / (2 * sizeof(int4)));
+  if (n_items > items_fit) n_items = items_fit;
+  w.n_items = (int)n_items;
+  w.parts = w.items + al256((size_t)n_items * 2 * sizeof(int4));
+  // a part holds at least one pass: short tables cannot be cut into many.  Blocks
+  // are cut in small calls only, but what a small call can use, a large one reports
   const int64_t passes = (max_pages + 1) / 2 + 1;
-  int64_t n_parts = cut ? 2LL * cu_share(n_kv_heads) : 0;
-  const int64_t most = ((int64_t)chunk_blocks(n_q_total, group) + n_req) * (passes < MAX_PARTS ? passes : MAX_PARTS);
+  int64_t n_parts = 2LL * cu_share(n_kv_heads);
+  const int64_t most = blocks * (passes < MAX_PARTS ? passes : MAX_PARTS);
   if (n_parts > most) n_parts = most;
-  w.total = w.parts + (size_t)n_parts * n_kv_heads * chunk_part_floats(d) * sizeof(float);
+  const int64_t parts_fit = room < w.parts ? 0 : (int64_t)((room - w.parts) / chunk_part_bytes(n_kv_heads, d));
+  if (n_parts > parts_fit) n_parts = parts_fit;
+  w.n_parts = (int)n_parts;
+  w.total = w.parts + (size_t)n_parts * chunk_part_bytes(n_kv_heads, d);
   return w;
 }
 size_t chunk_ws_bytes(int n_req, int max_pages, int n_q_total, int n_kv_heads, int group, int d) {
-  return chunk_ws(n_req, max_pages, n_q_total, n_kv_heads, group, d).total;
+  return chunk_ws(n_req, max_pages, n_q_total, n_kv_heads, group, d, SIZE_MAX / 2).total;
+}
+size_t chunk_ws_least(int n_req, int max_pages) {
+  return chunk_ws(n_req, max_pages, 1, 1, 1, 128, 0).items + MAX_ITEMS * 2 * sizeof(int4);
 }
 
 // Page lists of a chunk call, one workgroup per request: the TQ3 and the FP8
@@ -208,12 +223,14 @@ __global__ __launch_bounds__(LIST_NT) void chunk_lists_kernel(const int32_t* bt,
 // items: two int4 per work item, {request, block of the request, first TQ3 pair,
 // TQ3 pairs}, {first FP8 pair, FP8 pairs, part slot or -1, -}; splits: {request,
 // block of the request, first part slot, parts}.
+// The table holds n_items items from row block b0 on; a call whose blocks do not fit
+// comes in several launches, its blocks whole (cut blocks fit any table).
 constexpr int COST3 = 4, COST8 = 4;
 constexpr int CUT_COST = 12 * COST3, MIN_PART = 4 * COST3;
 __global__ __launch_bounds__(1024) void chunk_plan_kernel(int n_req, const int32_t* cu_q, int n_q_total,
                                                           const int32_t* seq_lens, int max_pages,
-                                                          int group, int grid, int share, int may_cut,
-                                                          int max_slots, int stride, const int2* cum,
+                                                          int group, int grid, int b0, int n_items, int share,
+                                                          int may_cut, int max_slots, int stride, const int2* cum,
                                                           int32_t* rbo, int32_t* hdr, int4* items,
                                                           int4* splits, int32_t* err) {
   __shared__ int scratch[32];
@@ -266,15 +283,16 @@ __global__ __launch_bounds__(1024) void chunk_plan_kernel(int n_req, const int32
     f8 = (c.x + 1) / 2;
   };
   const bool cut = may_cut && nblk <= 2 * share;
-  if (!cut) {
-    for (int b = tid; b < nblk; b += 1024) {
+  if (!cut || b0 > 0) {
+    const int n = max(0, min(nblk - b0, n_items));  // (none after a call's cut blocks)
+    for (int b = tid; b < n; b += 1024) {
       int r, x, t3, f8;
-      locate(b, r, x, t3, f8);
+      locate(b0 + b, r, x, t3, f8);
       items[2 * b] = make_int4(r, x, 0, t3);
       items[2 * b + 1] = make_int4(0, f8, -1, 0);
     }
     if (tid == 0) {
-      hdr[0] = nblk;
+      hdr[0] = n;
       hdr[1] = 0;
     }
     return;
@@ -314,8 +332,8 @@ __global__ __launch_bounds__(1024) void chunk_plan_kernel(int n_req, const int32
     }
   // item and part slots
   const int ns = tid < nblk ? max(1, (cost + U - 1) / U) : 0;
-  int n_items, n_slots, n_split;
-  const int it0 = block_excl_scan(ns, scratch, &n_items);
+  int n_used, n_slots, n_split;
+  const int it0 = block_excl_scan(ns, scratch, &n_used);
   const int sl0 = block_excl_scan(ns > 1 ? ns : 0, scratch, &n_slots);
   const int sp0 = block_excl_scan(ns > 1 ? 1 : 0, scratch, &n_split);
   if (tid < nblk) {
@@ -333,7 +351,7 @@ __global__ __launch_bounds__(1024) void chunk_plan_kernel(int n_req, const int32
     if (ns > 1) splits[sp0] = make_int4(r, x, sl0, ns);
   }
   if (tid == 0) {
-    hdr[0] = n_items;
+    hdr[0] = n_used;
     hdr[1] = n_split;
   }
 }
@@ -1493,7 +1511,7 @@ __global__ __launch_bounds__(64 * NSW) void chunk_merge_kernel(ChunkArgs a, cons
 hipError_t launch_chunk(const PoolView& P, int layer, int n_req, const uint16_t* q,
                         const int32_t* cu_q, int n_q_total, const int32_t* bt, const uint8_t* tags,
                         int max_pages, const int32_t* seq_lens, float* out, void* ws,
-                        hipStream_t s) {
+                        size_t ws_bytes, hipStream_t s) {
   ChunkArgs a;
   a.P = P;
   a.layer = layer;
@@ -1505,7 +1523,7 @@ hipError_t launch_chunk(const PoolView& P, int layer, int n_req, const uint16_t*
   a.seq_lens = seq_lens;
   a.out = out;
   uint8_t* w = reinterpret_cast<uint8_t*>(ws);
-  const ChunkWs wl = chunk_ws(n_req, max_pages, n_q_total, P.n_kv_heads, P.group, P.d);
+  const ChunkWs wl = chunk_ws(n_req, max_pages, n_q_total, P.n_kv_heads, P.group, P.d, ws_bytes);
   int2* list8 = reinterpret_cast<int2*>(w + wl.list8);
   int2* list3 = reinterpret_cast<int2*>(w + wl.list3);
   int2* cum = reinterpret_cast<int2*>(w + wl.cum);
@@ -1524,17 +1542,6 @@ hipError_t launch_chunk(const PoolView& P, int layer, int n_req, const uint16_t*
                      seq_lens, P.n_fp8, P.n_tq3, list8, list3, cum, P.ctrl + CTRL_ERR);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  // row blocks of all requests: at most ceil(n_q_total G / 128) + n_req when
-  // the query ranges do not overlap
-  const int blocks = (int)chunk_blocks(n_q_total, P.group) + n_req;
-  const bool cut = chunk_may_cut(n_q_total, P.group, P.n_kv_heads);
-  const int share = cu_share(P.n_kv_heads);
-  const int max_slots = (int)((wl.total - wl.parts) / (P.n_kv_heads * chunk_part_floats(P.d) * sizeof(float)));
-  hipLaunchKernelGGL(chunk_plan_kernel, dim3(1), dim3(1024), 0, s, n_req, cu_q, n_q_total, seq_lens, max_pages,
-                     P.group, blocks, share, cut ? 1 : 0, max_slots, wl.stride, cum, rbo, hdr, items, splits,
-                     P.ctrl + CTRL_ERR);
-  e = hipGetLastError();
-  if (e != hipSuccess) return e;
   const size_t lds = P.d == 256 ? (size_t)ChunkLds<256>::TOTAL : (size_t)ChunkLds<128>::TOTAL;
   const void* kern = P.d == 256 ? (const void*)chunk_kernel<256> : (const void*)chunk_kernel<128>;
   // the dynamic-LDS limit is raised once per kernel instance and device
@@ -1548,17 +1555,32 @@ hipError_t launch_chunk(const PoolView& P, int layer, int n_req, const uint16_t*
     if (e != hipSuccess) return e;
     if (dev >= 0 && dev < 64) attr_done[dev].fetch_or(bit);
   }
-  const int n_items = cut && blocks < 2 * share ? 2 * share : blocks;
-  dim3 grid(n_items, P.n_kv_heads);
-  void* args[] = {&a};
-  e = hipLaunchKernel(kern, grid, dim3(64 * CW), args, lds, s);
-  if (e != hipSuccess || !cut) return e;
-  const dim3 mgrid(blocks < share ? blocks : share, P.n_kv_heads, NSW);
-  if (P.d == 256)
-    hipLaunchKernelGGL(chunk_merge_kernel<256>, mgrid, dim3(64 * NSW), 0, s, a, splits);
-  else
-    hipLaunchKernelGGL(chunk_merge_kernel<128>, mgrid, dim3(64 * NSW), 0, s, a, splits);
-  return hipGetLastError();
+  // row blocks of all requests: at most ceil(n_q_total G / 128) + n_req when
+  // the query ranges do not overlap
+  const int blocks = (int)chunk_blocks(n_q_total, P.group) + n_req;
+  const int share = cu_share(P.n_kv_heads);
+  const bool cut = wl.n_parts > 0 && chunk_may_cut(n_q_total, P.group, P.n_kv_heads);
+  for (int b0 = 0; b0 < blocks; b0 += wl.n_items) {  // one turn where the workspace holds the call's items
+    hipLaunchKernelGGL(chunk_plan_kernel, dim3(1), dim3(1024), 0, s, n_req, cu_q, n_q_total, seq_lens, max_pages,
+                       P.group, blocks, b0, wl.n_items, share, cut ? 1 : 0, wl.n_parts, wl.stride, cum, rbo, hdr,
+                       items, splits, P.ctrl + CTRL_ERR);
+    e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    int n = blocks - b0 < wl.n_items ? blocks - b0 : wl.n_items;
+    if (cut && b0 == 0 && n < 2 * share) n = 2 * share;
+    void* args[] = {&a};
+    e = hipLaunchKernel(kern, dim3(n, P.n_kv_heads), dim3(64 * CW), args, lds, s);
+    if (e != hipSuccess) return e;
+    if (!cut || b0 > 0) continue;
+    const dim3 mgrid(blocks < share ? blocks : share, P.n_kv_heads, NSW);
+    if (P.d == 256)
+      hipLaunchKernelGGL(chunk_merge_kernel<256>, mgrid, dim3(64 * NSW), 0, s, a, splits);
+    else
+      hipLaunchKernelGGL(chunk_merge_kernel<128>, mgrid, dim3(64 * NSW), 0, s, a, splits);
+    e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
 }
 
 }  // namespace mkv

@@ -126,9 +126,10 @@ hipError_t launch_stream_read(const void* buf, size_t bytes, uint32_t* sink, int
 
 // mkv_chunk.hip
 size_t chunk_ws_bytes(int n_req, int max_pages, int n_q_total, int n_kv_heads, int group, int d);
+size_t chunk_ws_least(int n_req, int max_pages);  // the smallest workspace a call runs with
 hipError_t launch_chunk(const PoolView& P, int layer, int n_req, const uint16_t* q,
                         const int32_t* cu_q, int n_q_total, const int32_t* bt,
                         const uint8_t* tags, int max_pages, const int32_t* seq_lens, float* out,
-                        void* ws, hipStream_t s);
+                        void* ws, size_t ws_bytes, hipStream_t s);
 
 }  // namespace mkv

@@ -229,9 +229,9 @@ class Twin:
     def advance(self, n=1):
         self.cur = [c + n for c in self.cur]
 
-    def chunk(self, n_q, layer=0, sample_stride=1):
+    def chunk(self, n_q, layer=0, sample_stride=1, ws=None):
         """Chunk attention for the last n_q[r] tokens of each request (already
-        appended).  The oracle computes every sample_stride-th query of each
+        appended), on a workspace for this call unless one is given.  The oracle computes every sample_stride-th query of each
         request and its last one; the other rows of ref_out stay NaN."""
         import paper_2608_23834_amd as mk
         torch = _torch()
@@ -243,7 +243,7 @@ class Twin:
         cu = np.r_[0, np.cumsum(n_q)].astype(np.int32)
         sl = np.array(self.cur, np.int32)
         out = torch.full((q.shape[0], w.n_q_heads, w.head_dim), float("nan"), device="cuda")
-        ws = mk.workspace(self.gpu, self.n_req, self.max_pages, q.shape[0])
+        ws = mk.workspace(self.gpu, self.n_req, self.max_pages, q.shape[0]) if ws is None else ws
         mk.paged_attn_chunk(self.gpu, layer, torch.from_numpy(q.view(np.int16)).cuda(),
                             torch.from_numpy(cu).cuda(), self.bt, self.tags,
                             torch.from_numpy(sl).cuda(), out, ws)

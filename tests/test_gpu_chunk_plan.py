@@ -34,12 +34,15 @@ def _bound(w, t, res):
     return 2.0 ** -15 * norm(res["q"]) * k / np.sqrt(w.head_dim) * 2 * v
 
 
-def _run(d, hq, hkv, ctx, nq, recent, stride=1, migrate_after=False, tol=lambda *a: TOL):
-    import paper_2608_23834_amd as mk
-    lens = [c + q for c, q in zip(ctx, nq)]
+def _twin(d, hq, hkv, lens, recent):
     w = dataclasses.replace(wl.workload(2), n_q_heads=hq, n_kv_heads=hkv, head_dim=d, ctx=tuple(lens),
                             n_req=len(lens), n_layers=1, recent=recent)
-    t = Twin(w, lens=lens, recent=recent)
+    return w, Twin(w, lens=lens, recent=recent)
+
+
+def _run(d, hq, hkv, ctx, nq, recent, stride=1, migrate_after=False, tol=lambda *a: TOL):
+    import paper_2608_23834_amd as mk
+    w, t = _twin(d, hq, hkv, [c + q for c, q in zip(ctx, nq)], recent)
     t.fill_to(ctx)
     t.migrate(np.zeros((t.n_req, t.max_pages), np.uint8))
     t.append(nq)
@@ -78,3 +81,69 @@ def test_chunk_many_requests(torch_cuda):
     # to the bound of the score product instead of the long contexts' tolerance
     n = 1030
     _run(128, 2, 1, [(7 * r) % 40 for r in range(n)], [1 + r % 3 for r in range(n)], 16, tol=_bound)
+
+
+def test_chunk_workspace_sizes(torch_cuda):
+    """A workspace sized for more queries, requests or pages is never the smaller one."""
+    import paper_2608_23834_amd as mk
+    for d, hq, hkv in ((256, 24, 4), (128, 32, 8), (128, 16, 1)):
+        _, t = _twin(d, hq, hkv, [16], 16)
+        size = lambda r, p, q: mk.paged_attn_workspace_bytes(t.gpu, r, p, q)
+        qs = [1, 2, 7, 64, 127, 128, 500, 2047, 2048, 2049, 2730, 2731, 4096, 8192, 65536, 1 << 20]
+        for r in (1, 3, 64, 1030):
+            for p in (1, 2, 40, 63, 4096):
+                now = [size(r, p, q) for q in qs]
+                assert all(a <= b for a, b in zip(now, now[1:]))
+                assert all(size(r, p, q) <= min(size(r + 1, p, q), size(r, p + 1, q)) for q in qs[::3])
+
+
+@pytest.mark.parametrize("nq", [[2100, 40], [900, 7, 1300, 1]])
+def test_chunk_workspace_serves_smaller_calls(torch_cuda, nq):
+    """One workspace, sized for the first chunk of a prompt (too many blocks to be cut), for
+    the chunks after it as well."""
+    import paper_2608_23834_amd as mk
+    _, t = _twin(128, 32, 8, [sum(nq)], 256)
+    ws = mk.workspace(t.gpu, 1, t.max_pages, max(nq))
+    for n in nq:
+        t.append([n])
+        t.migrate(np.zeros((1, t.max_pages), np.uint8))
+        res = t.chunk([n], sample_stride=max(1, n // 40), ws=ws)
+        ok = np.isfinite(res["ref_out"])
+        err = float(np.max(np.abs(res["out"][ok] - res["ref_out"][ok])))
+        print(f"chunk of {n}: max abs error {err:.2e}", flush=True)
+        assert np.isfinite(res["out"]).all() and err <= TOL
+    assert mk.kv_pool_check_errors(t.gpu) == 0
+
+
+def test_chunk_least_workspace(torch_cuda):
+    """The smallest workspace that is taken (it does not depend on the queries): blocks
+    left whole, and more of them than it holds work items for."""
+    import paper_2608_23834_amd as mk
+    ctx, nq = [300, 0, 40], [4200, 70, 5]
+    _, t = _twin(128, 16, 1, [c + q for c, q in zip(ctx, nq)], 64)
+    t.fill_to([c + q for c, q in zip(ctx, nq)])
+    t.migrate(np.zeros((t.n_req, t.max_pages), np.uint8))
+    full = t.chunk(nq, sample_stride=301)
+    lo, hi = 0, mk.paged_attn_workspace_bytes(t.gpu, t.n_req, t.max_pages, 1)
+    one = torch_cuda.zeros((3, 16, 128), dtype=torch_cuda.int16, device="cuda")
+    out = torch_cuda.zeros((3, 16, 128), device="cuda")
+    cu = torch_cuda.tensor([0, 1, 2, 3], dtype=torch_cuda.int32, device="cuda")
+    sl = torch_cuda.tensor(t.cur, dtype=torch_cuda.int32, device="cuda")
+    big = torch_cuda.zeros(hi, dtype=torch_cuda.uint8, device="cuda")
+    while hi - lo > 1:  # (a size that is too small is refused on the host)
+        mid = (lo + hi) // 2
+        try:
+            mk.paged_attn_chunk(t.gpu, 0, one, cu, t.bt, t.tags, sl, out, big[:mid])
+            hi = mid
+        except mk.MkvError as e:
+            assert e.code == 3
+            lo = mid
+    assert hi < 3 * 8 * 3 * (t.max_pages + 2) + 3 * 1280 + 3 * 256 + 512 * 48 + 256
+    small = t.chunk(nq, sample_stride=301, ws=big[:hi])
+    err = float(np.max(np.abs(full["out"] - small["out"])))
+    print(f"least workspace {hi} bytes, max abs difference {err:.2e}", flush=True)
+    assert np.isfinite(small["out"]).all()
+    assert err == 0  # (with room for parts so many blocks are left whole as well)
+    ok = np.isfinite(small["ref_out"])
+    assert float(np.max(np.abs(small["out"][ok] - small["ref_out"][ok]))) <= TOL
+    assert mk.kv_pool_check_errors(t.gpu) == 0
