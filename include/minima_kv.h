@@ -211,7 +211,8 @@ mkv_status kv_pool_read_refcounts(mkv_pool* pool, int32_t* rc_fp8, int32_t* rc_t
 /* Workspace bytes for paged_attn_decode and paged_attn_decode_append
  * (n_q_total = 0; the split partials, then n_req + 1 words the fused append
  * leaves for its merge kernel to publish) or paged_attn_chunk (n_q_total =
- * total chunk queries) at this batch shape. */
+ * total chunk queries) at this batch shape and every smaller one: the size never
+ * falls as n_req, max_pages or n_q_total >= 1 grow. */
 mkv_status paged_attn_workspace_bytes(const mkv_pool* pool, int32_t n_req, int32_t max_pages,
                                       int32_t n_q_total, size_t* bytes);
 

@@ -224,7 +224,7 @@ mkv_status paged_attn_workspace_bytes(const mkv_pool* pool, int32_t n_req, int32
                                       int32_t n_q_total, size_t* bytes) {
   if (!pool || !bytes || n_req < 1 || max_pages < 1 || n_q_total < 0) return MKV_EINVAL;
   if (n_q_total == 0)
-    *bytes = decode_ws_bytes(n_req, max_pages, pool->n_kv_heads, pool->group, pool->d, pool->recent);
+    *bytes = decode_ws_report(n_req, max_pages, pool->n_kv_heads, pool->group, pool->d, pool->recent);
   else
     *bytes = chunk_ws_bytes(n_req, max_pages, n_q_total, pool->n_kv_heads, pool->group, pool->d);
   return MKV_OK;

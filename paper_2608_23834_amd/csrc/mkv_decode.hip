@@ -154,15 +154,32 @@ DecodeShape decode_shape(int n_req, int max_pages, int n_kv_heads, int recent, i
 // past the request's end), so the merge needs no count
 __host__ __device__ constexpr int part_stride(int G, int D) { return (G * (D + 2) + 3) / 4 * 4; }
 
-// bytes of the split partials; the fused append's per-request records follow
-static size_t decode_part_bytes(const DecodeShape& s, int n_req, int n_kv_heads, int group, int d) {
-  return (size_t)n_req * n_kv_heads * s.max_chunks * part_stride(group, d) * sizeof(float);
+// bytes of `slots` split partials; the fused append's per-request records follow
+static size_t decode_part_bytes(int64_t slots, int group, int d) {
+  return (size_t)slots * part_stride(group, d) * sizeof(float);
 }
 static size_t decode_rec_bytes(int n_req) { return ((size_t)(n_req + 1) * 4 + 15) / 16 * 16; }
 
+// what a call needs
 size_t decode_ws_bytes(int n_req, int max_pages, int n_kv_heads, int group, int d, int recent) {
   const DecodeShape s = decode_shape(n_req, max_pages, n_kv_heads, recent, group, d);
-  return decode_part_bytes(s, n_req, n_kv_heads, group, d) + decode_rec_bytes(n_req);
+  return decode_part_bytes((int64_t)n_req * n_kv_heads * s.max_chunks, group, d) + decode_rec_bytes(n_req);
+}
+// what a program is told to hold: the slots of every call of at most these requests and
+// pages.  A smaller call can need more slots than a larger one, as its units round up
+// to a chunk more per pair (161 pages, 8 KV heads, d = 128: 520 for 13 requests, 576 for
+// 12).  They are at most pairs * ceil(cost / 32), and where the fill sets the units at most
+// fill + pairs - 1 (one per pair from fill pairs on), unless MAX_CHUNK_PAGES sets them.
+size_t decode_ws_report(int n_req, int max_pages, int n_kv_heads, int group, int d, int recent) {
+  const int64_t fill = decode_fill(d, group), pairs = (int64_t)n_req * n_kv_heads;
+  const int64_t tmax = request_cost(max_pages, old_pages((int64_t)max_pages * PAGE, recent));
+  const int64_t umin = 16 * COST_OLD, umax = (int64_t)(MAX_CHUNK_PAGES - 1) * COST_MIN;
+  const int64_t most = pairs * ((tmax + umin - 1) / umin);
+  const int64_t wide = pairs * ((tmax + umax - 1) / umax);
+  int64_t slots = (pairs < fill ? pairs : fill - 1) + fill - 1;
+  if (slots < wide) slots = wide;
+  if (slots > most) slots = most;
+  return decode_part_bytes(slots, group, d) + decode_rec_bytes(n_req);
 }
 
 template <int D>
@@ -1257,7 +1274,7 @@ hipError_t launch_decode(const PoolView& P, int layer, int n_req, const uint16_t
   a.tags_w = tags_w;
   a.page_mass = page_mass;
   a.app_rec = app ? reinterpret_cast<int32_t*>(reinterpret_cast<uint8_t*>(ws) +
-                                              decode_part_bytes(sh, n_req, P.n_kv_heads, P.group, P.d))
+                                              decode_part_bytes((int64_t)n_req * P.n_kv_heads * sh.max_chunks, P.group, P.d))
                   : nullptr;
   // dynamic LDS: three query operands, then the page ring (reused by the wave merge)
   const bool pair = P.group <= 8;

@@ -95,6 +95,7 @@ struct DecodeShape {
 };
 DecodeShape decode_shape(int n_req, int max_pages, int n_kv_heads, int recent, int group, int d);
 size_t decode_ws_bytes(int n_req, int max_pages, int n_kv_heads, int group, int d, int recent);
+size_t decode_ws_report(int n_req, int max_pages, int n_kv_heads, int group, int d, int recent);
 // the fixed device scratch of paged_attn_decode_noalloc: resolve its address on
 // device dev (dev must be current; once per device), and look it up
 hipError_t decode_scratch_init(int dev);

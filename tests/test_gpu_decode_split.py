@@ -1,4 +1,4 @@
-"""Decode merge at the edges of its shapes: as many chunk slots as one round of one
+"""Decode workspaces and the decode merge at the edges of its shapes: as many chunk slots as one round of one
 wave, of two, four and eight waves takes, one more, a second round of eight waves;
 every slot filled, and most of them past the request's end.  Against the oracle with
 the tolerance of the other decode tests."""
@@ -40,4 +40,45 @@ def test_merge_slots(d, slots):
     r = tw.decode_append()
     err = max(max_abs(r["out"], r["ref_out"]), max_abs(r["lse"], r["ref_lse"]))
     assert np.all(np.isfinite(r["out"])) and err <= TOL
+    assert mk.kv_pool_check_errors(tw.gpu) == 0
+
+
+def _pool(d, hq, hkv, recent):
+    import paper_2608_23834_amd as mk
+    return mk.Pool(1, hq, hkv, d, 1, 1, recent, np.ones(d, np.int8))
+
+
+@pytest.mark.parametrize("d,hq,hkv", [(256, 24, 4), (128, 32, 8), (128, 8, 1), (128, 16, 1), (256, 16, 2)])
+def test_workspace_sizes(d, hq, hkv):
+    """A workspace sized for more requests or pages is never the smaller one."""
+    import paper_2608_23834_amd as mk
+    for recent in (16, 1024, 1 << 20):
+        p = _pool(d, hq, hkv, recent)
+        size = np.array([[mk.paged_attn_workspace_bytes(p, r, m) for m in (1, 2, 15, 48, 161, 231, 1986, 4096, 65536)]
+                         for r in (1, 2, 7, 8, 12, 13, 27, 31, 32, 33, 36, 40, 63, 64, 65, 127, 128, 300, 5000)])
+        assert (np.diff(size, axis=0) >= 0).all() and (np.diff(size, axis=1) >= 0).all()
+
+
+@pytest.mark.parametrize("d,hq,hkv,more,n,max_pages", [(128, 32, 8, 13, 12, 161), (128, 32, 8, 64, 63, 60),
+                                                       (256, 24, 4, 8, 7, 1986), (128, 8, 1, 300, 299, 40)])
+def test_workspace_serves_fewer_requests(d, hq, hkv, more, n, max_pages):
+    """A decode of n requests on the workspace of `more` (the smaller call needs more
+    slots), with the tables as wide as the workspace was sized for."""
+    import paper_2608_23834_amd as mk
+    import torch
+    lens = [16 * max_pages - 5] + [37 + 11 * (r % 9) for r in range(n - 1)]
+    w = dataclasses.replace(wl.scaled(wl.workload(1 if d == 128 else 5), tuple(lens), n_layers=1, name=f"ws-{n}-{max_pages}"),
+                            n_q_heads=hq, n_kv_heads=hkv)
+    tw = Twin(w, lens=lens, recent=1024)
+    assert tw.max_pages == max_pages
+    tw.fill_to(lens)
+    tw.migrate()
+    ws = mk.workspace(tw.gpu, more, max_pages)
+    guard = torch.full((ws.numel() + 4096,), 0xA5, dtype=torch.uint8, device="cuda")
+    tw._ws = lambda ws_fill: guard[:ws.numel()]
+    r = tw.decode()
+    err = max(max_abs(r["out"], r["ref_out"]), max_abs(r["lse"], r["ref_lse"]))
+    print(f"d {d}: {n} requests on the workspace of {more}: {err:.2e}", flush=True)
+    assert np.all(np.isfinite(r["out"])) and err <= TOL
+    assert bool((guard[ws.numel():] == 0xA5).all())
     assert mk.kv_pool_check_errors(tw.gpu) == 0
