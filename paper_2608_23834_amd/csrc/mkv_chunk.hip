@@ -34,8 +34,9 @@
 // Pass p (one barrier): the score waves issue pair p's product and finish
 // pair p - 1 while the PV waves take pair p - 2.  FP8 pairs: the score waves
 // score them on the f16 MFMA against the plain query (the fp8 MFMA keeps too
-// few bits where FP8 keys carry large norms) and fold the pages' V scales into
-// the weights; the PV waves read the pages' values from the ring.  The
+// few bits where FP8 keys carry large norms) and fold the pages' V scales, less
+// their powers of two, into the weights; the PV waves read the pages' values from
+// the ring and scale them by those.  The
 // workgroups of one (request, KV head) read the same pages at about the same
 // time, so the page bytes come from L2 after the first reader.
 #include <hip/hip_runtime.h>
@@ -377,6 +378,18 @@ __device__ __forceinline__ void split2(float a, float b, float neg1, uint32_t& h
 __device__ __forceinline__ half8 h8u(uint32_t a, uint32_t b, uint32_t c, uint32_t d) {
   typedef uint32_t u4v __attribute__((ext_vector_type(4)));
   return __builtin_bit_cast(half8, u4v{a, b, c, d});
+}
+// Power of two of an FP8 page's V scale: the PV waves give it to the values'
+// conversion (exact: E4M3 values times 2^-15 .. 2^7 are fp16 numbers) and the score
+// waves fold what is left of the scale, 1 to 2, into the weights.  With the whole scale
+// folded in, the weights' low halves fell among the fp16 subnormals, whose last bit is
+// 2^-24 whatever the weight: 150 rows over 850 FP8 tokens (d = 128) were 6.5e-6 (2-norm)
+// off their 64-bit value, and 1.2e-3 with values 2^-8 of that size; now 4.4e-6 for both.
+__device__ __forceinline__ float vscale_pow2(float s) {
+  return fminf(fmaxf(__uint_as_float(__float_as_uint(s) & 0x7F800000u), 0x1p-15f), 0x1p7f);
+}
+__device__ __forceinline__ float vscale_rest(float s) {  // s over its power of two, exactly
+  return s * __int_as_float(0x7F000000 - __float_as_int(vscale_pow2(s)));
 }
 constexpr float CM_INIT = -1.0e30f;  // running max before the first score (finite: no inf - inf)
 
@@ -784,14 +797,14 @@ __device__ __forceinline__ void chunk_block(const ChunkArgs& a, int4 it0, int4 i
       lo = h8u(ll4[0], ll4[1], ll4[2], ll4[3]);
     };
     // hand the weights of stage j (and the rescale the PV accumulators owe
-    // before them) to the PV wave of this pair
-    auto put_weights = [&](int j, const TqW& w, float alpha) {
+    // before them; a TQ3 pair's zero term) to the PV waves
+    auto put_weights = [&](int j, const TqW& w, float alpha, auto zero) {
       uint8_t* ws = wslot(j);
       *reinterpret_cast<half8*>(ws + 0 * 1024 + 16 * lane) = w.ha;
       *reinterpret_cast<half8*>(ws + 1 * 1024 + 16 * lane) = w.la;
       *reinterpret_cast<half8*>(ws + 2 * 1024 + 16 * lane) = w.hb;
       *reinterpret_cast<half8*>(ws + 3 * 1024 + 16 * lane) = w.lb;
-      *reinterpret_cast<half8*>(ws + 4 * 1024 + 16 * lane) = w.z;
+      if constexpr (decltype(zero)::value) *reinterpret_cast<half8*>(ws + 4 * 1024 + 16 * lane) = w.z;
       reinterpret_cast<float*>(ws + LY::WF_ALPHA)[lane] = alpha;
     };
 
@@ -1008,7 +1021,7 @@ __device__ __forceinline__ void chunk_block(const ChunkArgs& a, int4 it0, int4 i
         split2(ra_, rb_, neg1, zh, zl);
         w.z = h8u(zh, zl, 0u, 0u);  // (R_a, R_b) hi, then lo
       }
-      put_weights(p - 1, w, alpha);
+      put_weights(p - 1, w, alpha, std::true_type{});
       __builtin_amdgcn_sched_barrier(0);
       // then this wave's share of the unpacking: keys of pair p + 1 or
       // values of pair p - 1, and the values' side data of pair p - 1
@@ -1074,7 +1087,9 @@ __device__ __forceinline__ void chunk_block(const ChunkArgs& a, int4 it0, int4 i
           for (int j = 0; j < 8; ++j) qop[s][j] = (_Float16)bf16_to_f32(hb[j]);
         }
       }
-      // key and value scales of the pages of FP8 stage p - 1
+      // key and value scales of the pages of FP8 stage p - 1, of the value scales the rest
+      // already where it is found under a pass's last products (d = 128 has none left there)
+      constexpr bool REST_EARLY = NKS > 10;
       float2 ksa_prev = make_float2(0.0f, 0.0f), ksb_prev = ksa_prev;
       Place pl8 = first8;  // of the next pair's page a
       for (int p = st3; p <= n_st; ++p) {
@@ -1097,7 +1112,13 @@ __device__ __forceinline__ void chunk_block(const ChunkArgs& a, int4 it0, int4 i
 #pragma unroll
         for (int w = 0; w < NKS / 2; ++w)
           kw[w] = *reinterpret_cast<const uint4*>(pk + 1024 * (w / 4) + (sw ^ (16 * (w % 4))));
-        const float2 ksa = *reinterpret_cast<const float2*>(ra + R8), ksb = *reinterpret_cast<const float2*>(rb_ + R8);
+        float2 ksa = *reinterpret_cast<const float2*>(ra + R8), ksb = *reinterpret_cast<const float2*>(rb_ + R8);
+        auto rest_early = [&]() {
+          if constexpr (REST_EARLY) {
+            ksa.y = vscale_rest(ksa.y);
+            ksb.y = vscale_rest(ksb.y);
+          }
+        };
         auto mf = [&](int s) {
           if (s < NKS) {
             const uint32_t k0 = s & 1 ? kw[s / 2].z : kw[s / 2].x, k1 = s & 1 ? kw[s / 2].w : kw[s / 2].y;
@@ -1109,6 +1130,7 @@ __device__ __forceinline__ void chunk_block(const ChunkArgs& a, int4 it0, int4 i
         if (p == st3) {
 #pragma unroll
           for (int s = 0; s < NKS; ++s) mf(s);
+          rest_early();
           if (p > 0) {  // the last TQ3 pair
             TqW w;
             float alpha;
@@ -1120,7 +1142,7 @@ __device__ __forceinline__ void chunk_block(const ChunkArgs& a, int4 it0, int4 i
               tq3_scores(rs_prev, st_prev, e_prev, w, alpha, std::true_type{});
             if (wid >= 2) unpack_v(rs_prev, vb_prev);
             unpack_side(rs_prev, vb_prev);
-            put_weights(p - 1, w, alpha);
+            put_weights(p - 1, w, alpha, std::true_type{});
           }
         } else {
           TqW w;
@@ -1138,11 +1160,12 @@ __device__ __forceinline__ void chunk_block(const ChunkArgs& a, int4 it0, int4 i
               lsum += sc[k];
             }
           };
-          // weights of page a (k0 = 0) or b (k0 = 8), the page's V scale folded in
+          // weights of page a (k0 = 0) or b (k0 = 8), the rest of the page's V scale folded in
           auto split = [&](int k0, float vs, half8& hi, half8& lo) {
+            const float vr = REST_EARLY ? vs : vscale_rest(vs);
             float pw[8];
 #pragma unroll
-            for (int k = 0; k < 8; ++k) pw[k] = sc[k0 + k] * vs;
+            for (int k = 0; k < 8; ++k) pw[k] = sc[k0 + k] * vr;
             split8(pw, hi, lo);
           };
           mf(0);
@@ -1175,8 +1198,8 @@ __device__ __forceinline__ void chunk_block(const ChunkArgs& a, int4 it0, int4 i
           mf(8);
           split(8, ksb_prev.y, w.hb, w.lb);
           mf(9);
-          w.z = w.la;
-          put_weights(p - 1, w, alpha);
+          put_weights(p - 1, w, alpha, std::false_type{});
+          rest_early();
 #pragma unroll
           for (int s = 10; s < NKS; ++s) mf(s);
         }
@@ -1229,7 +1252,7 @@ __device__ __forceinline__ void chunk_block(const ChunkArgs& a, int4 it0, int4 i
           for (int g = 0; g < NSW; ++g) acc[b][g] *= al[g];  // column = this lane's row
       }
     };
-    constexpr int REFILL_AT = 1;
+    constexpr int REFILL_AT = 1, VP_AT = 5;
     // O^T += V^T P^T for the TQ3 pair of stage j (values unpacked in vb),
     // with exact V operands: v = zero + scale * code is split as scale_hi *
     // code + scale_lo * code + zero.  The products that reach fp32 accuracy:
@@ -1323,12 +1346,23 @@ __device__ __forceinline__ void chunk_block(const ChunkArgs& a, int4 it0, int4 i
         __builtin_amdgcn_sched_barrier(0);
       }
     };
-    // O^T += V^T P^T for the FP8 pair of stage j (weights hi + lo, the pages' V
-    // scales already folded in): lane-chunks (rrow, lg) and (rrow, lg + 2) of V,
-    // dword m = tokens 4 g' .. 4 g' + 3 of channel CL rrow + m
+    // O^T += V^T P^T for the FP8 pair of stage j (weights hi + lo, the rest of the pages'
+    // V scales folded in, their powers of two in the values): lane-chunks (rrow, lg) and
+    // (rrow, lg + 2) of V, dword m = tokens 4 g' .. 4 g' + 3 of channel CL rrow + m
     Place pl8 = first8;  // of the next FP8 pair's page a
+    // powers of two of the V scales of the pair at pl8, found a pass early (it has landed
+    // by then) but for the first pair's
+    float vp[2], vp_next[2];
+    auto ld_vp = [&](Place c) {
+      vp_next[0] = vscale_pow2(*reinterpret_cast<const float*>(smem + c.so + R8 + 4));
+      next8(c);
+      vp_next[1] = vscale_pow2(*reinterpret_cast<const float*>(smem + c.so + R8 + 4));
+    };
     auto fp8_pv = [&](int j) {
       const int rrow = li & 15, hh = li >> 4;
+      if (j == st3) ld_vp(pl8);
+      vp[0] = vp_next[0];
+      vp[1] = vp_next[1];
       uint32_t vw[2][NBW][2];
 #pragma unroll
       for (int p = 0; p < 2; ++p) {
@@ -1351,7 +1385,9 @@ __device__ __forceinline__ void chunk_block(const ChunkArgs& a, int4 it0, int4 i
       ld_w2(j, 1, w[1]);
       rescale(j);
       auto op_of = [&](int p, int b) {
-        return h8(cvt_lo(vw[p][b][0]), cvt_hi(vw[p][b][0]), cvt_lo(vw[p][b][1]), cvt_hi(vw[p][b][1]));
+        auto cvt = [&](uint32_t x, auto hi) { return __builtin_amdgcn_cvt_scalef32_pk_f16_fp8(x, vp[p], decltype(hi)::value); };
+        return h8(cvt(vw[p][b][0], std::false_type{}), cvt(vw[p][b][0], std::true_type{}),
+                  cvt(vw[p][b][1], std::false_type{}), cvt(vw[p][b][1], std::true_type{}));
       };
       half8 A[2][NBW];
 #pragma unroll
@@ -1369,6 +1405,7 @@ __device__ __forceinline__ void chunk_block(const ChunkArgs& a, int4 it0, int4 i
             if (t == 0 && k == 0) A[1][b] = op_of(1, b);
             __builtin_amdgcn_sched_barrier(0);
           }
+        if (t == VP_AT) ld_vp(pl8);  // (past the last pair: some slot's bytes, not used)
         if constexpr (COPY_PV)
           if (t == REFILL_AT) refill(j + 2);
       }

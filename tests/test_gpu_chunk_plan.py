@@ -76,6 +76,36 @@ def test_chunk_tq3_past_early_rows(torch_cuda, d):
     _run(d, 12, 2, [96, 500], [220, 130], 16, migrate_after=True)
 
 
+@pytest.mark.parametrize("d", [128, 256])
+def test_chunk_fp8_value_scales(torch_cuda, d):
+    """FP8 pages only, values of every size.  Values times a power of two (scales of 2^-15 to
+    2^7 here) give the rows times it, up to what the products make of the same operands: a
+    weight keeps 22 bits and the values' conversion is exact, whatever the scale.  2^-20 of
+    the rows' 2-norm is two units of a weight's last bit."""
+    import paper_2608_23834_amd as mk
+    ctx, nq = [700, 33], [150, 40]
+    rows = {}
+    for power in (0, -8, -5, 4, 11):
+        w, t = _twin(d, 8, 2, [c + q for c, q in zip(ctx, nq)], 1 << 20)
+        for counts in (ctx, nq):
+            k, v = zip(*(wl.kv_layer(w, 0, n, token_offset=r * 1_000_000 + t.cur[r]) for r, n in enumerate(counts)))
+            v = wl.bf16_round(wl.bf16_to_f32(np.concatenate(v)) * np.float32(2.0 ** power))
+            t.append(counts, layer_kv=(np.concatenate(k)[None], v[None]))
+        assert (t.otags != 2).all()
+        scales = t.gpu.fp8_scales_view()[0, :, :, 1]
+        scales = scales[scales > 0]
+        assert float(scales.min()) >= 2.0 ** -15 and float(scales.max()) < 2.0 ** 8
+        res = t.chunk(nq)
+        rows[power] = res["out"] * np.float32(2.0 ** -power)
+        ref = res["ref_out"] * 2.0 ** -power
+        err, moved = (float(np.linalg.norm(rows[power] - x) / np.linalg.norm(ref)) for x in (ref, rows[0]))
+        print(f"chunk d{d}, values times 2^{power}: relative error {err:.2e}, off the unscaled rows by "
+              f"{moved:.2e}", flush=True)
+        assert float(np.max(np.abs(rows[power] - ref))) <= TOL
+        assert moved <= 2.0 ** -20
+        assert mk.kv_pool_check_errors(t.gpu) == 0
+
+
 def test_chunk_many_requests(torch_cuda):
     # 4,000 rows over at most 42 tokens, many of them nearly one token's value: held
     # to the bound of the score product instead of the long contexts' tolerance
