@@ -1064,6 +1064,12 @@ __device__ __forceinline__ void enc_values(const uint8_t* f8, float sV, uint8_t*
       emin = fminf(emin, e[t]);
       emax = fmaxf(emax, e[t]);
     }
+    // (a page that holds an infinity has an infinite scale: a token whose code is zero is
+    // then no number and counts for neither bound)
+    if (sV == INFINITY) {
+      emin = emin == 0.0f ? 1.0f : emin;
+      emax = emax == 0.0f ? -1.0f : emax;
+    }
     const double lo = (double)sV * (double)emin, hi = (double)sV * (double)emax;  // exact; sV >= 0
     const uint16_t z16 = f64_to_f16_rne_sat(lo);
     const uint16_t s16 = f64_to_f16_rne_sat((hi - lo) / 7.0);

@@ -133,6 +133,31 @@ def test_encode_special_pages(torch_cuda, d):
 
 
 @pytest.mark.parametrize("d", [128, 256])
+def test_encode_infinite_values(torch_cuda, d):
+    """A page with an infinite value has an infinite V scale; its other values are zero
+    codes, no numbers, and count for neither bound of their channel.  Their metadata stays
+    finite: zero 65504 and scale -65504 (the bounds that saw nothing), codes 0; a channel
+    that holds an infinity has zero -65504."""
+    t = _twin(d, 1, [32], recent=16, with_oracle=False)
+    rng = np.random.default_rng(d)
+    x = _rows(rng, 32, 1, d)
+    for ch in (5, d - 1):
+        x[3, 0, ch] = np.inf
+    k, v = wl.bf16_round(_rows(rng, 32, 1, d))[None], wl.bf16_round(x)[None]
+    t.append([32], layer_kv=(k, v))
+    t.migrate(np.zeros((1, 2), np.uint8))
+    page = int(t.bt[0, 0])
+    assert int(t.tags[0, 0]) == 2
+    reg = t.gpu.tq3_view()[0, page, 0].cpu().numpy()
+    scale, zero = (reg[a: a + 2 * d].view(np.float16) for a in (12 * d + 32, 14 * d + 32))
+    inf = np.zeros(d, bool)
+    inf[[5, d - 1]] = True
+    assert (zero[~inf] == 65504).all() and (scale[~inf] == -65504).all()
+    assert (zero[inf] == -65504).all() and np.isnan(scale[inf]).all()
+    assert (reg[6 * d: 12 * d] == 0).all()
+
+
+@pytest.mark.parametrize("d", [128, 256])
 def test_promote_special_pages(torch_cuda, d):
     """The same pages back to FP8: zero scales, scales without a fast division, saturated
     and subnormal metadata; every byte as the oracle's."""
