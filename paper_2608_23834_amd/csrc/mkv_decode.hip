@@ -1161,8 +1161,9 @@ __global__ __launch_bounds__(64 * W) void decode_merge_kernel(int G, int H, int 
     for (int w = 0; w < W; ++w) {
       const float f = lw[w] > 0.0f ? exp2f(mw[w] - M) : 0.0f;
       L = fmaf(f, lw[w], L);
+      // (a wave of no weight is skipped like a slot of none: its sums may be infinite)
 #pragma unroll
-      for (int i = 0; i < NC; ++i) O[i] = fmaf(f, ow[w][i], O[i]);
+      for (int i = 0; i < NC; ++i) O[i] = fmaf(f, f != 0.0f ? ow[w][i] : 0.0f, O[i]);
     }
   }
   const int64_t row = (int64_t)r * Hq + h * G + n;

@@ -43,6 +43,29 @@ def test_merge_slots(d, slots):
     assert mk.kv_pool_check_errors(tw.gpu) == 0
 
 
+@pytest.mark.parametrize("d", [128, 256])
+@pytest.mark.parametrize("pages,waves", [(70, 2), (200, 4), (500, 8)])
+def test_merge_of_huge_values_without_weight(d, pages, waves):
+    """The tokens of the first wave's slots have values near the largest fp32 number and
+    scores so low that their weight is zero: the wave's sums are infinite, and must not
+    reach the output (all ones)."""
+    import paper_2608_23834_amd as mk
+    n = 16 * pages
+    w = dataclasses.replace(wl.scaled(wl.workload(1 if d == 128 else 5), (n,), n_layers=1, name=f"huge-{pages}"),
+                            n_q_heads=3, n_kv_heads=1)
+    tw = Twin(w, lens=[n], recent=1 << 20)
+    slots = -(-3 * pages // 32)  # 3 cost units per page, 32 per chunk
+    first = -(-32 * (-(-slots // waves)) // 3)  # pages of the first wave's slots
+    low = (np.arange(n) < 16 * first)[:, None, None]
+    k = np.broadcast_to(np.where(low, -8.0, 8.0), (n, 1, d)).astype(np.float32)
+    v = np.broadcast_to(np.where(low, 3.3e38, 1.0), (n, 1, d)).astype(np.float32)
+    tw.append([n], layer_kv=(wl.bf16_round(k)[None], wl.bf16_round(v)[None]))
+    r = tw.decode(q=wl.bf16_round(np.full((1, 3, d), 1.0, np.float32)))
+    print(f"d {d}, {pages} pages: {r['out'].min()} to {r['out'].max()}", flush=True)
+    assert max_abs(r["out"], 1.0) <= TOL and max_abs(r["out"], r["ref_out"]) <= TOL
+    assert mk.kv_pool_check_errors(tw.gpu) == 0
+
+
 def _pool(d, hq, hkv, recent):
     import paper_2608_23834_amd as mk
     return mk.Pool(1, hq, hkv, d, 1, 1, recent, np.ones(d, np.int8))
