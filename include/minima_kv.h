@@ -302,6 +302,12 @@ mkv_status paged_attn_decode_noalloc(mkv_pool* pool, int32_t layer, int32_t n_re
  * overlap so much that their 128-row blocks (ceil(n_r * group / 128) per
  * request) exceed ceil(n_q_total * group / 128) + n_req set the error word
  * and the call writes nothing to out.
+ * Row blocks of 128 (query, head) rows of a request are cut along their pages where
+ * the call has too few of them for the chip; where they are cut depends on all
+ * requests of the call and on the workspace's size, so a row can change with
+ * either, within its rounding error.  From call to call they are the same for the same inputs and
+ * workspace size; on a deterministic pool (below) no block is cut and a row's bits
+ * depend on its own request only.
  * (The paper runs prefill on a generic dense path, Sec. 4.1; this variant
  * keeps the mixed pages and uses MFMA for the dense contraction.) */
 mkv_status paged_attn_chunk(mkv_pool* pool, int32_t layer, int32_t n_req, const uint16_t* q,
@@ -387,9 +393,11 @@ mkv_status kv_pool_counters(mkv_pool* pool, mkv_counters* out);
  * wave of a split a fixed list of stages (wave w: stages w, w + NW, ...)
  * instead of claiming them at run time, so out and lse are bit-identical from
  * call to call for the same inputs (otherwise they can differ in the last
- * bits, by fp32 summation order).  Off by default: the fixed schedule balances
- * the waves of a SIMD less well.  Takes effect for calls enqueued after it;
- * part of the cohort key. */
+ * bits, by fp32 summation order); paged_attn_chunk, which is so in either case,
+ * leaves its row blocks whole, so that a row does not depend on the other
+ * requests of the call.  Off by default: the fixed schedule balances the waves
+ * of a SIMD less well, and whole blocks leave CUs idle in small chunk calls.
+ * Takes effect for calls enqueued after it; part of the cohort key. */
 mkv_status paged_attn_set_deterministic(mkv_pool* pool, int32_t enable);
 
 /* Kernel timing for measurement tools; correct use never needs it.  When

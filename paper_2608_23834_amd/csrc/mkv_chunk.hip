@@ -1596,7 +1596,9 @@ hipError_t launch_chunk(const PoolView& P, int layer, int n_req, const uint16_t*
   // the query ranges do not overlap
   const int blocks = (int)chunk_blocks(n_q_total, P.group) + n_req;
   const int share = cu_share(P.n_kv_heads);
-  const bool cut = wl.n_parts > 0 && chunk_may_cut(n_q_total, P.group, P.n_kv_heads);
+  // (where the cut falls depends on every request of the call; deterministic pools keep
+  // a row's bits to its own request)
+  const bool cut = !P.deterministic && wl.n_parts > 0 && chunk_may_cut(n_q_total, P.group, P.n_kv_heads);
   for (int b0 = 0; b0 < blocks; b0 += wl.n_items) {  // one turn where the workspace holds the call's items
     hipLaunchKernelGGL(chunk_plan_kernel, dim3(1), dim3(1024), 0, s, n_req, cu_q, n_q_total, seq_lens, max_pages,
                        P.group, blocks, b0, wl.n_items, share, cut ? 1 : 0, wl.n_parts, wl.stride, cum, rbo, hdr,

@@ -17,7 +17,7 @@ struct mkv_pool {
   uint64_t decode_routes, chunk_routes;
   hipEvent_t timing_ev[4];  // scan start and end, merge start and end (timing on)
   int timing, timed;
-  int deterministic;  // decode with a fixed stage schedule
+  int deterministic;  // decode with a fixed stage schedule, chunk blocks whole
 };
 
 namespace mkv {
@@ -38,7 +38,7 @@ struct PoolView {
   int32_t* last8;
   int32_t* last3;
   int n_layers, n_kv_heads, d, group, n_fp8, n_tq3, recent;
-  int deterministic;  // decode: fixed stage schedule instead of run-time claiming
+  int deterministic;  // decode: fixed stage schedule instead of run-time claiming; chunk: no block is cut
 };
 
 inline PoolView view_of(const mkv_pool* p) {

@@ -113,6 +113,36 @@ def test_chunk_many_requests(torch_cuda):
     _run(128, 2, 1, [(7 * r) % 40 for r in range(n)], [1 + r % 3 for r in range(n)], 16, tol=_bound)
 
 
+@pytest.mark.parametrize("d", [128, 256])
+def test_chunk_rows_without_the_other_requests(torch_cuda, d):
+    """On a deterministic pool the rows of a request are the same, bit for bit, alone and
+    beside the others of a call; otherwise its blocks are cut in other places, and both are
+    within the other tests' tolerance of the exact rows."""
+    import paper_2608_23834_amd as mk
+    lens, nq = [8200, 900, 5000, 64, 3000], [64, 33, 40, 64, 10]
+    w, t = _twin(d, 12, 2, lens, 256)
+    t.orc = None
+    t.fill_to(lens)
+    t.migrate(np.zeros((t.n_req, t.max_pages), np.uint8))
+    for fixed in (False, True):
+        mk.paged_attn_set_deterministic(t.gpu, fixed)
+        both = t.chunk(nq)
+        q = torch_cuda.from_numpy(both["q"].view(np.int16)).cuda()
+        for r in range(t.n_req):
+            a, b = both["cu"][r], both["cu"][r + 1]
+            out = torch_cuda.full((nq[r], 12, d), float("nan"), device="cuda")
+            mk.paged_attn_chunk(t.gpu, 0, q[a:b].contiguous(), torch_cuda.tensor([0, nq[r]], dtype=torch_cuda.int32, device="cuda"),
+                                t.bt[r:r + 1].contiguous(), t.tags[r:r + 1].contiguous(),
+                                torch_cuda.tensor(lens[r:r + 1], dtype=torch_cuda.int32, device="cuda"), out,
+                                mk.workspace(t.gpu, 1, t.max_pages, nq[r]))
+            alone = out.cpu().numpy()
+            off = float(np.max(np.abs(alone - both["out"][a:b])))
+            print(f"d{d} deterministic {fixed}: request {r} alone and beside the others: {off:.2e}", flush=True)
+            assert off == 0 if fixed else off <= 2 * TOL
+    mk.paged_attn_set_deterministic(t.gpu, False)
+    assert mk.kv_pool_check_errors(t.gpu) == 0
+
+
 def test_chunk_workspace_sizes(torch_cuda):
     """A workspace sized for more queries, requests or pages is never the smaller one."""
     import paper_2608_23834_amd as mk
