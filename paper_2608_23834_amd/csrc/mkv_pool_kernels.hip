@@ -1639,8 +1639,10 @@ __global__ __launch_bounds__(REL_NT) void pages_release_kernel(int n, const int3
       if (r < 0 || r >= n_req || (j > 0 && reqs[j - 1] >= r)) atomicOr(&s_err, (int)MKV_DEVERR_RANGE);
     }
     __syncthreads();
-    if (s_err) {
-      if (tid == 0) atomicOr(&P.ctrl[CTRL_ERR], s_err);
+    const int err = s_err;
+    __syncthreads();  // read by every wave before one finds a bad entry below
+    if (err) {
+      if (tid == 0) atomicOr(&P.ctrl[CTRL_ERR], err);
       return;
     }
   }

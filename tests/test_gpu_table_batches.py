@@ -56,3 +56,35 @@ def test_table_batches(n_req, max_pages):
         np.repeat(live, 2).astype(np.int32), np.repeat(tw.otags[0][:1], 2))))
     assert mk.kv_pool_check_errors(tw.gpu, clear=True) != 0
     check()
+
+
+@pytest.mark.parametrize("n_req,max_pages", [(4, 1024), (5, 1024)])
+def test_finish_of_a_bad_row(n_req, max_pages):
+    """Finish over rows of which one names a page outside the pool, or a free one (one batch
+    of entries, and two): the reference error alone, nothing changed, and the same rows
+    finish once they are sound."""
+    import paper_2608_23834_amd as mk
+    import torch
+    lens = [16 * max_pages] + [500] * (n_req - 1)
+    w = dataclasses.replace(wl.scaled(wl.workload(1), tuple(lens), n_layers=1, name=f"finish-{n_req}"),
+                            n_q_heads=1, n_kv_heads=1)
+    tw = Twin(w, lens=lens, recent=16)
+    tw.fill_to([n - 17 for n in lens])
+    tw.migrate(np.zeros((n_req, max_pages), np.uint8))
+    free = int(tw.orc.fp8_stack[0])
+    rows = torch.arange(n_req, dtype=torch.int32, device="cuda")
+    state = lambda: [x.clone() for x in (tw.bt, tw.tags, tw.gpu.ctrl[3:])]  # (but for the error word)
+    for at, bad in (((n_req - 1, 3), tw.n_tq3), ((0, max_pages - 1), free), ((0, 0), 1 << 30)):
+        keep, tag = int(tw.bt[at]), int(tw.tags[at])
+        tw.bt[at] = bad
+        if bad == free:
+            tw.tags[at] = 0
+        before = state()
+        for _ in range(10):
+            mk.kv_request_finish(tw.gpu, rows, tw.bt, tw.tags)
+            assert mk.kv_pool_check_errors(tw.gpu, clear=True) == mk.DEVERR["REFCOUNT"]
+        assert all(torch.equal(a, b) for a, b in zip(state(), before))
+        tw.bt[at], tw.tags[at] = keep, tag
+    tw.finish(list(range(n_req)))
+    tw.check_tables()
+    tw.check_refcounts()
