@@ -472,18 +472,18 @@ __global__ __launch_bounds__(DecodeCfg<PAIR>::NT, PAIR && D == 128 ? 4 : 2) void
     int id = pg_id[k];
     if (APP && holds && p0 + pi == p_new) {
       tg = TAG_R;
-      if (id < 0) id = 0;  // fresh: placeholder until the append wave has popped the id
+      // placeholder: a fresh page's until the append wave has popped the id, an
+      // out-of-range one's in a call that fails
+      if (id < 0 || id >= P.n_fp8) id = 0;
     }
-    const bool is3 = tg == TAG_S, is8 = (tg == TAG_R || tg == TAG_A);
+    bool is3 = tg == TAG_S, is8 = (tg == TAG_R || tg == TAG_A);
     if (wid == 0 && pi < n_pg && !is3 && !is8) atomicOr(&P.ctrl[CTRL_ERR], (int)MKV_DEVERR_BAD_TAG);
-    int lp = p0 + pi;
     if ((is3 || is8) && (id < 0 || id >= (is3 ? P.n_tq3 : P.n_fp8))) {
-      // out-of-range physical id: read page 0 instead, mask every token
+      // out-of-range physical id: left out (no page can stand in where the pool has none)
       if (wid == 0) atomicOr(&P.ctrl[CTRL_ERR], (int)MKV_DEVERR_RANGE);
-      id = 0;
-      lp = MASK_LP;
+      is3 = is8 = false;
     }
-    pg_lp[k] = lp;
+    pg_lp[k] = p0 + pi;
     pg_id[k] = id;
     m3w[k] = __ballot(is3);
     m8w[k] = __ballot(is8);

@@ -1,4 +1,4 @@
-"""Decode workspaces and the decode merge at the edges of its shapes: as many chunk slots as one round of one
+"""Decode workspaces, pages outside the pool, and the decode merge at the edges of its shapes: as many chunk slots as one round of one
 wave, of two, four and eight waves takes, one more, a second round of eight waves;
 every slot filled, and most of them past the request's end.  Against the oracle with
 the tolerance of the other decode tests."""
@@ -41,6 +41,50 @@ def test_merge_slots(d, slots):
     err = max(max_abs(r["out"], r["ref_out"]), max_abs(r["lse"], r["ref_lse"]))
     assert np.all(np.isfinite(r["out"])) and err <= TOL
     assert mk.kv_pool_check_errors(tw.gpu) == 0
+
+
+@pytest.mark.parametrize("d,hq", [(128, 6), (256, 16), (256, 24)])
+def test_pages_outside_the_pool_are_left_out(d, hq):
+    """Ids outside the pool set the error word and are left out; page 0, here without valid
+    contents, does not stand in for them.  The bad pages are the last ones, so the shorter
+    request is the reference."""
+    import paper_2608_23834_amd as mk
+    import torch
+    n, keep = 700, 39  # pages 39 .. 42 go bad: TQ3 pages, then the last ones in FP8
+    w = dataclasses.replace(wl.scaled(wl.workload(1 if d == 128 else 5), (n,), n_layers=1, name=f"bad-{hq}"),
+                            n_q_heads=hq, n_kv_heads=2)
+    tw = Twin(w, lens=[n], recent=32)
+    tw.fill_to([n])
+    tw.migrate(np.zeros((1, tw.max_pages), np.uint8))
+    bt, tags = tw.obt.copy(), tw.otags
+    assert tags[0, keep] == 2 and tags[0, -1] == 0
+    good = tw.decode(seq_lens=[16 * keep])
+    live8, live3 = bt[0, :keep][tags[0, :keep] < 2], bt[0, :keep][tags[0, :keep] == 2]
+    free = lambda count, live: torch.from_numpy(np.setdiff1d(np.arange(count), live)).cuda()
+    tw.gpu.fp8_scales_view()[:, free(tw.n_fp8, live8)] = float("nan")
+    tw.gpu.tq3_view()[:, free(tw.n_tq3, live3), :, 12 * d:] = 0xFF
+    tw.orc = None
+    for bad in (-1, 1 << 30):
+        tw.bt[0, keep:] = bad
+        r = tw.decode()
+        assert mk.kv_pool_check_errors(tw.gpu, clear=True) == mk.DEVERR["RANGE"]
+        err = max(max_abs(r["out"], good["ref_out"]), max_abs(r["lse"], good["ref_lse"]))
+        print(f"d {d} heads {hq} id {bad}: {err:.2e}", flush=True)
+        assert np.all(np.isfinite(r["out"])) and err <= TOL
+
+
+def test_pool_without_tq3_pages():
+    """A Stale tag in a pool that holds no TQ3 page: left out, whatever follows it."""
+    import paper_2608_23834_amd as mk
+    w = dataclasses.replace(wl.scaled(wl.workload(1), (300,), n_layers=1, name="no-tq3"), n_q_heads=4, n_kv_heads=1)
+    tw = Twin(w, lens=[300], recent=1 << 20, n_tq3=0)
+    tw.fill_to([300])
+    good = tw.decode(seq_lens=[16 * 16])
+    tw.orc = None
+    tw.tags[0, 16:] = 2
+    r = tw.decode()
+    assert mk.kv_pool_check_errors(tw.gpu, clear=True) == mk.DEVERR["RANGE"]
+    assert max_abs(r["out"], good["ref_out"]) <= TOL and max_abs(r["lse"], good["ref_lse"]) <= TOL
 
 
 @pytest.mark.parametrize("d", [128, 256])
