@@ -141,9 +141,10 @@ size_t chunk_ws_least(int n_req, int max_pages) {
 // Page lists of a chunk call, one workgroup per request: the TQ3 and the FP8
 // pages in logical order, so entries 2 j and 2 j + 1 are pair j of their format
 // (an odd list ends with a masked page), and per logical page the counts of both
-// formats up to and including it.  Ids outside the pool become page 0 with every
-// token masked, and set the range error bit.  Four consecutive pages per thread,
-// one scan of both counts per 4,096 pages: the cost is round trips.
+// formats up to and including it.  Pages whose id lies outside their pool are left out
+// (a pool without TQ3 pages has no memory that could stand in), and set the range error
+// bit.  Four consecutive pages per thread, one scan of both counts per 4,096 pages: the
+// cost is round trips.
 constexpr int LIST_NT = 1024, LIST_KB = 4;
 __global__ __launch_bounds__(LIST_NT) void chunk_lists_kernel(const int32_t* bt, const uint8_t* tags,
                                                               int max_pages, int stride,
@@ -172,9 +173,19 @@ __global__ __launch_bounds__(LIST_NT) void chunk_lists_kernel(const int32_t* bt,
       id[j] = bt[i];
       if (p >= np) tg[j] = -1;
     }
+    bool is3[LIST_KB], is8[LIST_KB];
     int v = 0;
 #pragma unroll
-    for (int j = 0; j < LIST_KB; ++j) v += tg[j] == TAG_S ? 1 << 16 : (tg[j] == TAG_R || tg[j] == TAG_A) ? 1 : 0;
+    for (int j = 0; j < LIST_KB; ++j) {
+      is3[j] = tg[j] == TAG_S;
+      is8[j] = tg[j] == TAG_R || tg[j] == TAG_A;
+      if (tg[j] >= 0 && !is3[j] && !is8[j]) bad |= MKV_DEVERR_BAD_TAG;
+      if ((is3[j] || is8[j]) && (id[j] < 0 || id[j] >= (is3[j] ? n_tq3 : n_fp8))) {
+        bad |= MKV_DEVERR_RANGE;
+        is3[j] = is8[j] = false;
+      }
+      v += is3[j] ? 1 << 16 : is8[j] ? 1 : 0;
+    }
     int tot;
     const int pre = block_excl_scan(v, scratch, &tot);
     int r8 = b8 + (pre & 0xFFFF), r3 = b3 + (pre >> 16);
@@ -182,15 +193,8 @@ __global__ __launch_bounds__(LIST_NT) void chunk_lists_kernel(const int32_t* bt,
     for (int j = 0; j < LIST_KB; ++j) {
       const int p = c0 + LIST_KB * tid + j;
       if (tg[j] < 0) continue;
-      const bool is3 = tg[j] == TAG_S, is8 = tg[j] == TAG_R || tg[j] == TAG_A;
-      int2 e = make_int2(p, id[j]);
-      if (id[j] < 0 || id[j] >= (is3 ? n_tq3 : n_fp8)) {
-        if (is3 || is8) bad |= MKV_DEVERR_RANGE;
-        e = make_int2(CMASK_LP, 0);
-      }
-      if (is3) l3[r3++] = e;
-      else if (is8) l8[r8++] = e;
-      else bad |= MKV_DEVERR_BAD_TAG;
+      if (is3[j]) l3[r3++] = make_int2(p, id[j]);
+      if (is8[j]) l8[r8++] = make_int2(p, id[j]);
       cm[p] = make_int2(r8, r3);
       if (p == np - 1) {  // the masked partners of odd lists
         l8[r8] = make_int2(CMASK_LP, 0);
@@ -620,7 +624,8 @@ __device__ __forceinline__ void chunk_block(const ChunkArgs& a, int4 it0, int4 i
       else if (i < CSLOTS8) ready = st3 > 0 ? st3 + 2 : -1;
       else ready = st3 + (i - CSLOTS8) / 2 + 3;
       if (ready > pass) break;
-      // a masked page b reads page a (its weights are zero, its values have to be finite)
+      // a masked page b reads page a (its weights are zero, its values have to be finite);
+      // page a of a pair is never masked
       const int id_b = e_iss.z == CMASK_LP ? e_iss.y : e_iss.w;
       const bool first = i < 0 || !(i & 1);  // the first unit of its stage
       if (first) {

@@ -113,6 +113,63 @@ def test_chunk_many_requests(torch_cuda):
     _run(128, 2, 1, [(7 * r) % 40 for r in range(n)], [1 + r % 3 for r in range(n)], 16, tol=_bound)
 
 
+def _chunk_and_decode(torch, t, w, q):
+    """The last query of every request by the chunk call and by the decode, with the error
+    word of each."""
+    import paper_2608_23834_amd as mk
+    n, rows = t.n_req, torch.from_numpy(q.view(np.int16)).cuda()
+    cu = torch.arange(n + 1, dtype=torch.int32, device="cuda")
+    sl = torch.tensor(t.cur, dtype=torch.int32, device="cuda")
+    out = torch.full((n, w.n_q_heads, w.head_dim), float("nan"), device="cuda")
+    ref = out.clone()
+    mk.paged_attn_chunk(t.gpu, 0, rows, cu, t.bt, t.tags, sl, out, mk.workspace(t.gpu, n, t.max_pages, n))
+    e0 = mk.kv_pool_check_errors(t.gpu, clear=True)
+    mk.paged_attn_decode(t.gpu, 0, rows, t.bt, t.tags, sl, ref, None, mk.workspace(t.gpu, n, t.max_pages))
+    return out.cpu().numpy(), ref.cpu().numpy(), e0, mk.kv_pool_check_errors(t.gpu, clear=True)
+
+
+@pytest.mark.parametrize("d", [128, 256])
+def test_chunk_leaves_out_pages_outside_the_pool(torch_cuda, d):
+    """Ids outside the pool set the error word and are left out, as in the decode; page 0,
+    here without valid contents, does not stand in for them."""
+    import paper_2608_23834_amd as mk
+    w, t = _twin(d, 8, 2, [700, 333], 128)
+    t.orc = None
+    t.fill_to([700, 333])
+    t.migrate(np.zeros((2, t.max_pages), np.uint8))
+    bt, tags = t.bt.cpu().numpy(), t.tags.cpu().numpy()
+    for bad8, bad3 in ((t.n_fp8, t.n_tq3), (-5, -1), (1 << 30, 1 << 30)):
+        t.bt.copy_(torch_cuda.from_numpy(bt))
+        for r in range(2):
+            t.bt[r, int(np.argmax(tags[r] == 2))] = bad3       # the first of its format: page a of a pair
+            t.bt[r, int(np.argmax(tags[r] == 2)) + 5] = bad3
+            t.bt[r, int(np.argmax(tags[r] == 0))] = bad8
+            t.bt[r, int(np.argmax(tags[r] == 0)) + 1] = bad8
+        live = t.bt.cpu().numpy()
+        # contents that are no numbers where no live page lies
+        f8, f3 = ((np.setdiff1d(np.arange(n), live[m]), n) for n, m in ((t.n_fp8, tags < 2), (t.n_tq3, tags == 2)))
+        t.gpu.fp8_scales_view()[:, torch_cuda.from_numpy(f8[0]).cuda()] = float("nan")
+        t.gpu.tq3_view()[:, torch_cuda.from_numpy(f3[0]).cuda(), :, 12 * d:] = 0xFF
+        out, ref, e0, e1 = _chunk_and_decode(torch_cuda, t, w, wl.q_decode(w, 0)[:2])
+        assert e0 == e1 == mk.DEVERR["RANGE"]
+        assert np.isfinite(ref).all() and np.isfinite(out).all()
+        assert float(np.max(np.abs(out - ref))) <= TOL
+
+
+def test_chunk_pool_without_tq3_pages(torch_cuda):
+    """A Stale tag in a pool that holds no TQ3 page."""
+    import paper_2608_23834_amd as mk
+    w = dataclasses.replace(wl.workload(2), n_q_heads=8, n_kv_heads=2, head_dim=128, ctx=(300, 90), n_req=2,
+                            n_layers=1, recent=1 << 20)
+    t = Twin(w, lens=[300, 90], recent=1 << 20, n_tq3=0, with_oracle=False)
+    t.fill_to([300, 90])
+    t.tags[0, 3:5] = 2
+    t.tags[1, 0] = 2
+    out, ref, e0, e1 = _chunk_and_decode(torch_cuda, t, w, wl.q_decode(w, 0)[:2])
+    assert e0 == e1 == mk.DEVERR["RANGE"]
+    assert np.isfinite(out).all() and float(np.max(np.abs(out - ref))) <= TOL
+
+
 @pytest.mark.parametrize("d", [128, 256])
 def test_chunk_rows_without_the_other_requests(torch_cuda, d):
     """On a deterministic pool the rows of a request are the same, bit for bit, alone and
