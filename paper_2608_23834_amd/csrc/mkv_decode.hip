@@ -472,14 +472,13 @@ __global__ __launch_bounds__(DecodeCfg<PAIR>::NT, PAIR && D == 128 ? 4 : 2) void
     int id = pg_id[k];
     if (APP && holds && p0 + pi == p_new) {
       tg = TAG_R;
-      // placeholder: a fresh page's until the append wave has popped the id, an
-      // out-of-range one's in a call that fails
-      if (id < 0 || id >= P.n_fp8) id = 0;
+      if (id < 0) id = 0;  // fresh: placeholder until the append wave has popped the id
     }
     bool is3 = tg == TAG_S, is8 = (tg == TAG_R || tg == TAG_A);
     if (wid == 0 && pi < n_pg && !is3 && !is8) atomicOr(&P.ctrl[CTRL_ERR], (int)MKV_DEVERR_BAD_TAG);
     if ((is3 || is8) && (id < 0 || id >= (is3 ? P.n_tq3 : P.n_fp8))) {
-      // out-of-range physical id: left out (no page can stand in where the pool has none)
+      // out-of-range physical id: left out (no page can stand in where the pool has none).
+      // The page of the new token among them: the append then fails, and with it the call
       if (wid == 0) atomicOr(&P.ctrl[CTRL_ERR], (int)MKV_DEVERR_RANGE);
       is3 = is8 = false;
     }

@@ -73,6 +73,28 @@ def test_pages_outside_the_pool_are_left_out(d, hq):
         assert np.all(np.isfinite(r["out"])) and err <= TOL
 
 
+@pytest.mark.parametrize("d,hq", [(128, 6), (256, 16), (256, 24)])
+@pytest.mark.parametrize("n", [5, 700])
+def test_fused_append_to_a_page_outside_the_pool(d, hq, n):
+    """The page that the new token lands in has no valid id: the fused step fails as a whole
+    (range error, zero rows, nothing changed), whether or not the chunk holds other pages."""
+    import paper_2608_23834_amd as mk
+    import torch
+    w = dataclasses.replace(wl.scaled(wl.workload(1 if d == 128 else 5), (n, 90), n_layers=1, name=f"app-{hq}-{n}"),
+                            n_q_heads=hq, n_kv_heads=2)
+    tw = Twin(w, lens=[n, 90], recent=32, headroom=16)
+    tw.fill_to([n, 90])
+    tw.migrate(np.zeros((2, tw.max_pages), np.uint8))
+    tw.orc = None
+    tw.bt[0, n // 16] = tw.n_fp8
+    state = lambda: [x.clone() for x in (tw.bt, tw.tags, tw.gpu.ctrl[3:], tw.gpu.fp8, tw.gpu.fp8_scales, tw.gpu.tq3)]
+    before = state()
+    r = tw.decode_append()
+    assert mk.kv_pool_check_errors(tw.gpu, clear=True) == mk.DEVERR["RANGE"]
+    assert (r["out"] == 0).all() and np.isneginf(r["lse"]).all()
+    assert all(torch.equal(a, b) for a, b in zip(state(), before))
+
+
 def test_pool_without_tq3_pages():
     """A Stale tag in a pool that holds no TQ3 page: left out, whatever follows it."""
     import paper_2608_23834_amd as mk
