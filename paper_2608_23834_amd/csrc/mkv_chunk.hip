@@ -250,9 +250,23 @@ __global__ __launch_bounds__(1024) void chunk_plan_kernel(int n_req, const int32
     const bool ok = q0 >= 0 && q1 >= q0 && q1 <= n_q_total;
     return ok ? max(1, (int)(((int64_t)(q1 - q0) * group + NSW * 32 - 1) / (NSW * 32))) : 1;
   };
-  int sum = 0;
-  for (int r = ra; r < rb; ++r) sum += blocks(r);
+  int64_t sum64 = 0;
+  for (int r = ra; r < rb; ++r) sum64 += blocks(r);
+  // (a thread's sum stops at one more than `grid`: 1,024 of them fit an int for grids below
+  // 2^17, and for larger ones where a first scan, in units of 1,024 blocks, finds no more
+  // than the grid)
+  const int sum = (int)min(sum64, (int64_t)grid + 1);
   int nblk;
+  if (grid >= 1 << 17) {
+    block_excl_scan(sum >> 10, scratch, &nblk);
+    if ((int64_t)nblk << 10 > grid) {  // workgroup-uniform
+      if (tid == 0) {
+        atomicOr(err, (int)MKV_DEVERR_RANGE);
+        hdr[0] = hdr[1] = 0;
+      }
+      return;
+    }
+  }
   int base = block_excl_scan(sum, scratch, &nblk);
   const bool in_lds = n_req <= 1024;
   for (int r = ra; r < rb; ++r) {

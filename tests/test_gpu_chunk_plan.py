@@ -113,6 +113,27 @@ def test_chunk_many_requests(torch_cuda):
     _run(128, 2, 1, [(7 * r) % 40 for r in range(n)], [1 + r % 3 for r in range(n)], 16, tol=_bound)
 
 
+@pytest.mark.parametrize("n_q", [70_000, 540_000])
+def test_chunk_overlapping_ranges_of_many_requests(torch_cuda, n_q):
+    """Every second request claims all queries: 2^28 row blocks, and more than 2^31 where the
+    call may have 133,035.  The range error, and nothing is written."""
+    import paper_2608_23834_amd as mk
+    n_req, hq = 65535, 16
+    pool = mk.Pool(1, hq, 1, 128, 1, 1, 16, np.ones(128, np.int8))
+    cu = torch_cuda.zeros(n_req + 1, dtype=torch_cuda.int32, device="cuda")
+    cu[1::2] = n_q
+    q = torch_cuda.empty((n_q, hq, 128), dtype=torch_cuda.int16, device="cuda")
+    out = torch_cuda.full((n_q, hq, 128), 7.0, device="cuda")
+    bt = torch_cuda.zeros((n_req, 1), dtype=torch_cuda.int32, device="cuda")
+    tags = torch_cuda.zeros((n_req, 1), dtype=torch_cuda.uint8, device="cuda")
+    sl = torch_cuda.ones(n_req, dtype=torch_cuda.int32, device="cuda")
+    ws = mk.workspace(pool, n_req, 1, n_q)
+    mk.paged_attn_chunk(pool, 0, q, cu, bt, tags, sl, out, ws)
+    assert mk.kv_pool_check_errors(pool, clear=True) == mk.DEVERR["RANGE"]
+    assert bool((out == 7.0).all())
+    print(f"{n_q} queries claimed by {n_req // 2 + 1} requests: refused", flush=True)
+
+
 def _chunk_and_decode(torch, t, w, q):
     """The last query of every request by the chunk call and by the decode, with the error
     word of each."""
