@@ -693,11 +693,10 @@ __device__ __forceinline__ void chunk_block(const ChunkArgs& a, int4 it0, int4 i
     // diag(sigma)), times the softmax scale log2(e)/sqrt(d) (scores come out
     // in base 2) and a power-of-two row scale qsc that puts the row's
     // largest entry in [128, 256), as three E4M3 terms t0 + t1 + t2 (each
-    // the E4M3 rounding of what the earlier ones left; the remainder sits
-    // below E4M3's subnormal step, about 2^-17 of the largest entry).  B
-    // operand of the 32x32x64 fp8 MFMA: lane (li, lg) holds, for k-step s,
-    // channels 64 s + 32 lg + j (j < 32) of row rb + li; the key operand
-    // uses the same order.
+    // the E4M3 rounding of what the earlier ones left; the remainder is at
+    // most 2^-14 of an entry, or 2^-10 where that is more).  B operand of
+    // the 32x32x64 fp8 MFMA: lane (li, lg) holds, for k-step s, channels 64 s +
+    // 32 lg + j (j < 32) of row rb + li; the key operand uses the same order.
     v8i qt[3][NK8];
     float qinv;
     {

@@ -194,8 +194,9 @@ constexpr float M_INIT = -1.0e30f;
 // The rotated query enters the TQ3 score product as a sum of E4M3 terms,
 // q sc = t0 + t1 + t2 (each term the E4M3 rounding of what the previous ones
 // left; sc a power of two that puts the head's largest |q sc| in [128, 256)).
-// The residual is below E4M3's subnormal step 2^-9, i.e. about 2^-17 of the
-// head's largest entry.
+// What they leave of an entry is at most 2^-14 of it (each term leaves half a unit of
+// its four significant bits) or 2^-10, half E4M3's smallest step: 2^-15 of the head's
+// largest entry at most, and down to 2^-18 for small ones.
 constexpr int QF8_TERMS = 3;
 
 // Column layout of a score tile (and row layout of the PV accumulator).  With
