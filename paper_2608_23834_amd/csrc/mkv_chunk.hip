@@ -24,13 +24,14 @@
 //    hi + lo pairs, handed over in LDS;
 //  * four PV waves, wave v owning the 32-channel blocks 2v, 2v + 1 of all
 //    128 rows, hold O^T accumulators (32 channels x 32 rows per block and
-//    score wave), copy every page (direct HBM -> LDS copies into a ring) and the
-//    page lists, and compute O^T += V^T P^T on v_mfma_f32_32x32x16_f16 (M =
+//    score wave) and compute O^T += V^T P^T on v_mfma_f32_32x32x16_f16 (M =
 //    32 channels, N = 32 rows, K = the 16 tokens of one page; a lane's score
 //    outputs are exactly the 8 tokens per page its weight operand holds):
 //    values as exact fp16 operands (scale_hi * code, scale_lo * code), the
 //    zero term as one rank-2 product of the pages' zeros and weight sums,
 //    applying the rescale the score waves passed along first.
+// The pages and the page lists are copied (direct HBM -> LDS copies into a ring) by
+// the score waves at d = 256, by the PV waves at d = 128 (see COPY_PV).
 // Pass p (one barrier): the score waves issue pair p's product and finish
 // pair p - 1 while the PV waves take pair p - 2.  FP8 pairs: the score waves
 // score them on the f16 MFMA against the plain query (the fp8 MFMA keeps too
@@ -222,9 +223,9 @@ __global__ __launch_bounds__(LIST_NT) void chunk_lists_kernel(const int32_t* bt,
 // of the chip, estimates a round as U + CUT_COST (a part's own start, its
 // partial results' way through memory and the merge, measured) and takes the
 // best, or leaves the blocks whole where that is estimated as good.  Cost
-// units: 4 per pass, of either format (1.80 us per TQ3 pair and 1.87 per FP8 pair at
-// d = 256; with 3 per FP8 pair a 6,001-token prefill's twelve calls took 2,738 us,
-// now 2,688).
+// units: 4 per pass, of either format (2.02 us per TQ3 pair and 1.88 per FP8 pair at
+// d = 256, 1.31 and 1.54 at d = 128, one workgroup on every CU; with 3 per FP8 pair a
+// 6,001-token prefill's twelve calls took 2,738 us, with 4 2,688).
 // items: two int4 per work item, {request, block of the request, first TQ3 pair,
 // TQ3 pairs}, {first FP8 pair, FP8 pairs, part slot or -1, -}; splits: {request,
 // block of the request, first part slot, parts}.
@@ -448,7 +449,6 @@ __device__ __forceinline__ void chunk_block(const ChunkArgs& a, int4 it0, int4 i
   constexpr int NKS = D / 16;   // k-steps of the FP8-page score product (16 channels each)
   constexpr int NK8 = D / 64;   // k-steps of the TQ3 score product (64 channels each)
   constexpr int NMB = D / 32;   // 32-channel blocks of the output
-  constexpr int KPC = QQ / 8;   // FP8-page k-steps per channel quarter
   constexpr int R3 = (int)tq3_region_bytes(D);
   constexpr int R8 = (int)fp8_region_bytes(D);
   constexpr int STAGE = 2 * R3;       // a TQ3 page pair, or one FP8 page + its two scales
@@ -473,7 +473,6 @@ __device__ __forceinline__ void chunk_block(const ChunkArgs& a, int4 it0, int4 i
   // MFMA lane roles: li = lane % 32 (row of A, column of B and of the
   // output), lg = lane / 32 (k-slot group)
   const int li = lane & 31, lg = lane >> 5;
-  const int ln = lane & 15, l4 = lane >> 4;  // the copy layout's view of the lane
   const int G = P.group, H = P.n_kv_heads, Hq = H * G;
   const int mp = a.max_pages;
 
@@ -576,8 +575,9 @@ __device__ __forceinline__ void chunk_block(const ChunkArgs& a, int4 it0, int4 i
   // ---- the copies.  At d = 256 the PV waves' products bound a TQ3 pass, so the
   // score waves copy; at d = 128 they have half the products and the score waves'
   // chain of scores, softmax and weights bounds a pass, so the PV waves copy
-  // (measured per TQ3 pass: d = 256 1.93 us with the score waves copying, 2.09
-  // with the PV waves; d = 128 1.49 and 1.36).
+  // (per TQ3 and FP8 pass, one workgroup on every CU: d = 256 2.02 and 1.88 us with
+  // the score waves copying, 2.21 and 2.12 with the PV waves; d = 128 1.46 and 1.67,
+  // 1.31 and 1.54).
   constexpr bool COPY_PV = D == 128;
   const int cwv = wid % NSW;
   // This wave's share of a unit's copies: OPS_W whole KiB (TQ3: KiB w OPS_W ..

@@ -1,15 +1,16 @@
 // Mixed-format paged decode attention (Sec. 3.3, Eq. softmax-merge; Sec. 4.1
 // direct fused decode) for gfx950.
 //
-// One launch per layer.  Grid (chunk, KV head, request); one workgroup per CU (two
-// at d = 128 with at most 8 heads per KV head): 8 wave64s with one ring slot each when a KV head's query group has at most
-// 8 heads (two pages share a score tile), else 8 waves with two slots.  Chunks
-// are ranges of logical pages of equal cost: a page wholly outside the Recent
-// window costs 2 units, a Recent (FP8) page 3 (twice the bytes, and it goes
-// alone through a stage that takes a pair of TQ3 pages; measured on short ragged
-// requests at d = 128 and d = 256: 27.2 and 18.9 us per scan with 3 units, 28.5
-// and 19.5 with 4, 30.6 and 20.3 with 5); the unit count per chunk is chosen so
-// that the launch fills the chip (decode_fill).  Each workgroup
+// One launch per layer.  Grid (chunk, KV head, request); one workgroup per CU (two at
+// d = 128 with at most 8 heads per KV head): 8 wave64s with one ring slot each when a
+// KV head's query group has at most 8 heads (two pages share a score tile), else 8
+// waves with two slots.  Chunks are ranges of logical pages of equal cost: a page wholly
+// outside the Recent window costs 2 units, a Recent (FP8) page 3 (twice the bytes, and
+// it goes alone through a stage that takes a pair of TQ3 pages; 24 requests of 131 to
+// 3,977 tokens at d = 128 and 8 of 2,003 to 6,007, window 4,096, at d = 256: 25.3 and
+// 20.5 us per scan with 3 units, 26.6 and 22.8 with 4, 28.2 and 24.9 with 5); the unit
+// count per chunk is chosen so that the launch fills the chip (decode_fill).  Each
+// workgroup
 //  1. loads its chunk's tags and page ids and the request's length together,
 //     and meanwhile builds the query operands in LDS: the plain query as fp16
 //     (FP8 pages) and the rotated query q_rot = R q (exact algebra: k_hat =
@@ -128,7 +129,7 @@ __device__ inline int page_at_cost(int64_t c, int n_old) {
 // (256 CUs), two with d = 128 and the paired score layout, whose registers (128)
 // and LDS (49 KB) leave room for two on a CU.  Twice the waves keep more copies in
 // flight, and chunks half as long level out uneven requests (24 requests of 131
-// to 3,977 tokens, 8 KV heads: the scan takes 29.3 us instead of 39.5; at d = 256,
+// to 3,977 tokens, 8 KV heads: the scan takes 25.3 us instead of 38.2; at d = 256,
 // where one workgroup fits, two rounds of half the chunk take 20.1 instead of 12.9
 // us at 16 K tokens).
 constexpr int decode_fill(int d, int group) { return d == 128 && group <= 8 ? 512 : 256; }

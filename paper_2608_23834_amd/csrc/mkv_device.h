@@ -77,7 +77,7 @@ __host__ __device__ constexpr int64_t tq3_region_bytes(int d) { return 16LL * d 
 __host__ __device__ constexpr int chunk_bytes(int d) { return 3 * d / 32; }
 
 // Byte selector of the 4 codes of quad q (one code in the low 3 bits of each
-// byte) from the chunk's dwords D[].
+// byte) from the chunk's dwords D[].  (The encode's pack_quads is its inverse.)
 template <int NDW>
 __device__ __forceinline__ uint32_t quad_sel(const uint32_t* D, int q) {
   if (q < 2 * NDW) {
@@ -89,33 +89,9 @@ __device__ __forceinline__ uint32_t quad_sel(const uint32_t* D, int q) {
   return ((D[3 * p + 1] >> 7) & 0x01010101u) | ((D[3 * p + 2] >> 5) & 0x06060606u);
 }
 
-// Inverse of quad_sel: OR the 3-bit code into the chunk dwords.
-template <int NDW>
-__device__ __forceinline__ void quad_put(uint32_t* D, int q, int b, uint32_t code) {
-  if (q < 2 * NDW) {
-    D[q >> 1] |= code << (8 * b + 3 * (q & 1));
-    return;
-  }
-  int e = q - 2 * NDW, p = e >> 1;
-  if ((e & 1) == 0) {
-    D[3 * p] |= (code & 3u) << (8 * b + 6);
-    D[3 * p + 1] |= ((code >> 2) & 1u) << (8 * b + 6);
-  } else {
-    D[3 * p + 1] |= (code & 1u) << (8 * b + 7);
-    D[3 * p + 2] |= ((code >> 1) & 3u) << (8 * b + 6);
-  }
-}
-
 // TQ3 codebook levels as E4M3 bytes, code 0..7 ascending:
 // -2.25, -1.375, -0.75, -0.25, 0.25, 0.75, 1.375, 2.25
 constexpr uint32_t KLUT_LO = 0xA8B4BBC1u, KLUT_HI = 0x413B3428u;
-// integers 0..7 as E4M3 bytes (value codes)
-constexpr uint32_t VLUT_LO = 0x44403800u, VLUT_HI = 0x4E4C4A48u;
-// 64 * level^2 per code
-__device__ __forceinline__ int mu2x64(int c) {
-  const int t[8] = {324, 121, 36, 4, 4, 36, 121, 324};
-  return t[c];
-}
 
 // ---------------------------------------------------------------------------
 // Scalar conversions
@@ -132,12 +108,6 @@ __device__ __forceinline__ float e4m3_to_f32(uint32_t byte) {
 __device__ __forceinline__ uint32_t f32_to_e4m3(float x) {
   x = fminf(fmaxf(x, -448.0f), 448.0f);
   return (uint32_t)__builtin_amdgcn_cvt_pk_fp8_f32(x, 0.0f, 0, false) & 0xFFu;
-}
-// E4M3 byte times 512 as an exact integer.
-__device__ __forceinline__ int32_t e4m3_times_512(uint32_t b) {
-  int e = (b >> 3) & 15, m = b & 7;
-  int32_t v = e ? ((8 + m) << (e - 1)) : m;
-  return (b & 0x80u) ? -v : v;
 }
 
 // fp64 -> binary16, round to nearest even, saturating at +-65504 (stored
@@ -192,12 +162,6 @@ __device__ inline int block_excl_scan(int v, int* scratch, int* total) {
   *total = scratch[nw];
   __syncthreads();
   return res;
-}
-
-__device__ inline int block_sum(int v, int* scratch) {
-  int tot;
-  block_excl_scan(v, scratch, &tot);
-  return tot;
 }
 
 }  // namespace mkv
