@@ -520,7 +520,7 @@ __global__ __launch_bounds__(64) void append_step_kernel(PoolView P, int layer_s
 #pragma unroll
   for (int j = 0; j < EQ; ++j) {
     ent_id[j] = ent_bt[j];
-    const int sl = rank[j] < 64 ? __shfl(stk, rank[j] & 63, 64) : -1;
+    const int sl = __shfl(stk, rank[j] & 63, 64);  // by every lane: one that sat out could not be read
     if (fresh[j] && bad == 0) ent_id[j] = rank[j] < 64 ? sl : P.fp8_stack[top - 1 - rank[j]];
   }
   if (bad == 0 && task < n_tasks) {

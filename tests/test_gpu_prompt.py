@@ -66,6 +66,26 @@ def test_append_plan_sizes(torch_cuda, n_req, n):
     t.check_pages()
 
 
+@pytest.mark.parametrize("n_req", [65, 130, 200, 256])
+@pytest.mark.parametrize("every", [2, 3, 64])
+def test_small_append_of_many_fresh_pages(torch_cuda, n_req, every):
+    """One token to more than 64 requests, some of which need a fresh page and some not: the
+    64th fresh page falls inside a group of 64 requests."""
+    t = _twin(128, 1, [40] * n_req)
+    rng = np.random.default_rng(n_req + every)
+
+    def step(counts):
+        k = wl.bf16_round(_rows(rng, sum(counts), 1, 128))[None]
+        t.append(counts, layer_kv=(k, k[:, ::-1].copy()))
+        t.check_tables()
+        t.check_pages()
+        t.check_refcounts()
+
+    step([1 if r % every == 0 else 16 if r % 5 else 0 for r in range(n_req)])
+    for _ in range(2):
+        step([1] * n_req)
+
+
 @pytest.mark.parametrize("n_req", [257, 1024, 1025])
 def test_append_no_tokens(torch_cuda, n_req):
     """A call without new tokens, of more requests than a decode-step append takes:
