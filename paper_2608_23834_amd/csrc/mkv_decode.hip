@@ -1,8 +1,8 @@
 // Mixed-format paged decode attention (Sec. 3.3, Eq. softmax-merge; Sec. 4.1
 // direct fused decode) for gfx950.
 //
-// One launch per layer.  Grid (chunk, KV head, request); one workgroup per CU (two at
-// d = 128 with at most 8 heads per KV head): 8 wave64s with one ring slot each when a
+// One launch per layer.  Grid: chunks, KV heads, requests (order: decode_chunks_last); one
+// workgroup per CU (two at d = 128 with at most 8 heads per KV head): 8 wave64s with one ring slot each when a
 // KV head's query group has at most 8 heads (two pages share a score tile), else 8
 // waves with two slots.  Chunks are ranges of logical pages of equal cost: a page wholly
 // outside the Recent window costs 2 units, a Recent (FP8) page 3 (twice the bytes, and
@@ -133,6 +133,14 @@ __device__ inline int page_at_cost(int64_t c, int n_old) {
 // where one workgroup fits, two rounds of half the chunk take 20.1 instead of 12.9
 // us at 16 K tokens).
 constexpr int decode_fill(int d, int group) { return d == 128 && group <= 8 ? 512 : 256; }
+// Order of the workgroups: where two fit a CU, all requests' first chunks before their
+// second ones and so on, else the chunks of a (request, KV head) in a row.  With 257 to
+// 511 pairs the fill cuts each into a long chunk and a short one; in a row, the long ones
+// of the last pairs start when everything else has ended, while last, the short ones fill
+// the gaps (63 requests of 2,000 tokens, 8 KV heads: 38.7 us a call, 55.4 in a row, 40.2
+// with one chunk each; 64 of 131 to 3,977 tokens 45.2, 75.8 in a row).  Not at d = 256:
+// 64 requests of 4 to 64 K tokens took 1,260 us a step instead of 1,080.
+constexpr bool decode_chunks_last(int d, bool pair) { return d == 128 && pair; }
 // Units per chunk: about that many workgroups for the whole launch, never below
 // 16 old pages' worth and never spanning more than MAX_CHUNK_PAGES pages.  (Where the
 // partials come near the library's own scratch, MAX_CHUNK_PAGES sets the units: the
@@ -290,7 +298,9 @@ __global__ __launch_bounds__(DecodeCfg<PAIR>::NT, PAIR && D == 128 ? 4 : 2) void
   static_assert(NCH_OF(PAIR) * D * 4 <= SLOTS * 2 * (int)tq3_region_bytes(D),
                 "a wave's merged rows fit its own ring slot");
   const PoolView& P = a.P;
-  const int r = blockIdx.z, h = blockIdx.y, chunk = blockIdx.x;
+  constexpr bool LAST = decode_chunks_last(D, PAIR);
+  const int r = LAST ? blockIdx.y : blockIdx.z, h = LAST ? blockIdx.x : blockIdx.y;
+  const int chunk = LAST ? blockIdx.z : blockIdx.x;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wid = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int G = P.group, H = P.n_kv_heads, Hq = H * G;
@@ -1301,7 +1311,8 @@ hipError_t launch_decode(const PoolView& P, int layer, int n_req, const uint16_t
     if (e != hipSuccess) return e;
     if (dev >= 0 && dev < 64) attr_done[dev].fetch_or(bit);
   }
-  dim3 grid(sh.max_chunks, P.n_kv_heads, n_req);
+  const dim3 grid = decode_chunks_last(P.d, pair) ? dim3(P.n_kv_heads, n_req, sh.max_chunks)
+                                                : dim3(sh.max_chunks, P.n_kv_heads, n_req);
   dim3 mgrid(P.group, P.n_kv_heads, n_req);
   // with timing on, the events track each kernel's own start and end (the
   // dispatch's timestamps, not markers around the launch)
