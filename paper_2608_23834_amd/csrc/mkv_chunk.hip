@@ -81,6 +81,14 @@ static size_t al256(size_t b) { return (b + 255) / 256 * 256; }
 static int cu_share(int n_kv_heads) { return n_kv_heads >= 256 ? 1 : 256 / n_kv_heads; }
 constexpr int MAX_ITEMS = 512;  // 2 * cu_share at most
 constexpr int MAX_PARTS = 32;   // parts of one block at most
+// cost units of the plan (see chunk_plan_kernel): a pass of each format, a part beside
+// its passes, the least size of a part
+constexpr int COST3 = 4, COST8 = 4;
+constexpr int CUT_COST = 12 * COST3, MIN_PART = 4 * COST3;
+// No block is cut where the dearest one costs no more than this: a round of the smallest
+// parts is estimated at MIN_PART + CUT_COST, and whole blocks take one round of the
+// dearest where cut ones could take one, two where they take two.
+constexpr int CUT_FROM = MIN_PART + CUT_COST;
 static int64_t chunk_blocks(int n_q_total, int group) { return ((int64_t)n_q_total * group + NSW * 32 - 1) / (NSW * 32); }
 // Blocks are cut only where at least that many of them (the query ranges not
 // overlapping) leave room in two rounds.
@@ -122,8 +130,8 @@ static ChunkWs chunk_ws(int n_req, int max_pages, int n_q_total, int n_kv_heads,
   w.parts = w.items + al256((size_t)n_items * 2 * sizeof(int4));
   // a part holds at least one pass: short tables cannot be cut into many.  Blocks
   // are cut in small calls only, but what a small call can use, a large one reports
-  const int64_t passes = (max_pages + 1) / 2 + 1;
-  int64_t n_parts = 2LL * cu_share(n_kv_heads);
+  const int64_t passes = max_pages / 2 + 1;
+  int64_t n_parts = passes * (COST3 > COST8 ? COST3 : COST8) > CUT_FROM ? 2LL * cu_share(n_kv_heads) : 0;
   const int64_t most = blocks * (passes < MAX_PARTS ? passes : MAX_PARTS);
   if (n_parts > most) n_parts = most;
   const int64_t parts_fit = room < w.parts ? 0 : (int64_t)((room - w.parts) / chunk_part_bytes(n_kv_heads, d));
@@ -231,8 +239,6 @@ __global__ __launch_bounds__(LIST_NT) void chunk_lists_kernel(const int32_t* bt,
 // block of the request, first part slot, parts}.
 // The table holds n_items items from row block b0 on; a call whose blocks do not fit
 // comes in several launches, its blocks whole (cut blocks fit any table).
-constexpr int COST3 = 4, COST8 = 4;
-constexpr int CUT_COST = 12 * COST3, MIN_PART = 4 * COST3;
 __global__ __launch_bounds__(1024) void chunk_plan_kernel(int n_req, const int32_t* cu_q, int n_q_total,
                                                           const int32_t* seq_lens, int max_pages,
                                                           int group, int grid, int b0, int n_items, int share,
@@ -326,6 +332,17 @@ __global__ __launch_bounds__(1024) void chunk_plan_kernel(int n_req, const int32
   int total;
   block_excl_scan(cost, scratch, &total);  // its barriers also publish the blocks
   const int cmax = s_max;
+  if (cmax <= CUT_FROM) {  // workgroup-uniform
+    if (tid < nblk) {
+      items[2 * tid] = make_int4(s_r[tid], s_x[tid], 0, s_t3[tid]);
+      items[2 * tid + 1] = make_int4(0, s_f8[tid], -1, 0);
+    }
+    if (tid == 0) {
+      hdr[0] = nblk;
+      hdr[1] = 0;
+    }
+    return;
+  }
   // wave w tries size k = w % 8 for 1 + w / 8 rounds
   {
     const int R = 1 + (wv >> 3), room = min(R * share, max_slots);
